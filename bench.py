@@ -109,10 +109,15 @@ def solve_flops(wl):
     return tot
 
 
-SWEEP_SOURCES = ("paper_1503_02564_amd/csrc/swr_sweep_kernel.h", "paper_1503_02564_amd/csrc/swr_lane.h",
-                 "paper_1503_02564_amd/csrc/swr_sweep_static.hip",
-                 "paper_1503_02564_amd/csrc/swr_sweep_static_s02.hip",
-                 "paper_1503_02564_amd/csrc/swr_sweep_group.hip",
+SWEEP_SOURCES = ("paper_1503_02564_amd/csrc/swr_rows.h",
+                 "paper_1503_02564_amd/csrc/swr_sweep_rows_kernel.h",
+                 "paper_1503_02564_amd/csrc/swr_sweep_rows.hip",
+                 "paper_1503_02564_amd/csrc/swr_sweep_rows4.hip",
+                 "paper_1503_02564_amd/csrc/swr_sweep_rows1_reg.hip",
+                 "paper_1503_02564_amd/csrc/swr_sweep_rows1_lds.hip",
+                 "paper_1503_02564_amd/csrc/swr_sweep_rows2_reg.hip",
+                 "paper_1503_02564_amd/csrc/swr_sweep_rows2_lds.hip",
+                 "paper_1503_02564_amd/csrc/swr_lane.h",
                  "paper_1503_02564_amd/csrc/swr_sweep.hip",
                  "paper_1503_02564_amd/csrc/swr_common.h",
                  "paper_1503_02564_amd/csrc/swr_host.hip",
@@ -474,7 +479,7 @@ def main():
     n_launch = float(np.mean([i["n_sweep"] for i in infos]))
     t_sweep_ms = float(np.mean([i["t_sweep_ms"] for i in infos]))
     achieved = flops / (1e-3 * t_sweep_ms) / 1e12
-    roof = {"bound": "alu", "kernel": "sweep_kernel (with the far_old_kernel products between its launches)",
+    roof = {"bound": "alu", "kernel": "sweep_rows_kernel (with the far_old_kernel products between its launches)",
             "achieved": achieved,
             "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
             "traffic": measured_traffic(), "avg_launch_ms": t_sweep_ms / n_launch,
@@ -505,7 +510,7 @@ def main():
         s_sweep = float(np.mean([i["t_sweep_ms"] for i in sinfos]))
         s_launch = float(np.mean([i["n_sweep"] for i in sinfos]))
         s_ach = flops / (1e-3 * s_sweep) / 1e12
-        out["roofline_staged"] = {"bound": "alu", "kernel": "sweep_kernel", "achieved": s_ach,
+        out["roofline_staged"] = {"bound": "alu", "kernel": "sweep_rows_kernel", "achieved": s_ach,
                                   "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                                   "frac": s_ach / PEAK_FP64_TFLOPS, "avg_launch_ms": s_sweep / s_launch,
                                   "launches_per_solve": s_launch, "sweep_ms_per_solve": s_sweep,

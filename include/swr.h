@@ -151,7 +151,8 @@ typedef struct {
     double t_total_ms;  /* the whole call on the device, factorisation to u(T) */
     double t_sweep_ms;  /* static V, new algorithm: summed durations of the subdomain sweep
                            launches (impulse/d sweeps and final sweep) ... */
-    int n_sweep;        /* ... and their number (0 when not measured) */
+    int n_sweep;        /* ... and their number, counted per chunk width ceil((J_k + 1) / 64) (0 when
+                           not measured) */
     int inner_iters;    /* V_TIME / V_CUBIC with more interfaces than the causal solve takes:
                            total inner BiCGStab iterations spent applying P^{-1} (else 0) */
     const double* history; /* host array owned by the context, valid until the next call on it:
@@ -166,12 +167,12 @@ typedef struct {
  * bound; the GMRES restart changes the iterate, not the tolerance met). */
 typedef struct {
     int pipeline;     /* pipeline chunk of the static causal solve, 0 = staged */
-    int help_max;     /* S0^2 sweeps: launches of at most this many tasks give every task a
-                         second wave that sums the far boundary history */
+    int help_max;     /* S0^2 sweeps of V(t,x) and |u|^2: launches of at most this many tasks give
+                         every task a second wave that sums the far boundary history (static
+                         potentials form it on the matrix cores inside the sweep) */
     int restart;      /* GMRES restart length */
-    int pair_from;    /* static Robin / S0^2 sweeps: launches that fill the GPU with one-wave
-                         tasks run two tasks of one subdomain per wave from this chunk width
-                         (ceil((J_k + 1) / 64) nodes per lane) on; 9 = never (default) */
+    int pair_from;    /* 1 or more; kept and reported, no launch depends on it (the static sweep
+                         chooses how many tasks share a wave from the problem's sizes) */
     int graph;        /* static causal solve: 1 = from the second solve with the same potential,
                          output pointers and schedule, replay the whole solve as one HIP graph
                          captured on the context's streams (bitwise the same results; no
@@ -179,11 +180,7 @@ typedef struct {
     int check;        /* GMRES: read the inner residual estimates back every this many steps
                          (default 4); the iterate and the iteration count are those of a check
                          after every step, the steps between reads need no host round trip */
-    int group;        /* static Robin / S0^2 sweeps: launches that fill the GPU with one-wave
-                         tasks run up to this many tasks of one subdomain and one potential (the
-                         problems of a batch) as the waves of one workgroup, reading one LDS
-                         copy of the subdomain's factors; 1..8, 1 = one task per workgroup
-                         (default 4); bitwise the same results */
+    int group;        /* 1..8; as pair_from */
     double ms;        /* swr_tune: wall time of the chosen schedule's solve */
     int candidates;   /* swr_tune: schedules timed */
 } swr_schedule;
@@ -293,9 +290,8 @@ swr_status swr_interface_matvec(swr_ctx* ctx, const double* x, double* y);
 swr_status swr_set_potential(swr_ctx* ctx, const double* V);
 
 /* The autotuner: times candidate schedules (pipeline chunks 0, 128, 256, 512,
- * 1024 for the static causal solve; helper-wave bounds 0, 512, all for S0^2;
- * two-task waves from widths 1, 4 or never for static Robin / S0^2 sweeps;
- * graph replay on and off for the static causal solve; restarts 20, 30, 60,
+ * 1024 for the static causal solve; helper-wave bounds 0, 512, all for S0^2
+ * with V(t,x) or |u|^2; graph replay on and off for the static causal solve; restarts 20, 30, 60,
  * 120 and residual read-back periods 1, 4, 16 for GMRES and the V(t,x)
  * iteration) with full
  * solves of the caller's u0 [B][nx] (one warm-up and the best of two timed

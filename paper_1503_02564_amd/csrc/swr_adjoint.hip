@@ -193,9 +193,13 @@ __global__ __launch_bounds__(64) void adjoint_kernel(AdjArgs a) {
             const int jj = m0 / kWave + 1;
             const int nsf = max(0, nt - kWave * jj);
             cd uf[P];
-            const cd* ck = a.ckpt + (((size_t)tix * (a.Jc + 1) + jj) * a.pstride) * kWave + t;
+            // (stored by node)
+            const cd* ck = a.ckpt + (((size_t)tix * (a.Jc + 1) + jj) * a.pstride) * kWave;
 #pragma unroll
-            for (int q = 0; q < P; ++q) uf[q] = ck[q * kWave];
+            for (int q = 0; q < P; ++q) {
+                uf[q] = zero;
+                if (s + q < n) uf[q] = ck[s + q];
+            }
             cd lf = zero, rf = zero;
             if (act) {
                 if (fw_l) lf = fw_l[nsf + t];

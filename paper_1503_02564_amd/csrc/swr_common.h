@@ -231,18 +231,43 @@ constexpr int kLongMaxQ = 8192;
 // 176 ms with 512-step chunks)
 constexpr int kHelpMaxTasks = 512;
 constexpr int kPipeChunk = 256;
-// chunk width from which filled launches run two tasks per wave (a schedule
-// parameter; kMaxP + 1 = never).  Measured on the batched-uneven workload the
-// one-task sweep is bound by instruction issue, not by its dependency chain:
-// two tasks per wave take twice as long per step (widths 4-7: 14.1-16.2 ms
-// per launch of two-task waves against 10.3-12.8 ms of one-task waves for
-// the same tasks), so the default is never
+// schedule parameters of launch forms that no longer exist; still validated,
+// saved and reported (bounds and defaults)
 constexpr int kPairFrom = kMaxP + 1;
-// largest group of tasks (one subdomain, one potential) that run as the
-// waves of one workgroup sharing an LDS copy of their factor record, and the
-// default group size (a schedule parameter; 1 = one task per workgroup)
 constexpr int kGroupMax = 8;
 constexpr int kGroupDefault = 4;
+
+// Row form of the static sweep (swr_rows.h): the kernels, by rows per task,
+// whether interior coefficients are read from LDS, waves per workgroup, and
+// the widest instantiation
+struct RowsKind { int RW; bool lds; int waves, pmax; };
+constexpr int kRowsKinds = 5;
+constexpr RowsKind kRowsKind[kRowsKinds] = {{4, false, 1, 8}, {1, false, 1, 8}, {1, true, 2, 14},
+                                              {2, false, 1, 8}, {2, true, 2, 16}};
+constexpr int kRowLevels = 4;      // cyclic reduction levels inside a row of 16 lanes
+constexpr int kRowsMaxP = 16;      // nodes per lane of the widest instantiation (RW 1 and 2)
+
+__host__ __device__ constexpr int rows_borders(int RW) { return 2 * (RW - 1); }
+// fields of the record after the 4 (P - 1) interior ones: a_sep, c_sep, the
+// reduction's multipliers, 1 / B, the border weights
+__host__ __device__ constexpr int rows_tail(int RW) { return 2 + 2 * kRowLevels + 1 + rows_borders(RW); }
+__host__ __device__ constexpr int rows_fields(int P, int RW) { return 4 * (P - 1) + rows_tail(RW); }
+constexpr int kRowsRegs = 138;       // registers for u, y and the record when it is partly in LDS
+constexpr int kRowsLdsP = 9;         // widths from this on keep them in LDS
+// Tasks of a context (build sweeps and final sweep together, which overlap)
+// from which fewer rows per task pay.  Measured on solves of 32 to 256 subdomains
+// over 512 steps, S0^2 (ms per solve, fewer rows against four):
+//   up to 128 nodes, one row:   101 nodes, 2016 tasks 1.65 / 1.60, 4032 1.90 / 2.25, 4158 2.34 / 2.62
+//   up to 256 nodes, two rows:  201 nodes, 2110 tasks 2.25 / 2.09, 4158 2.56 / 2.87, 8254 3.28 / 4.54
+//   above, two rows from LDS:   351 nodes, 2110 tasks 2.69 / 2.17, 4158 3.10 / 3.07, 8254 3.95 / 4.96
+//   up to 224 nodes, one row from LDS against two in registers: 201 nodes,
+//   8254 tasks 3.67 / 3.43, 16510 6.53 / 6.81, 33022 11.0 / 11.6 (251 nodes:
+//   16.5 / 14.9, so not there: 16 slots per lane spill)
+// LDS forms want records shared by four tasks or more (one potential, batch >= 4).
+constexpr size_t kRowsFill1 = 2560;
+constexpr size_t kRowsFill1Lds = 12288;
+constexpr size_t kRowsFill2 = 3072;
+constexpr size_t kRowsFill2Lds = 4608;
 
 // S0^2: the time window is cut into super-chunks of this many steps for the
 // far history (the part of a block's far sum older than its super-chunk is
@@ -286,8 +311,6 @@ struct SweepArgs {
     cd* state;                   // [ntasks][2][P][64] u_n and v_n carried between launches
     const EndCoef* endc;         // TR_GEN: [nf][2] end coefficients (left, right)
     int help_max;                // S0^2: launches of at most this many tasks use the helper wave
-    const int2* pairs;           // two-task waves: [.] task indices (second -1 for a single)
-    const int2* groups;          // shared-factor workgroups: [.] (first task, task count)
     int pstride;                 // chunk-width stride of the per-task state and checkpoint
                                  // records (the context's largest width; a launch's own P may
                                  // be smaller: subdomains are grouped by width)
@@ -311,6 +334,10 @@ struct SweepArgs {
     // the far sums of the launch's super-chunk (null: the far sums run from
     // q = 0; the launch then need not end at a super-chunk boundary)
     const cd* far_old;
+    // row form of the static sweep: one entry per workgroup, (first task, tasks, nodes per lane, -)
+    const int4* items;
+    const cd* rfac;              // row-form records and their stride
+    size_t rstride;
 };
 
 // far_old_kernel: for the super-chunk starting at step C (> 0), every task
@@ -375,19 +402,17 @@ constexpr int kRedThreads = 256;
 hipError_t launch_factor(const FactorArgs& a, hipStream_t st);
 hipError_t launch_sweep(const SweepArgs& a, int trans, int vk, hipStream_t st, bool plain = false);
 hipError_t launch_sweep_static(const SweepArgs& a, int trans, hipStream_t st);
-hipError_t launch_sweep_static_s02(const SweepArgs& a, hipStream_t st);
 hipError_t launch_sweep_static_pade(const SweepArgs& a, hipStream_t st);
 // subdomains of more than 64 * kMaxP nodes (swr_sweep_long.hip): a.lq nodes per lane
 hipError_t launch_sweep_long(const SweepArgs& a, int trans, int vk, hipStream_t st);
 hipError_t launch_factor_long(const FactorArgs& a, int Q, hipStream_t st);
 hipError_t launch_sweep_time(const SweepArgs& a, int trans, hipStream_t st);
 hipError_t launch_sweep_cubic(const SweepArgs& a, int trans, hipStream_t st);
-// static potential, Robin or S0^2: a.ntasks waves of two tasks each, the
-// pairs a.pairs[a.task0 ..] (swr_sweep_pair.hip)
-hipError_t launch_sweep_pairs(const SweepArgs& a, int trans, hipStream_t st);
-// static potential, Robin or S0^2: a.ntasks workgroups of gsize waves, the
-// task groups a.groups[a.task0 ..] (swr_sweep_group.hip)
-hipError_t launch_sweep_groups(const SweepArgs& a, int trans, int gsize, hipStream_t st);
+// static potential, Robin or S0^2 (swr_sweep_rows*.hip): the workgroups a.items[0 .. nitems - 1] of
+// one kind, records a.fac with stride a.fstride; pmax: their widest
+hipError_t launch_sweep_rows(const SweepArgs& a, int kind, int trans, int nitems, int pmax, hipStream_t st);
+// row-form records of the subdomains with RW rows (a.Pk: P + 32 RW per subdomain)
+hipError_t launch_rows_factor(const FactorArgs& a, int RW, int pmax, hipStream_t st);
 // the old part of the S0^2 far sums of one super-chunk (swr_sweep.hip)
 hipError_t launch_far_old(const FarOldArgs& a, hipStream_t st);
 hipError_t launch_finalize_ut(int N, int nx, int B, const int* off, const cd* ends, cd* uT,

@@ -37,6 +37,7 @@ using namespace swr;
 struct Iface {
     cd* cols = nullptr;     // [nv][N][4][nt]
     cd* fac = nullptr;      // factor records [nv*N][fields][64]
+    cd* rfac = nullptr;     // row-form factor records [nv*N][rstride]
     cd* lfac = nullptr;     // long-chunk factor records [nv*N][fac_fields(Qmax)][64]
     Task* tasks = nullptr;  // impulse tasks
     int ntasks = 0;
@@ -62,10 +63,19 @@ struct Iface {
 // no longer runs with the registers and padded rows of the widest one.
 struct WidthRun {
     int P, start, count;
-    int pstart, pcount;   // its waves of two tasks in the list's pair table
-    // its workgroups of at most g tasks of one factor record in the list's
-    // group table of size g (g = 2 .. kGroupMax)
-    int gstart[kGroupMax + 1], gcount[kGroupMax + 1];
+};
+
+// Row form of the static sweep (swr_sweep_rows_kernel.h): the workgroups of a
+// task list that one kernel runs, whatever their widths.
+struct RowsRun {
+    int kind;             // RowsKind
+    int pmax;             // widest of them (LDS size)
+    int start, count;     // in the list's item table
+};
+struct RowsList {
+    std::vector<int4> host;
+    int4* dev = nullptr;
+    std::vector<RowsRun> runs;
 };
 
 struct swr_ctx {
@@ -99,10 +109,12 @@ struct swr_ctx {
     cd* dLwork = nullptr;     // [max tasks][lwrec]
     int* dPk = nullptr;
     std::vector<WidthRun> runs_build, runs_sub, runs_L0;
-    int2* dPairsB = nullptr;  // pair tables of the build and the per-(problem, subdomain) lists
-    int2* dPairsS = nullptr;
-    int2* dGroupsB[kGroupMax + 1] = {};   // group tables of the two lists, by group size
-    int2* dGroupsS[kGroupMax + 1] = {};
+    // row form: RW and P of every subdomain as P + 32 RW (0: another form), the
+    // record stride, and the workgroups of the three task lists
+    std::vector<int> rows;
+    int* dRows = nullptr;
+    size_t rstride = 0;
+    RowsList rows_build, rows_sub, rows_L0;
     int n_launch_sweep = 0;   // sweep kernel launches of the current call
     Iface L, L0;              // interface operator of V and of V = 0
     cd* dD = nullptr;
@@ -171,8 +183,8 @@ struct swr_ctx {
     // causal solve (0 = staged), S0^2 helper-wave task bound, GMRES restart
     int pipe_chunk = 0;
     int help_max = kHelpMaxTasks;
-    int pair_from = kPairFrom;   // two tasks per wave from this chunk width on (9: never)
-    int group = kGroupDefault;   // tasks of one factor record per workgroup (1: one per wave)
+    int pair_from = kPairFrom;   // kept and saved with the schedule; no launch depends on them
+    int group = kGroupDefault;
     int graph = 0;               // 1: capture the static causal solve once, replay it
     int gm_check = 4;            // GMRES: read the residual estimates back every this many steps
     double* dResHist = nullptr;  // GMRES: [restart][B] residual estimate after every inner step
@@ -394,6 +406,66 @@ static std::vector<cd> pade_coefficients(int m, double theta) {
     return out;
 }
 
+// ---------------------------------------------------------------------------
+// Row form of the static sweep: how many rows of 16 lanes a task of each
+// subdomain gets.  Fewer rows put more tasks in a wave and cost less per task
+// (each step's separator reduction, boundary terms and lane moves are shared by
+// the wave's tasks), but need more tasks to fill the GPU and more registers
+// per lane; wide tasks keep their interior coefficients in LDS, one copy per
+// workgroup, which wants tasks that share a record.  The choice depends on
+// the problem's sizes only, never on the schedule, so every schedule computes
+// the same bits.
+// ---------------------------------------------------------------------------
+static void rows_plan(swr_ctx* c, size_t ntasks, int sharing) {
+    c->rows.assign(c->N, 0);
+    c->rstride = 0;
+    const bool shared = sharing >= 4;
+    for (int k = 0; k < c->N; ++k) {
+        const int n = c->J[k] + 1;
+        if (n > kWave * kMaxP) continue;               // long-chunk sweep
+        int RW = 4;
+        if (n <= 128) {
+            if (ntasks >= kRowsFill1) RW = 1;
+        } else if (n <= 224 && shared && ntasks >= kRowsFill1Lds) {
+            RW = 1;
+        } else if (n <= 256) {
+            if (ntasks >= kRowsFill2) RW = 2;
+        } else if (shared && ntasks >= kRowsFill2Lds) {
+            RW = 2;
+        }
+        const int T = 16 * RW, P = (n + T - 1) / T;
+        c->rows[k] = P + 32 * RW;
+        c->rstride = std::max(c->rstride, (size_t)rows_fields(P, RW) * T);
+    }
+}
+
+// the workgroups of a task list (its order: width, then factor record).  A
+// workgroup takes the tasks of one width that fit its waves; with the record
+// in LDS, of one record.
+static void rows_items(const swr_ctx* c, const std::vector<Task>& list, RowsList& out) {
+    for (int kind = 0; kind < kRowsKinds; ++kind) {
+        RowsRun run{kind, 0, (int)out.host.size(), 0};
+        const RowsKind& rk = kRowsKind[kind];
+        const int cap = c->o.plain ? 1 : rk.waves * (4 / rk.RW);
+        for (size_t i = 0; i < list.size();) {
+            const int key = c->rows[list[i].k], P = key % 32;
+            if (key == 0 || key / 32 != rk.RW || (P >= kRowsLdsP) != rk.lds) { ++i; continue; }
+            size_t j = i + 1;
+            while (j < list.size() && (int)(j - i) < cap && c->rows[list[j].k] == key &&
+                   (!rk.lds || list[j].f == list[i].f))
+                ++j;
+            out.host.push_back(make_int4((int)i, (int)(j - i), P, 0));
+            run.pmax = std::max(run.pmax, P);
+            i = j;
+        }
+        run.count = (int)out.host.size() - run.start;
+        // widest first: the longest workgroups start first
+        std::stable_sort(out.host.begin() + run.start, out.host.end(),
+                         [](const int4& x, const int4& y) { return x.z > y.z; });
+        if (run.count) out.runs.push_back(run);
+    }
+}
+
 extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, double dt, double T,
                                 int vk, const double* V, int tr, double s_re, double s_im,
                                 const swr_opts* opts, void* stream, swr_ctx** out) {
@@ -465,9 +537,8 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     for (int b = 0; b < B; ++b)
         for (int k = 0; k < N; ++k) sub.push_back(Task{k, b, vof(c, b) * N + k, 0});
     // ordered by width, then by factor record, so that tasks sharing a record
-    // are neighbours; each run of a width is cut into waves of two tasks of
-    // one record (a record with an odd count leaves a single)
-    auto by_width = [c](std::vector<Task>& list, std::vector<WidthRun>& runs, std::vector<int2>* pairs) {
+    // are neighbours
+    auto by_width = [c](std::vector<Task>& list, std::vector<WidthRun>& runs) {
         std::stable_sort(list.begin(), list.end(), [c](const Task& x, const Task& y) {
             if (c->Pk[x.k] != c->Pk[y.k]) return c->Pk[x.k] > c->Pk[y.k];
             return x.f < y.f;
@@ -475,44 +546,22 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
         runs.clear();
         for (int i = 0; i < (int)list.size(); ++i) {
             const int P = c->Pk[list[i].k];
-            if (runs.empty() || runs.back().P != P) runs.push_back(WidthRun{P, i, 0, 0, 0});
+            if (runs.empty() || runs.back().P != P) runs.push_back(WidthRun{P, i, 0});
             ++runs.back().count;
         }
-        if (!pairs) return;
-        pairs->clear();
-        for (WidthRun& r : runs) {
-            r.pstart = (int)pairs->size();
-            for (int i = r.start; i < r.start + r.count;) {
-                const bool two = i + 1 < r.start + r.count && list[i + 1].f == list[i].f;
-                pairs->push_back(make_int2(i, two ? i + 1 : -1));
-                i += two ? 2 : 1;
-            }
-            r.pcount = (int)pairs->size() - r.pstart;
-        }
     };
-    // ... and, for every group size g, into workgroups of at most g tasks of
-    // one record
-    auto by_group = [](const std::vector<Task>& list, std::vector<WidthRun>& runs, std::vector<int2>* groups) {
-        for (int g = 2; g <= kGroupMax; ++g) {
-            groups[g].clear();
-            for (WidthRun& r : runs) {
-                r.gstart[g] = (int)groups[g].size();
-                for (int i = r.start; i < r.start + r.count;) {
-                    int j = i + 1;
-                    while (j < r.start + r.count && j - i < g && list[j].f == list[i].f) ++j;
-                    groups[g].push_back(make_int2(i, j - i));
-                    i = j;
-                }
-                r.gcount[g] = (int)groups[g].size() - r.gstart[g];
-            }
+    by_width(build, c->runs_build);
+    by_width(sub, c->runs_sub);
+    by_width(imp0, c->runs_L0);
+    if (tr == SWR_ROBIN || tr == SWR_S02) {
+        rows_plan(c, vk == SWR_V_STATIC ? build.size() + sub.size() : imp0.size(), vk == SWR_V_STATIC && nv == 1 ? B : 0);
+        if (vk == SWR_V_STATIC) {
+            rows_items(c, build, c->rows_build);
+            rows_items(c, sub, c->rows_sub);
+        } else {
+            rows_items(c, imp0, c->rows_L0);
         }
-    };
-    std::vector<int2> pairs_build, pairs_sub, groups_build[kGroupMax + 1], groups_sub[kGroupMax + 1];
-    by_width(build, c->runs_build, &pairs_build);
-    by_width(sub, c->runs_sub, &pairs_sub);
-    by_width(imp0, c->runs_L0, nullptr);
-    by_group(build, c->runs_build, groups_build);
-    by_group(sub, c->runs_sub, groups_sub);
+    }
     c->nBuild = (int)build.size();
     // default schedule; a tuning cache entry for this problem replaces it
     c->pipe_chunk = o.pipeline >= 0 ? o.pipeline : kPipeChunk;
@@ -547,12 +596,9 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     ALLOC(c->dEnds, (size_t)B * N * 2);
     ALLOC(c->dBuild, build.size());
     ALLOC(c->dSub, sub.size());
-    ALLOC(c->dPairsB, pairs_build.size());
-    ALLOC(c->dPairsS, pairs_sub.size());
-    for (int g = 2; g <= kGroupMax; ++g) {
-        ALLOC(c->dGroupsB[g], groups_build[g].size());
-        ALLOC(c->dGroupsS[g], groups_sub[g].size());
-    }
+    if (c->rstride) ALLOC(c->dRows, N);
+    for (RowsList* l : {&c->rows_build, &c->rows_sub, &c->rows_L0})
+        if (!l->host.empty()) ALLOC(l->dev, l->host.size());
     ALLOC(c->dD, vec);
     ALLOC(c->dG, vec);
     ALLOC(c->dG2, vec);
@@ -571,7 +617,10 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     c->L.tasks = c->dBuild;   // its impulse tasks lead the build list
     c->L.ntasks = (int)impulse_tasks(N, nv).size();
     if (vk == SWR_V_STATIC) {
-        ALLOC(c->L.fac, (size_t)nv * N * fields * kWave);
+        // (the row form's contexts hold the 64-lane records only once a
+        // gradient has been asked for)
+        if (c->rstride) ALLOC(c->L.rfac, (size_t)nv * N * c->rstride);
+        else ALLOC(c->L.fac, (size_t)nv * N * fields * kWave);
         ALLOC(c->L.cols, (size_t)nv * N * 4 * nt);
         if (c->Qlong) ALLOC(c->L.lfac, (size_t)nv * N * c->lfstride);
     }
@@ -581,6 +630,7 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
         c->L0.nv = 1;
         c->L0.ntasks = (int)imp0.size();
         ALLOC(c->L0.fac, (size_t)N * fields * kWave);
+        if (c->rstride) ALLOC(c->L0.rfac, (size_t)N * c->rstride);
         ALLOC(c->L0.cols, (size_t)N * 4 * nt);
         if (c->Qlong) ALLOC(c->L0.lfac, (size_t)N * c->lfstride);
         ALLOC(c->L0.tasks, imp0.size());
@@ -619,16 +669,10 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     HIPCHK(hipMemcpyAsync(c->dPk, c->Pk.data(), N * sizeof(int), hipMemcpyHostToDevice, c->st));
     HIPCHK(hipMemcpyAsync(c->dBuild, build.data(), build.size() * sizeof(Task), hipMemcpyHostToDevice, c->st));
     HIPCHK(hipMemcpyAsync(c->dSub, sub.data(), sub.size() * sizeof(Task), hipMemcpyHostToDevice, c->st));
-    HIPCHK(hipMemcpyAsync(c->dPairsB, pairs_build.data(), pairs_build.size() * sizeof(int2),
-                          hipMemcpyHostToDevice, c->st));
-    HIPCHK(hipMemcpyAsync(c->dPairsS, pairs_sub.data(), pairs_sub.size() * sizeof(int2),
-                          hipMemcpyHostToDevice, c->st));
-    for (int g = 2; g <= kGroupMax; ++g) {
-        HIPCHK(hipMemcpyAsync(c->dGroupsB[g], groups_build[g].data(), groups_build[g].size() * sizeof(int2),
-                              hipMemcpyHostToDevice, c->st));
-        HIPCHK(hipMemcpyAsync(c->dGroupsS[g], groups_sub[g].data(), groups_sub[g].size() * sizeof(int2),
-                              hipMemcpyHostToDevice, c->st));
-    }
+    if (c->dRows) HIPCHK(hipMemcpyAsync(c->dRows, c->rows.data(), N * sizeof(int), hipMemcpyHostToDevice, c->st));
+    for (RowsList* l : {&c->rows_build, &c->rows_sub, &c->rows_L0})
+        if (l->dev)
+            HIPCHK(hipMemcpyAsync(l->dev, l->host.data(), l->host.size() * sizeof(int4), hipMemcpyHostToDevice, c->st));
     if (c->L0.tasks)
         HIPCHK(hipMemcpyAsync(c->L0.tasks, imp0.data(), imp0.size() * sizeof(Task), hipMemcpyHostToDevice, c->st));
     HIPCHK(hipMemsetAsync(c->dZero, 0, vec * sizeof(cd), c->st));
@@ -704,7 +748,7 @@ static int ktr(const swr_ctx* c) {
     return c->tr == SWR_ROBIN ? TR_ROBIN : (c->tr == SWR_S02 ? TR_S02 : TR_GEN);
 }
 
-static SweepArgs sweep_args(swr_ctx* c, const Task* tasks, int ntasks, const cd* fac, cd* cols) {
+static SweepArgs sweep_args(swr_ctx* c, const Task* tasks, int ntasks, const Iface& I, cd* cols) {
     SweepArgs a{};
     a.N = c->N; a.nt = c->nt; a.B = c->B; a.nx = c->nx; a.ns = c->ns; a.ntasks = ntasks;
     a.P = c->P;
@@ -712,7 +756,7 @@ static SweepArgs sweep_args(swr_ctx* c, const Task* tasks, int ntasks, const cd*
     a.h = c->h;
     a.sigma = c->sigma;
     a.c2 = c->c2;
-    a.J = c->dJ; a.off = c->dOff; a.tasks = tasks; a.fac = fac; a.beta = c->dBeta;
+    a.J = c->dJ; a.off = c->dOff; a.tasks = tasks; a.fac = I.fac; a.beta = c->dBeta;
     a.cols = cols; a.hist = c->dHist; a.ends = c->dEnds; a.maxdiff = c->dMax;
     a.endc = c->dEndc;
     a.tr = c->tr;
@@ -730,7 +774,9 @@ static SweepArgs sweep_args(swr_ctx* c, const Task* tasks, int ntasks, const cd*
     a.help_max = c->help_max;
     a.pstride = c->P;
     a.fstride = (size_t)fac_fields(c->P) * kWave;
-    a.lfac = fac == c->L.fac ? c->L.lfac : (fac == c->L0.fac ? c->L0.lfac : nullptr);
+    a.rfac = I.rfac;
+    a.rstride = c->rstride;
+    a.lfac = I.lfac;
     a.lfstride = c->lfstride;
     a.lwork = c->dLwork;
     a.lq = 0;
@@ -741,11 +787,11 @@ static SweepArgs sweep_args(swr_ctx* c, const Task* tasks, int ntasks, const cd*
     return a;
 }
 
-// factor records of a static potential (V = null: zero potential)
-static swr_status run_factor(swr_ctx* c, const double* V, int nv, cd* fac) {
+// 64-lane factor records of a static potential (V = null: zero potential)
+static swr_status run_factor64(swr_ctx* c, const double* V, int nv, Iface& I) {
     FactorArgs f{};
     f.N = c->N; f.nx = c->nx; f.nf = nv * c->N; f.P = c->P; f.h = c->h; f.dt = c->dt;
-    f.sigma = c->sigma; f.J = c->dJ; f.off = c->dOff; f.V = V; f.fac = fac;
+    f.sigma = c->sigma; f.J = c->dJ; f.off = c->dOff; f.V = V; f.fac = I.fac;
     f.tr = c->tr; f.c2 = c->c2; f.endc = c->dEndc;
     f.pade = c->dPade; f.pade_m = c->o.pade_m;
     f.Pk = c->dPk;
@@ -754,16 +800,15 @@ static swr_status run_factor(swr_ctx* c, const double* V, int nv, cd* fac) {
     std::vector<int> widths(c->Pk);
     std::sort(widths.begin(), widths.end());
     widths.erase(std::unique(widths.begin(), widths.end()), widths.end());
-    cd* lfac = fac == c->L.fac ? c->L.lfac : (fac == c->L0.fac ? c->L0.lfac : nullptr);
     for (int P : widths) {
         f.P = P;
         if (P <= kMaxP) {
-            HIPCHK(launch_factor(f, c->st));
+            if (I.fac) HIPCHK(launch_factor(f, c->st));
         } else {
             // long-chunk records (swr_sweep_long.hip)
-            if (!lfac) return SWR_EINVAL;
+            if (!I.lfac) return SWR_EINVAL;
             FactorArgs fl = f;
-            fl.fac = lfac;
+            fl.fac = I.lfac;
             fl.fstride = c->lfstride;
             HIPCHK(launch_factor_long(fl, P, c->st));
         }
@@ -771,12 +816,30 @@ static swr_status run_factor(swr_ctx* c, const double* V, int nv, cd* fac) {
     return SWR_OK;
 }
 
-// the factor records used by the per-(problem, subdomain) sweeps
-static const cd* main_fac(swr_ctx* c) { return c->vk == SWR_V_STATIC ? c->L.fac : c->L0.fac; }
+// the records that the sweeps of the operator's contexts read
+static swr_status run_factor(swr_ctx* c, const double* V, int nv, Iface& I, bool impulses) {
+    // (V(t,x) and |u|^2: the row form serves the impulse sweeps of L_0 only)
+    if (I.rfac && (c->vk == SWR_V_STATIC || impulses)) {
+        FactorArgs f{};
+        f.N = c->N; f.nx = c->nx; f.nf = nv * c->N; f.h = c->h; f.dt = c->dt;
+        f.sigma = c->sigma; f.J = c->dJ; f.off = c->dOff; f.V = V; f.fac = I.rfac;
+        f.Pk = c->dRows;
+        f.fstride = c->rstride;
+        int pmax[5] = {};
+        for (int key : c->rows) pmax[key / 32] = std::max(pmax[key / 32], key % 32);
+        for (int RW : {1, 2, 4})
+            if (pmax[RW]) HIPCHK(launch_rows_factor(f, RW, pmax[RW], c->st));
+        if (c->vk == SWR_V_STATIC && !c->Qlong) return SWR_OK;
+    }
+    return run_factor64(c, V, nv, I);
+}
+
+// the records used by the per-(problem, subdomain) sweeps
+static Iface& main_iface(swr_ctx* c) { return c->vk == SWR_V_STATIC ? c->L : c->L0; }
 
 // every (problem, subdomain) swept once with the fluxes io.g_in (null: zero)
 static SweepArgs sub_args(swr_ctx* c, const SweepIO& io) {
-    SweepArgs a = sweep_args(c, c->dSub, c->nSub, main_fac(c), nullptr);
+    SweepArgs a = sweep_args(c, c->dSub, c->nSub, main_iface(c), nullptr);
     a.u0 = io.u0;
     a.g_in = io.g_in ? io.g_in : c->dZero;
     a.g_out = io.g_out;
@@ -817,76 +880,49 @@ static cd* state_of(const swr_ctx* c, const Task* tasks) {
     return nullptr;
 }
 
-static const int2* pairs_of(const swr_ctx* c, const Task* tasks) {
-    if (tasks == c->dBuild) return c->dPairsB;
-    if (tasks == c->dSub) return c->dPairsS;
-    return nullptr;
+// the row-form workgroups of a task list
+static const RowsList& rows_of(const swr_ctx* c, const Task* tasks) {
+    if (tasks == c->dBuild) return c->rows_build;
+    if (tasks == c->dSub) return c->rows_sub;
+    return c->rows_L0;
 }
 
-static const int2* groups_of(const swr_ctx* c, const Task* tasks, int g) {
-    if (tasks == c->dBuild) return c->dGroupsB[g];
-    if (tasks == c->dSub) return c->dGroupsS[g];
-    return nullptr;
-}
-
-// largest group size at most g whose workgroup (the width-P factor record and
-// the waves' staging) fits the 64 KiB of LDS a workgroup may use by default
-static int group_fit(int P, int g) {
-    auto lds = [P](int q) {
-        return sizeof(cd) * ((size_t)fac_fields(P) * kWave + (size_t)q * 2 * kWave) +
-               sizeof(double) * (size_t)q * 2 * kWave + sizeof(double) * 2 * kWave;
-    };
-    while (g > 1 && lds(g) > 65536) --g;
-    return g;
-}
-
-// all tasks of a's list (a.task0 = 0, a.ntasks = the whole list), one launch
-// per chunk width, in order on one stream; *launches counts the kernels.  A
-// run that fills the GPU with one-wave tasks (more than help_max of them) of
-// a static potential with Robin or S0^2 runs two tasks per wave where it has
-// pairs from width pair_from on, else, with group >= 2 and tasks that share
-// factor records (two or more per record on average), workgroups of up to
-// group tasks of one record reading one LDS copy of it: the same arithmetic
-// per task in every form.
+// all tasks of a's list (a.task0 = 0, a.ntasks = the whole list), in order on
+// one stream; *launches counts them per chunk width (plain: per task).  Static
+// potential with Robin or S0^2: the row form, one launch for all widths of a
+// kind (plain: one per task).  Else one launch per chunk width.
 static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hipStream_t st, bool plain,
                                       int* launches) {
-    const int2* pairs = pairs_of(c, a.tasks);
     const int tr = ktr(c);
+    const bool rows = vk == SWR_V_STATIC && (tr == TR_S02 || tr == TR_ROBIN);
+    if (rows) {
+        const RowsList& l = rows_of(c, a.tasks);
+        SweepArgs r = a;
+        r.fac = a.rfac;
+        r.fstride = a.rstride;
+        for (const RowsRun& run : l.runs) {
+            r.items = l.dev + run.start;
+            const int per = plain ? 1 : run.count;
+            for (int i = 0; i < run.count; i += per, r.items += per) {
+                const hipError_t e = launch_sweep_rows(r, run.kind, tr, per, run.pmax, st);
+                if (e != hipSuccess) return e;
+            }
+        }
+    }
     for (const WidthRun& r : runs_of(c, a.tasks)) {
         a.P = r.P;
+        a.task0 = r.start;
+        a.ntasks = r.count;
+        hipError_t e;
         if (r.P > kMaxP) {
             // subdomains beyond 64 * kMaxP nodes: the long-chunk sweep, one launch
-            a.task0 = r.start;
-            a.ntasks = r.count;
             a.lq = r.P;
-            const hipError_t e = launch_sweep_long(a, tr, vk, st);
-            if (e != hipSuccess) return e;
-            if (launches) *launches += 1;
-            continue;
-        }
-        const bool two = !plain && pairs && vk == SWR_V_STATIC && (tr == TR_S02 || tr == TR_ROBIN) &&
-                         r.P >= c->pair_from && r.count > c->help_max && 4 * r.pcount <= 3 * r.count;
-        const int gsz = group_fit(r.P, c->group);
-        const bool grp = !two && !plain && gsz >= 2 && vk == SWR_V_STATIC && (tr == TR_S02 || tr == TR_ROBIN) &&
-                         r.count > c->help_max && groups_of(c, a.tasks, gsz) && 2 * r.gcount[gsz] <= r.count;
-        hipError_t e;
-        if (two) {
-            a.pairs = pairs;
-            a.task0 = r.pstart;
-            a.ntasks = r.pcount;
-            e = launch_sweep_pairs(a, tr, st);
-        } else if (grp) {
-            a.groups = groups_of(c, a.tasks, gsz);
-            a.task0 = r.gstart[gsz];
-            a.ntasks = r.gcount[gsz];
-            e = launch_sweep_groups(a, tr, gsz, st);
+            e = launch_sweep_long(a, tr, vk, st);
         } else {
-            a.task0 = r.start;
-            a.ntasks = r.count;
-            e = launch_sweep(a, tr, vk, st, plain);
+            e = rows ? hipSuccess : launch_sweep(a, tr, vk, st, plain);
         }
         if (e != hipSuccess) return e;
-        if (launches) *launches += plain ? r.count : 1;
+        if (launches) *launches += plain && r.P <= kMaxP ? r.count : 1;
     }
     return hipSuccess;
 }
@@ -942,7 +978,7 @@ static swr_status run_sweeps(swr_ctx* c, const SweepIO& io) {
 
 // static potential: impulse sweeps of L and the d sweeps in ONE launch
 static swr_status run_build(swr_ctx* c, const double* u0) {
-    SweepArgs a = sweep_args(c, c->dBuild, c->nBuild, c->L.fac, c->L.cols);
+    SweepArgs a = sweep_args(c, c->dBuild, c->nBuild, c->L, c->L.cols);
     a.u0 = reinterpret_cast<const cd*>(u0);
     a.g_in = c->dZero;
     a.g_out = c->dD;
@@ -953,8 +989,8 @@ static swr_status run_build(swr_ctx* c, const double* u0) {
 
 // impulse sweeps of the zero-potential operator L_0 (Sec. 5)
 static swr_status run_build_L0(swr_ctx* c) {
-    CHK(run_factor(c, nullptr, 1, c->L0.fac));
-    SweepArgs a = sweep_args(c, c->L0.tasks, c->L0.ntasks, c->L0.fac, c->L0.cols);
+    CHK(run_factor(c, nullptr, 1, c->L0, true));
+    SweepArgs a = sweep_args(c, c->L0.tasks, c->L0.ntasks, c->L0, c->L0.cols);
     a.g_in = c->dZero;
     HIPCHK(launch_widths(c, a, SWR_V_STATIC, c->st, c->o.plain));
     c->L0.dirty = true;
@@ -1524,7 +1560,7 @@ static swr_status run_static_pipelined(swr_ctx* c, const cd* u0, cd* g, const Sw
     HIPCHK(hipStreamWaitEvent(s2, ev_fork, 0));
     HIPCHK(hipStreamWaitEvent(s3, ev_fork, 0));
 
-    SweepArgs ab = sweep_args(c, c->dBuild, c->nBuild, c->L.fac, c->L.cols);
+    SweepArgs ab = sweep_args(c, c->dBuild, c->nBuild, c->L, c->L.cols);
     ab.u0 = u0;
     ab.g_in = c->dZero;
     ab.g_out = c->dD;
@@ -1610,7 +1646,7 @@ static bool graph_ready(const swr_ctx* c, const swr_ctx::GraphKey& key) {
 static swr_status enqueue_static_causal(swr_ctx* c, const cd* u0, cd* uT, cd* g, cd* utrace, cd* snaps) {
     const size_t vec = (size_t)c->B * c->ns * c->nt;
     hipStream_t st = c->st;
-    CHK(run_factor(c, c->dV, c->nv, c->L.fac));
+    CHK(run_factor(c, c->dV, c->nv, c->L, false));
     SweepIO io;
     io.u0 = u0; io.g_in = c->dG; io.g_out = c->dG2;
     io.uT = uT; io.trace = utrace; io.snaps = snaps;
@@ -1715,7 +1751,7 @@ extern "C" swr_status swr_solve(swr_ctx* c, const double* u0d, double* uT, doubl
     if (graph_ready(c, gkey)) return solve_graph(c, gkey, u0d, uT, g, utrace, snaps, info);
     HIPCHK(hipEventRecord(c->ev[0], st));
     // 1. assembly + factorisation
-    if (c->vk == SWR_V_STATIC) CHK(run_factor(c, c->dV, c->nv, c->L.fac));
+    if (c->vk == SWR_V_STATIC) CHK(run_factor(c, c->dV, c->nv, c->L, false));
     else CHK(run_build_L0(c));   // zero-potential factors + impulses of L_0
     HIPCHK(hipEventRecord(c->ev[1], st));
     const bool fixed = c->vk == SWR_V_STATIC && c->o.solver == SWR_SOLVER_FIXED;
@@ -1864,8 +1900,8 @@ extern "C" swr_status swr_solve(swr_ctx* c, const double* u0d, double* uT, doubl
 extern "C" swr_status swr_apply_R(swr_ctx* c, const double* u0, const double* g_in, double* g_out,
                                   double* uT, double* maxdiff) {
     if (!c || !g_in || !g_out) return SWR_EINVAL;
-    if (c->vk == SWR_V_STATIC) CHK(run_factor(c, c->dV, c->nv, c->L.fac));
-    else CHK(run_factor(c, nullptr, 1, c->L0.fac));
+    if (c->vk == SWR_V_STATIC) CHK(run_factor(c, c->dV, c->nv, c->L, false));
+    else CHK(run_factor(c, nullptr, 1, c->L0, false));
     SweepIO io;
     io.u0 = reinterpret_cast<const cd*>(u0);
     io.g_in = reinterpret_cast<const cd*>(g_in);
@@ -1890,8 +1926,8 @@ extern "C" swr_status swr_apply_R_noalloc(swr_ctx* c, const double* u0, const do
     auto* word = reinterpret_cast<unsigned long long*>(base);
     cd* dEnds = reinterpret_cast<cd*>(base + 256);
     cd* dHist = dEnds + ends;
-    if (c->vk == SWR_V_STATIC) CHK(run_factor(c, c->dV, c->nv, c->L.fac));
-    else CHK(run_factor(c, nullptr, 1, c->L0.fac));
+    if (c->vk == SWR_V_STATIC) CHK(run_factor(c, c->dV, c->nv, c->L, false));
+    else CHK(run_factor(c, nullptr, 1, c->L0, false));
     SweepIO io;
     io.u0 = reinterpret_cast<const cd*>(u0);
     io.g_in = reinterpret_cast<const cd*>(g_in);
@@ -1996,11 +2032,8 @@ extern "C" swr_status swr_tune(swr_ctx* c, const double* u0, double budget_ms, s
     if (!c->dUT) ALLOC_LIVE(c->dUT, (size_t)c->B * c->nx);
     double* uT = reinterpret_cast<double*>(c->dUT);
     // candidate values (the current schedule first)
-    std::vector<int> pipes{c->pipe_chunk}, helps{c->help_max}, restarts{c->o.restart}, pairs{c->pair_from},
-        graphs{c->graph}, checks{c->gm_check}, groups{c->group};
-    if (c->vk == SWR_V_STATIC && c->tr <= SWR_S02)
-        for (int g : {1, 2, 4, 8})
-            if (std::find(groups.begin(), groups.end(), g) == groups.end()) groups.push_back(g);
+    std::vector<int> pipes{c->pipe_chunk}, helps{c->help_max}, restarts{c->o.restart}, graphs{c->graph},
+        checks{c->gm_check};
     if (c->o.solver == SWR_SOLVER_GMRES || c->vk == SWR_V_TIME)
         for (int q : {1, 4, 16})
             if (std::find(checks.begin(), checks.end(), q) == checks.end()) checks.push_back(q);
@@ -2008,26 +2041,20 @@ extern "C" swr_status swr_tune(swr_ctx* c, const double* u0, double budget_ms, s
     if (c->vk == SWR_V_STATIC && c->o.solver == SWR_SOLVER_CAUSAL)
         for (int p : {0, 128, 256, 512, 1024})
             if (p < c->nt && std::find(pipes.begin(), pipes.end(), p) == pipes.end()) pipes.push_back(p);
-    if (c->tr == SWR_S02)
+    if (c->tr == SWR_S02 && c->vk != SWR_V_STATIC)
         for (int h : {0, kHelpMaxTasks, 1 << 30})
             if (std::find(helps.begin(), helps.end(), h) == helps.end()) helps.push_back(h);
     if (c->o.solver == SWR_SOLVER_GMRES || c->vk == SWR_V_TIME)
         for (int m : {20, 30, 60, 120})
             if (std::find(restarts.begin(), restarts.end(), m) == restarts.end()) restarts.push_back(m);
-    if (c->vk == SWR_V_STATIC && c->tr <= SWR_S02)
-        for (int w : {1, 4, kMaxP + 1})
-            if (std::find(pairs.begin(), pairs.end(), w) == pairs.end()) pairs.push_back(w);
-    const int p0 = c->pipe_chunk, h0 = c->help_max, m0 = c->o.restart, w0 = c->pair_from, q0 = c->graph,
-              k0 = c->gm_check, g0 = c->group;
+    const int p0 = c->pipe_chunk, h0 = c->help_max, m0 = c->o.restart, q0 = c->graph, k0 = c->gm_check;
     double best = INFINITY;
-    int bp = p0, bh = h0, bm = m0, bw = w0, bq = q0, bk = k0, bg = g0, tried = 0;
+    int bp = p0, bh = h0, bm = m0, bq = q0, bk = k0, tried = 0;
     double spent = 0;
     auto t_now = [] { return std::chrono::steady_clock::now(); };
     const auto t_start = t_now();
     for (int m : restarts)
         for (int kc : checks)
-        for (int gz : groups)
-        for (int w : pairs)
         for (int q : graphs)
         for (int p : pipes)
             for (int h : helps) {
@@ -2035,10 +2062,8 @@ extern "C" swr_status swr_tune(swr_ctx* c, const double* u0, double budget_ms, s
                 c->pipe_chunk = p;
                 c->help_max = h;
                 c->o.restart = m;
-                c->pair_from = w;
                 c->graph = q;
                 c->gm_check = kc;
-                c->group = gz;
                 // warm-up (with a graph: the uncaptured solve, then the capture)
                 swr_status rs = swr_solve(c, u0, uT, nullptr, nullptr, nullptr, nullptr);
                 if (rs == SWR_OK && q) rs = swr_solve(c, u0, uT, nullptr, nullptr, nullptr, nullptr);
@@ -2053,24 +2078,22 @@ extern "C" swr_status swr_tune(swr_ctx* c, const double* u0, double budget_ms, s
                     ms = std::min(ms, std::chrono::duration<double, std::milli>(t_now() - t0).count());
                 }
                 ++tried;
-                if (ms < best) { best = ms; bp = p; bh = h; bm = m; bw = w; bq = q; bk = kc; bg = gz; }
+                if (ms < best) { best = ms; bp = p; bh = h; bm = m; bq = q; bk = kc; }
                 spent = std::chrono::duration<double, std::milli>(t_now() - t_start).count();
             }
     c->pipe_chunk = bp;
     c->help_max = bh;
     c->o.restart = bm;
-    c->pair_from = bw;
     c->graph = bq;
     c->gm_check = bk;
-    c->group = bg;
     if (chosen) {
         chosen->pipeline = bp;
         chosen->help_max = bh;
         chosen->restart = bm;
-        chosen->pair_from = bw;
+        chosen->pair_from = c->pair_from;
         chosen->graph = bq;
         chosen->check = bk;
-        chosen->group = bg;
+        chosen->group = c->group;
         chosen->ms = best;
         chosen->candidates = tried;
     }
@@ -2111,7 +2134,7 @@ extern "C" swr_status swr_get_schedule(const swr_ctx* c, swr_schedule* s) {
 extern "C" swr_status swr_build_interface(swr_ctx* c, const double* u0, double* cols, double* d) {
     if (!c || !u0) return SWR_EINVAL;
     if (c->vk == SWR_V_STATIC) {
-        CHK(run_factor(c, c->dV, c->nv, c->L.fac));
+        CHK(run_factor(c, c->dV, c->nv, c->L, false));
         CHK(run_build(c, u0));
         if (cols) HIPCHK(hipMemcpyAsync(cols, c->L.cols, (size_t)c->nv * c->N * 4 * c->nt * sizeof(cd),
                                         hipMemcpyDeviceToDevice, c->st));
@@ -2227,11 +2250,13 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
         ALLOC_LIVE(c->dWends, (size_t)c->B * c->N * 2);
         ALLOC_LIVE(c->dUT, (size_t)c->B * c->nx);
     }
+    if (!c->L.fac) ALLOC_LIVE(c->L.fac, (size_t)c->nv * c->N * fac_fields(c->P) * kWave);
     int it_f = 0, it_b = 0;
     // ---- forward: factor, impulses + d, interface solve, final sweep with
     //      checkpoints (the S0^2 boundary history of this sweep stays in dHist)
     HIPCHK(hipEventRecord(c->ev[0], st));
-    CHK(run_factor(c, c->dV, c->nv, c->L.fac));
+    CHK(run_factor(c, c->dV, c->nv, c->L, false));
+    CHK(run_factor64(c, c->dV, c->nv, c->L));   // the adjoint sweep's records
     swr_status rf = SWR_OK;
     if (pipelined(c)) {
         SweepIO io;

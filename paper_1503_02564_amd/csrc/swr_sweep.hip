@@ -29,7 +29,7 @@
 // added by the sweeping wave with one fused multiply-add per lane each.
 //
 // The kernel template itself is in swr_sweep_kernel.h; swr_sweep_static.hip,
-// swr_sweep_static_s02.hip, swr_sweep_time.hip and swr_sweep_cubic.hip
+// swr_sweep_time.hip and swr_sweep_cubic.hip
 // instantiate it.
 #include "swr_lane.h"
 

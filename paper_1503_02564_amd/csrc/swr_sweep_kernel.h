@@ -149,34 +149,18 @@ __device__ inline void gen_end_coef(int tr, double W, double dW, double dt, cd c
 // dependent (rows rebuilt and refactored every step from the streamed V rows)
 // or |u|^2 (V-free factors, inner fixed point of eq. AvMNL every step).
 // ---------------------------------------------------------------------------
-//
-// GRP: the workgroup's waves run a group of tasks that share one factor record
-// (one subdomain, one potential: the problems of a batch, the impulse tasks),
-// a.groups[task0 + blockIdx.x] = (first task, count); the record is copied
-// once into LDS and every wave's solve reads it from there instead of holding
-// it in VGPRs, which leaves room for more waves per SIMD.  The arithmetic is
-// the one-wave form's, term for term.  Dynamic LDS: the record, then per wave
-// the staging of the far history (2 * 64 complex + 2 * 64 doubles).
-template <int P, int TR, int VK, bool HELP = false, bool GRP = false>
-__global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void sweep_kernel(SweepArgs a) {
+template <int P, int TR, int VK, bool HELP = false>
+__global__ __launch_bounds__(sweep_threads(HELP)) void sweep_kernel(SweepArgs a) {
     static_assert(!HELP || TR == TR_S02, "the helper wave serves S0^2");
-    static_assert(!GRP || (!HELP && VK == VK_STATIC && (TR == TR_S02 || TR == TR_ROBIN)),
-                  "shared-factor groups: static potential, Robin or S0^2");
+    static_assert(VK != VK_STATIC || (TR == TR_GEN || TR == TR_PADE),
+                  "static potential with Robin or S0^2: the row form");
     __shared__ double sbeta[2 * kWave];       // beta_0 .. beta_127
     __shared__ cd ffa[2][kWave], ffb[2][kWave];   // S0^2: far sums from the helper wave
     __shared__ cd sha[kWave], shb[kWave];     // staged chunk of the boundary history
     __shared__ double sb[2 * kWave];          // beta window of that chunk
-    extern __shared__ cd sgrp[];              // GRP: factor record, then per-wave staging
-    constexpr int kFacN = fac_fields(P) * kWave;
     const int t = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x / kWave;     // 1: the S0^2 helper wave; GRP: the group member
-    int tix = a.task0 + blockIdx.x;         // task index (per-task buffers)
-    int gcount = 1;
-    if (GRP) {
-        const int2 g = a.groups[a.task0 + blockIdx.x];
-        gcount = g.y;
-        tix = g.x + min(wv, g.y - 1);
-    }
+    const int wv = threadIdx.x / kWave;     // 1: the S0^2 helper wave
+    const int tix = a.task0 + blockIdx.x;   // task index (per-task buffers)
     const Task task = a.tasks[tix];
     const int k = task.k, b = task.b, f = task.f;
     const int fl = (task.flags & a.flags_and) | a.flags_or;
@@ -187,27 +171,12 @@ __global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void
     const int lastl = (n - 1) / P;          // lane holding node n-1
     const cd zero = mk(0, 0);
 
-    if (GRP) {
-        // every task of the group has this record (f)
-        const cd* src = a.fac + (size_t)f * a.fstride;
-        for (int i = threadIdx.x; i < kFacN; i += blockDim.x) sgrp[i] = src[i];
-    }
-    if (TR == TR_S02 || TR == TR_GEN || GRP) {
-        if (wv == 0 && (TR == TR_S02 || TR == TR_GEN)) {
+    if (TR == TR_S02 || TR == TR_GEN) {
+        if (wv == 0) {
             sbeta[t] = a.beta[t];
             sbeta[kWave + t] = a.beta[kWave + t];
         }
         __syncthreads();
-    }
-    if (GRP && wv >= gcount) return;        // a short group: no later workgroup barrier
-    // this wave's staging of the far history
-    cd* wsha = sha;
-    cd* wshb = shb;
-    double* wsb = sb;
-    if (GRP) {
-        wsha = sgrp + kFacN + wv * 2 * kWave;
-        wshb = wsha + kWave;
-        wsb = reinterpret_cast<double*>(sgrp + kFacN + (blockDim.x / kWave) * 2 * kWave) + wv * 2 * kWave;
     }
     cd* Ha = a.hist ? a.hist + (size_t)tix * 2 * (nt + 1) : nullptr;
     cd* Hb = Ha ? Ha + (nt + 1) : nullptr;
@@ -323,7 +292,7 @@ __global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void
             vprev[q] = (s + q < n) ? Vt[(size_t)nbeg * a.nx + s + q] : 0.0;
             vnext[q] = (s + q < n) ? Vt[(size_t)(nbeg + 1) * a.nx + s + q] : 0.0;
         }
-    } else if (!GRP) {
+    } else {
         load_fac<P>(a.fac + (size_t)f * a.fstride + t, F);
     }
 
@@ -370,12 +339,6 @@ __global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void
     if ((TR == TR_S02 || TR == TR_GEN) && t == 0 && first) {
         Ha[0] = va0;
         Hb[0] = vb0;
-    }
-    // checkpoints for the adjoint: u at forward steps max(0, nt - 64 jj), jj = 1..Jc
-    cd* ck = (fl & T_CKPT) ? a.ckpt + ((size_t)tix * (a.Jc + 1) * a.pstride) * kWave + t : nullptr;
-    if (ck && first) {
-#pragma unroll
-        for (int q = 0; q < P; ++q) ck[((size_t)a.Jc * a.pstride + q) * kWave] = u[q];
     }
     // snapshots u_n, n = 0, stride, 2 stride, ...: interior nodes straight to
     // the output, the two end nodes to a side store (averaged across the
@@ -496,7 +459,7 @@ __global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void
                 fb = ffb[kb & 1][t];
             } else {
                 __threadfence_block();
-                far_sum_s02(a, Ha, Hb, n0, t, wsha, wshb, wsb, fa, fb, fo);
+                far_sum_s02(a, Ha, Hb, n0, t, sha, shb, sb, fa, fb, fo);
             }
             acc_a = fa + nxt_a;
             acc_b = fb + nxt_b;
@@ -584,9 +547,6 @@ __global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void
 
         for (int i = 0; i < nb; ++i) {
             const int nstep = n0 + 1 + i;
-            // GRP: read the LDS factor record anew every step (the compiler
-            // would otherwise keep it in VGPRs across the loop)
-            if (GRP) asm volatile("" ::: "memory");
             // implicit coefficients of this step's boundary rows and of the
             // exchange (static potential: constant)
             cd sgA_n = a.sigma, sgB_n = a.sigma, sgsA_n = a.sigma, sgsB_n = a.sigma;
@@ -779,8 +739,6 @@ __global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void
                 nl_worst = max(nl_worst, conv ? it : a.nl_maxit);
 #pragma unroll
                 for (int q = 0; q < P; ++q) vlast[q] = x[q];
-            } else if (GRP) {
-                lane_solve_with<P>(FacLds<P>{sgrp + t}, d, x);
             } else {
                 lane_solve<P>(F, d, x);
             }
@@ -788,11 +746,6 @@ __global__ __launch_bounds__(GRP ? kGroupMax * kWave : sweep_threads(HELP)) void
 #pragma unroll
             for (int q = 0; q < P; ++q) u[q] = mk(2.0 * x[q].x - u[q].x, 2.0 * x[q].y - u[q].y);
             if (snap && nstep % a.snap_stride == 0) put_snap(nstep);
-            if (ck && nstep < nt && ((nt - nstep) & (kWave - 1)) == 0) {
-                const int jj = (nt - nstep) / kWave;
-#pragma unroll
-                for (int q = 0; q < P; ++q) ck[((size_t)jj * a.pstride + q) * kWave] = u[q];
-            }
             const cd va = rdlane(x[0], 0);
             const cd vb = at_last(x);
             const cd sgA = sgsA_n;

@@ -1,0 +1,33 @@
+// swr_sweep_rows.hip -- launches the row form of the static sweep
+// (swr_sweep_rows_kernel.h), instantiated one kind per file.
+#include "swr_sweep_rows_kernel.h"
+
+namespace swr {
+
+hipError_t launch_sweep_rows4(const SweepArgs& a, int trans, int nitems, size_t lds, hipStream_t st);
+hipError_t launch_sweep_rows1_reg(const SweepArgs& a, int trans, int nitems, size_t lds, hipStream_t st);
+hipError_t launch_sweep_rows1_lds(const SweepArgs& a, int trans, int nitems, size_t lds, hipStream_t st);
+hipError_t launch_sweep_rows2_reg(const SweepArgs& a, int trans, int nitems, size_t lds, hipStream_t st);
+hipError_t launch_sweep_rows2_lds(const SweepArgs& a, int trans, int nitems, size_t lds, hipStream_t st);
+
+hipError_t launch_sweep_rows(const SweepArgs& a, int kind, int trans, int nitems, int pmax, hipStream_t st) {
+    if (nitems == 0) return hipSuccess;
+    if (kind < 0 || kind >= kRowsKinds || !a.items || !a.fac || (trans != TR_S02 && trans != TR_ROBIN))
+        return hipErrorInvalidValue;
+    const RowsKind& k = kRowsKind[kind];
+    if (pmax < 1 || pmax > k.pmax) return hipErrorInvalidValue;
+    if (trans == TR_S02 && (!a.hist || !a.beta)) return hipErrorInvalidValue;
+    if ((a.n_begin > 0 || a.n_end < a.nt) && !a.state) return hipErrorInvalidValue;
+    const size_t lds = sizeof(cd) * (kRowsBetaLds / 2 + (size_t)k.waves * kRowsWaveLds +
+                                     (k.lds ? (size_t)rows_fields(pmax, k.RW) * 16 * k.RW : 0));
+    switch (kind) {
+        case 0: return launch_sweep_rows4(a, trans, nitems, lds, st);
+        case 1: return launch_sweep_rows1_reg(a, trans, nitems, lds, st);
+        case 2: return launch_sweep_rows1_lds(a, trans, nitems, lds, st);
+        case 3: return launch_sweep_rows2_reg(a, trans, nitems, lds, st);
+        case 4: return launch_sweep_rows2_lds(a, trans, nitems, lds, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace swr

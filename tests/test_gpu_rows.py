@@ -1,0 +1,67 @@
+"""Row form of the static sweep: contexts with enough tasks run a subdomain on
+one or two rows of 16 lanes (two to four tasks per wave), interior coefficients
+in registers or in LDS.  One sweep at the edges of every form's widths against
+the oracle's sweep, element by element, and independence of the tasks of a wave."""
+import numpy as np
+import pytest
+
+from paper_1503_02564_amd import workloads as W
+from tests.gpu_util import make_problem, rel, say, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+# (label, J, B, potential per problem, transmission): node counts J + 1 at the
+# first and last of a width, fewer nodes than lanes, every width up to the
+# form's widest; batches that leave waves partly filled
+CASES = [
+    # 2560 tasks: one row, registers (up to 128 nodes)
+    ("one-row", [1, 2, 14, 15, 16, 30, 31, 32, 47, 62, 63, 64, 79, 95, 111, 126, 127], 101, False, W.S02),
+    ("one-row-robin", [3, 15, 16, 31, 46, 63, 64, 127], 251, False, W.ROBIN),
+    ("one-row-per-problem", [15, 40, 64, 100, 127], 257, True, W.S02),
+    # 3072 / 4608 tasks: two rows, registers (129 to 256 nodes) and LDS (above)
+    ("two-rows", [128, 129, 159, 160, 191, 223, 224, 255, 100], 191, False, W.S02),
+    ("two-rows-lds", [256, 257, 287, 288, 320, 383, 384, 416, 447, 480, 511], 223, False, W.S02),
+    ("two-rows-robin", [255, 300, 128, 511], 643, False, W.ROBIN),
+    # 12288 tasks: one row, LDS (129 to 224 nodes)
+    ("one-row-lds", [128, 143, 144, 159, 160, 175, 176, 191, 207, 208, 223], 571, False, W.S02),
+]
+
+
+@pytest.mark.parametrize("label,J,B,per_problem,trans", CASES, ids=[c[0] for c in CASES])
+def test_one_sweep_equals_the_oracle(dev, label, J, B, per_problem, trans):
+    import torch
+    import oracle as O
+    from paper_1503_02564_amd import swr
+    nt = 300          # a ragged last block of every block length; past one far-history super-chunk
+    wl = W.small_case(J=J, nt=nt, trans=trans, B=B, seed=5, a0=-10.0, b0=10.0)
+    Vs = None
+    if per_problem:
+        Vs = np.stack([(0.5 + b / B) * np.asarray(wl.V) for b in range(B)])
+        wl = W.Workload("pp", wl.a0, wl.b0, wl.J, wl.dt, wl.nt, W.V_STATIC, Vs, trans, wl.sigma, wl.u0)
+    rng = np.random.default_rng(9)
+    ns = 2 * len(J) - 2
+    g = rng.standard_normal((B, ns, nt)) + 1j * rng.standard_normal((B, ns, nt))
+    say("rows", label, "tasks", 2 * B * len(J))
+    pb = make_problem(wl, v_per_problem=per_problem)
+    gd = to_dev(g)
+    out = torch.zeros_like(gd)
+    uT = torch.zeros((B, wl.nx), dtype=torch.complex128, device=dev)
+    swr.swr_apply_R(pb.ctx, to_dev(wl.u0), gd, out, uT)
+    got = to_np(out)
+    for b in (0, 1, 2, 3, B // 2, B - 2, B - 1):
+        one = W.Workload("one", wl.a0, wl.b0, wl.J, wl.dt, wl.nt, W.V_STATIC,
+                         wl.V if Vs is None else Vs[b], trans, wl.sigma, wl.u0[b:b + 1])
+        uref, ref = O.local_solution(one, one.u0[0], g[b])
+        assert rel(got[b], ref) < 1e-12, (label, b)
+        assert rel(to_np(uT)[b], uref) < 1e-12, (label, b)
+    # a problem with a non-finite flux leaves the other tasks of its waves, and
+    # its own steps before it, as they were
+    gd[1, :, 40] = float("nan")
+    out2 = torch.zeros_like(gd)
+    swr.swr_apply_R(pb.ctx, to_dev(wl.u0), gd, out2, None)
+    keep = [b for b in range(B) if b != 1]
+    got2 = to_np(out2)
+    assert np.array_equal(got2[keep], got[keep])
+    assert np.array_equal(got2[1][:, :40], got[1][:, :40])
+    assert not np.isfinite(got2[1][:, 40]).any()
+    pb.close()
