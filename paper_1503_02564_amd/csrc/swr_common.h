@@ -252,6 +252,11 @@ __host__ __device__ constexpr int rows_borders(int RW) { return 2 * (RW - 1); }
 // reduction's multipliers, 1 / B, the border weights
 __host__ __device__ constexpr int rows_tail(int RW) { return 2 + 2 * kRowLevels + 1 + rows_borders(RW); }
 __host__ __device__ constexpr int rows_fields(int P, int RW) { return 4 * (P - 1) + rows_tail(RW); }
+// wide form: complex entries of a record
+constexpr int kWideMaxP = 12;
+__host__ __device__ constexpr size_t wide_record(int P, int NW) {
+    return (size_t)(4 * (P - 1) + rows_tail(4) + 4) * 64 * NW;
+}
 constexpr int kRowsRegs = 138;       // registers for u, y and the record when it is partly in LDS
 constexpr int kRowsLdsP = 9;         // widths from this on keep them in LDS
 // Tasks of a context (build sweeps and final sweep together, which overlap)
@@ -336,8 +341,10 @@ struct SweepArgs {
     const cd* far_old;
     // row form of the static sweep: one entry per workgroup, (first task, tasks, nodes per lane, -)
     const int4* items;
-    const cd* rfac;              // row-form records and their stride
+    const cd* rfac;              // row-form and wide-form records and their strides
     size_t rstride;
+    const cd* wfac;
+    size_t wstride;
 };
 
 // far_old_kernel: for the super-chunk starting at step C (> 0), every task
@@ -413,6 +420,11 @@ hipError_t launch_sweep_cubic(const SweepArgs& a, int trans, hipStream_t st);
 hipError_t launch_sweep_rows(const SweepArgs& a, int kind, int trans, int nitems, int pmax, hipStream_t st);
 // row-form records of the subdomains with RW rows (a.Pk: P + 32 RW per subdomain)
 hipError_t launch_rows_factor(const FactorArgs& a, int RW, int pmax, hipStream_t st);
+// static potential, Robin or S0^2, subdomains of more than 64 * kMaxP nodes
+// (swr_sweep_wide.hip): NW waves per task, P nodes per lane; records a.fac with
+// stride a.fstride (a.Pk of the factorisation: P + 32 NW per subdomain)
+hipError_t launch_sweep_wide(const SweepArgs& a, int trans, int NW, int P, hipStream_t st);
+hipError_t launch_wide_factor(const FactorArgs& a, int NW, hipStream_t st);
 // the old part of the S0^2 far sums of one super-chunk (swr_sweep.hip)
 hipError_t launch_far_old(const FarOldArgs& a, hipStream_t st);
 hipError_t launch_finalize_ut(int N, int nx, int B, const int* off, const cd* ends, cd* uT,

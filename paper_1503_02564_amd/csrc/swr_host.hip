@@ -39,6 +39,7 @@ struct Iface {
     cd* fac = nullptr;      // factor records [nv*N][fields][64]
     cd* rfac = nullptr;     // row-form factor records [nv*N][rstride]
     cd* lfac = nullptr;     // long-chunk factor records [nv*N][fac_fields(Qmax)][64]
+    cd* wfac = nullptr;     // wide-form factor records [nv*N][wstride]
     Task* tasks = nullptr;  // impulse tasks
     int ntasks = 0;
     int nv = 1;
@@ -115,6 +116,12 @@ struct swr_ctx {
     int* dRows = nullptr;
     size_t rstride = 0;
     RowsList rows_build, rows_sub, rows_L0;
+    // wide form (swr_sweep_wide.hip): NW and P of every subdomain as P + 32 NW
+    // (0: another form) and the record stride
+    std::vector<int> wide;
+    int* dWide = nullptr;
+    size_t wstride = 0;
+    bool stream_static = false;   // static sweeps with subdomains past the wide form's sizes
     int n_launch_sweep = 0;   // sweep kernel launches of the current call
     Iface L, L0;              // interface operator of V and of V = 0
     cd* dD = nullptr;
@@ -416,13 +423,27 @@ static std::vector<cd> pade_coefficients(int m, double theta) {
 // the problem's sizes only, never on the schedule, so every schedule computes
 // the same bits.
 // ---------------------------------------------------------------------------
+// Wide form: waves per task for a subdomain of at most 64 Pk nodes (Pk > kMaxP),
+// 0 past its sizes.  More waves than needed for 5 to 9 nodes per lane only add
+// exchanges; fewer would not hold the state in registers.
+static int wide_waves(int Pk) { return Pk <= 18 ? 2 : Pk <= 36 ? 4 : Pk <= 8 * kWideMaxP ? 8 : 0; }
+
 static void rows_plan(swr_ctx* c, size_t ntasks, int sharing) {
     c->rows.assign(c->N, 0);
-    c->rstride = 0;
+    c->wide.assign(c->N, 0);
+    c->rstride = c->wstride = 0;
+    c->stream_static = false;
     const bool shared = sharing >= 4;
     for (int k = 0; k < c->N; ++k) {
         const int n = c->J[k] + 1;
-        if (n > kWave * kMaxP) continue;               // long-chunk sweep
+        if (n > kWave * kMaxP) {
+            const int NW = wide_waves(c->Pk[k]);
+            if (NW == 0) { c->stream_static = true; continue; }
+            const int P = (c->Pk[k] + NW - 1) / NW;
+            c->wide[k] = P + 32 * NW;
+            c->wstride = std::max(c->wstride, wide_record(P, NW));
+            continue;
+        }
         int RW = 4;
         if (n <= 128) {
             if (ntasks >= kRowsFill1) RW = 1;
@@ -574,10 +595,12 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     const size_t vec = (size_t)B * ns * nt;
     const size_t max_tasks = std::max(build.size(), std::max(sub.size(), imp0.size()));
     const int fields = fac_fields(c->P);
+    // the streaming sweep's arrays: V(t,x) and |u|^2, or what the wide form leaves
+    const bool streams = c->Qlong && (vk != SWR_V_STATIC || c->stream_static);
     if (c->Qlong) {
         c->lfstride = (size_t)fac_fields(c->Qlong) * kWave;
         c->lwrec = (size_t)(3 * c->Qlong + (vk == SWR_V_TIME ? fac_fields(c->Qlong) : 0)) * kWave;
-        ALLOC(c->dLwork, max_tasks * c->lwrec);
+        if (streams) ALLOC(c->dLwork, max_tasks * c->lwrec);
     }
     ALLOC(c->dJ, N);
     ALLOC(c->dOff, N);
@@ -597,6 +620,7 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     ALLOC(c->dBuild, build.size());
     ALLOC(c->dSub, sub.size());
     if (c->rstride) ALLOC(c->dRows, N);
+    if (c->wstride) ALLOC(c->dWide, N);
     for (RowsList* l : {&c->rows_build, &c->rows_sub, &c->rows_L0})
         if (!l->host.empty()) ALLOC(l->dev, l->host.size());
     ALLOC(c->dD, vec);
@@ -620,9 +644,10 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
         // (the row form's contexts hold the 64-lane records only once a
         // gradient has been asked for)
         if (c->rstride) ALLOC(c->L.rfac, (size_t)nv * N * c->rstride);
-        else ALLOC(c->L.fac, (size_t)nv * N * fields * kWave);
+        else if (tr > SWR_S02) ALLOC(c->L.fac, (size_t)nv * N * fields * kWave);
+        if (c->wstride) ALLOC(c->L.wfac, (size_t)nv * N * c->wstride);
         ALLOC(c->L.cols, (size_t)nv * N * 4 * nt);
-        if (c->Qlong) ALLOC(c->L.lfac, (size_t)nv * N * c->lfstride);
+        if (streams) ALLOC(c->L.lfac, (size_t)nv * N * c->lfstride);
     }
     // ... and of the zero potential (preconditioner; also the V-free factors
     // of the |u|^2 scheme)
@@ -631,6 +656,7 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
         c->L0.ntasks = (int)imp0.size();
         ALLOC(c->L0.fac, (size_t)N * fields * kWave);
         if (c->rstride) ALLOC(c->L0.rfac, (size_t)N * c->rstride);
+        if (c->wstride) ALLOC(c->L0.wfac, (size_t)N * c->wstride);
         ALLOC(c->L0.cols, (size_t)N * 4 * nt);
         if (c->Qlong) ALLOC(c->L0.lfac, (size_t)N * c->lfstride);
         ALLOC(c->L0.tasks, imp0.size());
@@ -669,6 +695,7 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     HIPCHK(hipMemcpyAsync(c->dPk, c->Pk.data(), N * sizeof(int), hipMemcpyHostToDevice, c->st));
     HIPCHK(hipMemcpyAsync(c->dBuild, build.data(), build.size() * sizeof(Task), hipMemcpyHostToDevice, c->st));
     HIPCHK(hipMemcpyAsync(c->dSub, sub.data(), sub.size() * sizeof(Task), hipMemcpyHostToDevice, c->st));
+    if (c->dWide) HIPCHK(hipMemcpyAsync(c->dWide, c->wide.data(), N * sizeof(int), hipMemcpyHostToDevice, c->st));
     if (c->dRows) HIPCHK(hipMemcpyAsync(c->dRows, c->rows.data(), N * sizeof(int), hipMemcpyHostToDevice, c->st));
     for (RowsList* l : {&c->rows_build, &c->rows_sub, &c->rows_L0})
         if (l->dev)
@@ -776,6 +803,8 @@ static SweepArgs sweep_args(swr_ctx* c, const Task* tasks, int ntasks, const Ifa
     a.fstride = (size_t)fac_fields(c->P) * kWave;
     a.rfac = I.rfac;
     a.rstride = c->rstride;
+    a.wfac = I.wfac;
+    a.wstride = c->wstride;
     a.lfac = I.lfac;
     a.lfstride = c->lfstride;
     a.lwork = c->dLwork;
@@ -805,7 +834,9 @@ static swr_status run_factor64(swr_ctx* c, const double* V, int nv, Iface& I) {
         if (P <= kMaxP) {
             if (I.fac) HIPCHK(launch_factor(f, c->st));
         } else {
-            // long-chunk records (swr_sweep_long.hip)
+            // streaming records (swr_sweep_long.hip); V(t,x) sweeps build their
+            // own every step, static ones only past the wide form's sizes
+            if (c->vk != SWR_V_CUBIC && wide_waves(P)) continue;
             if (!I.lfac) return SWR_EINVAL;
             FactorArgs fl = f;
             fl.fac = I.lfac;
@@ -818,18 +849,25 @@ static swr_status run_factor64(swr_ctx* c, const double* V, int nv, Iface& I) {
 
 // the records that the sweeps of the operator's contexts read
 static swr_status run_factor(swr_ctx* c, const double* V, int nv, Iface& I, bool impulses) {
-    // (V(t,x) and |u|^2: the row form serves the impulse sweeps of L_0 only)
-    if (I.rfac && (c->vk == SWR_V_STATIC || impulses)) {
+    // (V(t,x) and |u|^2: the row and wide forms serve the impulse sweeps of L_0 only)
+    if ((I.rfac || I.wfac) && (c->vk == SWR_V_STATIC || impulses)) {
         FactorArgs f{};
         f.N = c->N; f.nx = c->nx; f.nf = nv * c->N; f.h = c->h; f.dt = c->dt;
-        f.sigma = c->sigma; f.J = c->dJ; f.off = c->dOff; f.V = V; f.fac = I.rfac;
+        f.sigma = c->sigma; f.J = c->dJ; f.off = c->dOff; f.V = V;
+        int pmax[5] = {}, waves[9] = {};
+        for (int key : c->rows) pmax[key / 32] = std::max(pmax[key / 32], key % 32);
+        for (int key : c->wide) waves[key / 32] = 1;
+        f.fac = I.rfac;
         f.Pk = c->dRows;
         f.fstride = c->rstride;
-        int pmax[5] = {};
-        for (int key : c->rows) pmax[key / 32] = std::max(pmax[key / 32], key % 32);
         for (int RW : {1, 2, 4})
             if (pmax[RW]) HIPCHK(launch_rows_factor(f, RW, pmax[RW], c->st));
-        if (c->vk == SWR_V_STATIC && !c->Qlong) return SWR_OK;
+        f.fac = I.wfac;
+        f.Pk = c->dWide;
+        f.fstride = c->wstride;
+        for (int NW : {2, 4, 8})
+            if (waves[NW]) HIPCHK(launch_wide_factor(f, NW, c->st));
+        if (c->vk == SWR_V_STATIC && !c->stream_static) return SWR_OK;
     }
     return run_factor64(c, V, nv, I);
 }
@@ -915,9 +953,17 @@ static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hip
         a.ntasks = r.count;
         hipError_t e;
         if (r.P > kMaxP) {
-            // subdomains beyond 64 * kMaxP nodes: the long-chunk sweep, one launch
-            a.lq = r.P;
-            e = launch_sweep_long(a, tr, vk, st);
+            // subdomains beyond 64 * kMaxP nodes: one launch
+            const int NW = rows ? wide_waves(r.P) : 0;
+            if (NW) {
+                SweepArgs w = a;
+                w.fac = a.wfac;
+                w.fstride = a.wstride;
+                e = launch_sweep_wide(w, tr, NW, (r.P + NW - 1) / NW, st);
+            } else {
+                a.lq = r.P;
+                e = launch_sweep_long(a, tr, vk, st);
+            }
         } else {
             e = rows ? hipSuccess : launch_sweep(a, tr, vk, st, plain);
         }

@@ -14,8 +14,10 @@
 // them through the three passes of the partition solve (forward, backward,
 // recovery).  The S0^2 history uses the register sweep's arithmetic
 // (far_sum_s02 plus the block-before and in-block terms, same order).
-// Transmissions: Robin and S0^2; potentials: static, V(t,x) (the task's own
-// record refactorised every step), |u|^2 (inner fixed point of eq. AvMNL).
+// Transmissions: Robin and S0^2; potentials: V(t,x) (the task's own
+// record refactorised every step), |u|^2 (inner fixed point of eq. AvMNL), and
+// static ones past the sizes of the wide form (swr_sweep_wide.hip), which holds
+// the state on chip.
 #include "swr_sweep_kernel.h"
 
 namespace swr {

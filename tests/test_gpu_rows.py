@@ -65,3 +65,48 @@ def test_one_sweep_equals_the_oracle(dev, label, J, B, per_problem, trans):
     assert np.array_equal(got2[1][:, :40], got[1][:, :40])
     assert not np.isfinite(got2[1][:, 40]).any()
     pb.close()
+
+
+# node counts J + 1 at the first and last width of every workgroup size of the
+# wide form (2, 4, 8 waves; 5 to 9, for 8 waves to 12 nodes per lane), with and
+# without copied slots, the first size past it, and a short neighbour
+WIDE = [
+    ("two-waves", [512, 639, 640, 700, 1023, 1151, 99], W.S02),
+    ("two-waves-robin", [520, 1151, 300], W.ROBIN),
+    ("four-waves", [1152, 1279, 1280, 1900, 2303], W.S02),
+    ("eight-waves", [2304, 2559, 4200, 4607], W.S02),
+    ("eight-waves-long", [4608, 5119, 6143, 6144], W.S02),
+]
+
+
+@pytest.mark.parametrize("label,J,trans", WIDE, ids=[c[0] for c in WIDE])
+def test_one_wide_sweep_equals_the_oracle(dev, label, J, trans):
+    """Long subdomains on a workgroup of 2, 4 or 8 waves: one sweep against the
+    oracle's at 1e-11, the bar of the streaming form's test (chunks of many
+    nodes), and steps before a non-finite flux unchanged."""
+    import torch
+    import oracle as O
+    from paper_1503_02564_amd import swr
+    nt, B = 135, 2
+    wl = W.small_case(J=J, nt=nt, trans=trans, sigma=2 - 3j, B=B, seed=5, a0=-12.0, b0=12.0)
+    rng = np.random.default_rng(3)
+    ns = 2 * len(J) - 2
+    g = 0.3 * (rng.standard_normal((B, ns, nt)) + 1j * rng.standard_normal((B, ns, nt)))
+    say("wide", label)
+    pb = make_problem(wl)
+    gd = to_dev(g)
+    out = torch.zeros_like(gd)
+    uT = torch.zeros((B, wl.nx), dtype=torch.complex128, device=dev)
+    swr.swr_apply_R(pb.ctx, to_dev(wl.u0), gd, out, uT)
+    got = to_np(out)
+    for b in range(B):
+        uref, ref = O.local_solution(wl, wl.u0[b], g[b])
+        eg, eu = rel(got[b], ref), rel(to_np(uT)[b], uref)
+        say("wide", label, b, "g", eg, "uT", eu)
+        assert eg < 1e-11 and eu < 1e-11
+    gd[1, :, 70] = float("nan")
+    out2 = torch.zeros_like(gd)
+    swr.swr_apply_R(pb.ctx, to_dev(wl.u0), gd, out2, None)
+    got2 = to_np(out2)
+    assert np.array_equal(got2[0], got[0]) and np.array_equal(got2[1][:, :70], got[1][:, :70])
+    pb.close()
