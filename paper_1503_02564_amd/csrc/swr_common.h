@@ -152,13 +152,29 @@ __device__ inline cd shfl_dn_raw(cd v, int d) {
     return mk(__shfl(v.x, src), __shfl(v.y, src));
 }
 
+// Sum and maximum over the wave, on every lane: rotations inside rows of 16
+// lanes, then the lane swaps between rows -- no LDS round trips (as
+// butterflies of __shfl_xor the six steps took about 1000 cycles of latency).
+// Every lane of the result has the same bits.
 __device__ inline double wave_max(double v) {
-    for (int d = 32; d >= 1; d >>= 1) v = fmax(v, __shfl_xor(v, d));
-    return v;
+    v = fmax(v, dpp_shift<0x128>(v));             // row_ror:8
+    v = fmax(v, dpp_shift<0x124>(v));
+    v = fmax(v, dpp_shift<0x122>(v));
+    v = fmax(v, dpp_shift<0x121>(v));
+    const RowPair r = swap16(v);
+    v = fmax(r.first, r.second);
+    const RowPair h = swap32(v);
+    return fmax(h.first, h.second);
 }
 __device__ inline double wave_sum(double v) {
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-    return v;
+    v += dpp_shift<0x128>(v);
+    v += dpp_shift<0x124>(v);
+    v += dpp_shift<0x122>(v);
+    v += dpp_shift<0x121>(v);
+    const RowPair r = swap16(v);
+    v = r.first + r.second;
+    const RowPair h = swap32(v);
+    return h.first + h.second;
 }
 
 // ---------------------------------------------------------------------------
