@@ -327,6 +327,8 @@ struct SweepArgs {
     int flags_and, flags_or;     // per-launch override of the task flags
     cd* ckpt;                    // [ntasks][Jc+1][P][64] checkpoints of u
     int Jc;                      // ceil(nt / 64)
+    cd* bsum;                    // [ntasks][2][nt] with the checkpoints: running sums (history less
+                                 // flux) of every step's two boundary terms, for the replay
     int task0;                   // this launch runs tasks task0 .. task0 + ntasks - 1
     int n_begin, n_end;          // steps n_begin+1 .. n_end of this launch (n_begin % 64 == 0)
     cd* state;                   // [ntasks][2][P][64] u_n and v_n carried between launches
@@ -517,31 +519,34 @@ hipError_t launch_causal_gen(int N, int nt, int ns, int B, int per_problem, cons
                              const cd* pcr, int levels, const cd* d, cd* base, cd* g, int n_lo,
                              int n_hi, const cd* facc, int s_from, hipStream_t st);
 struct AdjArgs {
-    int N, nt, B, nx, ns, ntasks, P, Jc;
-    int task0, pstride;          // this launch runs tasks task0 ..; record stride as SweepArgs
+    int N, nt, B, nx, ns, Jc;
+    int pstride;                 // record stride of checkpoints, segments and state, as SweepArgs
     size_t fstride;
     double kappa, h;
     cd sigma, c2;
     const int* J;
     const int* off;
     const Task* tasks;
-    const cd* fac;
+    const int4* items;           // workgroups, as SweepArgs
+    const cd* fac;               // row-form records
     const double* beta;
     const cd* gbar;          // [B][nx]
     const cd* g_in;          // adjoint fluxes [B][ns][nt] (null: zero)
-    cd* g_out;               // outgoing adjoint fluxes (null: not written)
+    cd* g_out;               // outgoing adjoint fluxes
     cd* hist;                // adjoint boundary history [ntasks][2][nt+1]
+    const cd* far_old;       // as SweepArgs
+    cd* state;               // [ntasks][2][P][64] w and the gradient sums carried between launches
+    int m_begin, m_end;      // adjoint steps of this launch (m_begin % 64 == 0)
     int grad;                // replay the forward and accumulate dJ/dV
     const cd* ckpt;          // [ntasks][Jc+1][P][64]
-    const cd* g_fwd;         // forward converged fluxes
-    const cd* hist_fwd;      // forward boundary history [ntasks][2][nt+1]
+    const cd* bsum;          // [ntasks][2][nt] the forward's boundary sums
     cd* seg;                 // [ntasks][64][P][64] forward v of one block
     double* dV;              // [B][nx] (nodes interior to a subdomain)
     cd* du0;                 // [B][nx] (nodes interior to a subdomain)
     double* gends;           // [B][N][2] dJ/dV partial sums at the end nodes
     cd* wends;               // [B][N][2] w at the end nodes
 };
-hipError_t launch_adjoint(const AdjArgs& a, int trans, hipStream_t st);
+hipError_t launch_adjoint(const AdjArgs& a, int kind, int trans, int nitems, int pmax, hipStream_t st);
 hipError_t launch_finalize_grad(int N, int nx, int B, const int* off, const double* gends,
                                 const cd* wends, double* dV, cd* du0, hipStream_t st);
 hipError_t launch_maxabs(const cd* x, long M, int B, double* partial, double* out, hipStream_t st);

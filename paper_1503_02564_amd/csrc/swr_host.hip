@@ -161,7 +161,7 @@ struct swr_ctx {
     int Jc = 0;
     cd* dCkpt = nullptr;
     cd* dSeg = nullptr;
-    cd* dHist2 = nullptr;
+    cd* dBsum = nullptr;      // [nSub][2][nt] the forward final sweep's boundary sums
     cd* dGfwd = nullptr;
     cd* dDadj = nullptr;
     cd* dGadj = nullptr;
@@ -413,6 +413,11 @@ static std::vector<cd> pade_coefficients(int m, double theta) {
     return out;
 }
 
+// Wide form: waves per task for a subdomain of at most 64 Pk nodes (Pk > kMaxP),
+// 0 past its sizes.  More waves than needed for 5 to 9 nodes per lane only add
+// exchanges; fewer would not hold the state in registers.
+static int wide_waves(int Pk) { return Pk <= 18 ? 2 : Pk <= 36 ? 4 : Pk <= 8 * kWideMaxP ? 8 : 0; }
+
 // ---------------------------------------------------------------------------
 // Row form of the static sweep: how many rows of 16 lanes a task of each
 // subdomain gets.  Fewer rows put more tasks in a wave and cost less per task
@@ -423,11 +428,6 @@ static std::vector<cd> pade_coefficients(int m, double theta) {
 // the problem's sizes only, never on the schedule, so every schedule computes
 // the same bits.
 // ---------------------------------------------------------------------------
-// Wide form: waves per task for a subdomain of at most 64 Pk nodes (Pk > kMaxP),
-// 0 past its sizes.  More waves than needed for 5 to 9 nodes per lane only add
-// exchanges; fewer would not hold the state in registers.
-static int wide_waves(int Pk) { return Pk <= 18 ? 2 : Pk <= 36 ? 4 : Pk <= 8 * kWideMaxP ? 8 : 0; }
-
 static void rows_plan(swr_ctx* c, size_t ntasks, int sharing) {
     c->rows.assign(c->N, 0);
     c->wide.assign(c->N, 0);
@@ -641,8 +641,6 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     c->L.tasks = c->dBuild;   // its impulse tasks lead the build list
     c->L.ntasks = (int)impulse_tasks(N, nv).size();
     if (vk == SWR_V_STATIC) {
-        // (the row form's contexts hold the 64-lane records only once a
-        // gradient has been asked for)
         if (c->rstride) ALLOC(c->L.rfac, (size_t)nv * N * c->rstride);
         else if (tr > SWR_S02) ALLOC(c->L.fac, (size_t)nv * N * fields * kWave);
         if (c->wstride) ALLOC(c->L.wfac, (size_t)nv * N * c->wstride);
@@ -888,6 +886,7 @@ static SweepArgs sub_args(swr_ctx* c, const SweepIO& io) {
                  (io.uT ? T_OUT_UT : 0) | (io.trace ? T_OUT_TRACE : 0) | (io.maxdiff ? T_MAXDIFF : 0) |
                  (io.ckpt ? T_CKPT : 0) | (io.snaps ? T_OUT_SNAP : 0);
     a.ckpt = c->dCkpt;
+    a.bsum = c->dBsum;
     a.Jc = c->Jc;
     a.snaps = io.snaps;
     a.snap_ends = c->dSnapEnds;
@@ -2246,30 +2245,47 @@ static swr_status solve_interface(swr_ctx* c, const cd* d, cd* g, int* iters) {
 
 static AdjArgs adj_args(swr_ctx* c) {
     AdjArgs a{};
-    a.N = c->N; a.nt = c->nt; a.B = c->B; a.nx = c->nx; a.ns = c->ns; a.ntasks = c->nSub;
-    a.P = c->P; a.Jc = c->Jc;
+    a.N = c->N; a.nt = c->nt; a.B = c->B; a.nx = c->nx; a.ns = c->ns; a.Jc = c->Jc;
     a.kappa = c->h / (3.0 * c->dt);
     a.h = c->h;
     a.sigma = c->sigma;
     a.c2 = c->c2;
-    a.J = c->dJ; a.off = c->dOff; a.tasks = c->dSub; a.fac = c->L.fac; a.beta = c->dBeta;
-    a.hist = c->dHist2;
-    a.ckpt = c->dCkpt; a.g_fwd = c->dGfwd; a.hist_fwd = c->dHist; a.seg = c->dSeg;
+    a.J = c->dJ; a.off = c->dOff; a.tasks = c->dSub; a.fac = c->L.rfac; a.beta = c->dBeta;
+    a.fstride = c->rstride;
+    // (the forward's history is no longer needed: its replay reads the sums)
+    a.hist = c->dHist;
+    a.state = c->dStateF;
+    a.ckpt = c->dCkpt; a.bsum = c->dBsum; a.seg = c->dSeg;
     a.gends = c->dGends; a.wends = c->dWends;
-    a.task0 = 0;
     a.pstride = c->P;
-    a.fstride = (size_t)fac_fields(c->P) * kWave;
     return a;
 }
 
-// the adjoint sweep over every (problem, subdomain), one launch per chunk width
-static hipError_t launch_adjoint_widths(const swr_ctx* c, AdjArgs a, hipStream_t st) {
-    for (const WidthRun& r : c->runs_sub) {
-        a.P = r.P;
-        a.task0 = r.start;
-        a.ntasks = r.count;
-        const hipError_t e = launch_adjoint(a, ktr(c), st);
-        if (e != hipSuccess) return e;
+// the adjoint sweep over every (problem, subdomain), the workgroups of the
+// forward's row form; S0^2 in pieces that end at super-chunk boundaries, as
+// launch_widths
+static hipError_t launch_adjoint_all(const swr_ctx* c, AdjArgs a, hipStream_t st) {
+    const bool split = far_split(c);
+    a.far_old = split ? c->dFarS : nullptr;
+    for (int s0 = 0; s0 < c->nt; s0 = a.m_end) {
+        if (s0 > 0) {
+            FarOldArgs f{};
+            f.hist = a.hist;
+            f.beta = a.beta;
+            f.out = c->dFarS;
+            f.ntasks = c->nSub;
+            f.nt = c->nt;
+            f.C = s0;
+            const hipError_t e = launch_far_old(f, st);
+            if (e != hipSuccess) return e;
+        }
+        a.m_begin = s0;
+        a.m_end = split ? std::min(c->nt, s0 + kFarSuper) : c->nt;
+        for (const RowsRun& run : c->rows_sub.runs) {
+            a.items = c->rows_sub.dev + run.start;
+            const hipError_t e = launch_adjoint(a, run.kind, ktr(c), run.count, run.pmax, st);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
@@ -2288,7 +2304,7 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
         c->Jc = (c->nt + kWave - 1) / kWave;
         ALLOC_LIVE(c->dCkpt, (size_t)c->nSub * (c->Jc + 1) * c->P * kWave);
         ALLOC_LIVE(c->dSeg, (size_t)c->nSub * kWave * c->P * kWave);
-        ALLOC_LIVE(c->dHist2, (size_t)c->nSub * 2 * (c->nt + 1));
+        ALLOC_LIVE(c->dBsum, (size_t)c->nSub * 2 * c->nt);
         ALLOC_LIVE(c->dGfwd, vec);
         ALLOC_LIVE(c->dDadj, vec);
         ALLOC_LIVE(c->dGadj, vec);
@@ -2296,13 +2312,11 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
         ALLOC_LIVE(c->dWends, (size_t)c->B * c->N * 2);
         ALLOC_LIVE(c->dUT, (size_t)c->B * c->nx);
     }
-    if (!c->L.fac) ALLOC_LIVE(c->L.fac, (size_t)c->nv * c->N * fac_fields(c->P) * kWave);
     int it_f = 0, it_b = 0;
     // ---- forward: factor, impulses + d, interface solve, final sweep with
-    //      checkpoints (the S0^2 boundary history of this sweep stays in dHist)
+    //      checkpoints
     HIPCHK(hipEventRecord(c->ev[0], st));
     CHK(run_factor(c, c->dV, c->nv, c->L, false));
-    CHK(run_factor64(c, c->dV, c->nv, c->L));   // the adjoint sweep's records
     swr_status rf = SWR_OK;
     if (pipelined(c)) {
         SweepIO io;
@@ -2333,7 +2347,7 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
     a.g_in = nullptr;
     a.g_out = c->ns ? c->dDadj : nullptr;
     a.grad = 0;
-    HIPCHK(launch_adjoint_widths(c, a, st));
+    HIPCHK(launch_adjoint_all(c, a, st));
     HIPCHK(hipEventRecord(c->ev[2], st));
     c->hist.clear();   // the history reported is the adjoint interface solve's
     swr_status rb = solve_interface(c, c->dDadj, c->dGadj, &it_b);
@@ -2345,7 +2359,7 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
     a.grad = 1;
     a.dV = dJdV;
     a.du0 = reinterpret_cast<cd*>(dJdu0);
-    HIPCHK(launch_adjoint_widths(c, a, st));
+    HIPCHK(launch_adjoint_all(c, a, st));
     HIPCHK(launch_finalize_grad(c->N, c->nx, c->B, c->dOff, c->dGends, c->dWends, dJdV,
                                 reinterpret_cast<cd*>(dJdu0), st));
     HIPCHK(hipEventRecord(c->ev[4], st));

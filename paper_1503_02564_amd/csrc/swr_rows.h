@@ -174,6 +174,95 @@ __device__ inline cd rows_front(const cd (&v)[P], bool dup) {
     return sel_c(dup, v[P < 2 ? 0 : 1], v[0]);
 }
 
+// the mass stencil u_{i-1} + 4 u_i + u_{i+1} of slot q (2 u at an end node:
+// weights w0, wL of slots 0 and P - 1); uL, uR: the neighbouring lanes' nodes
+template <int P>
+__device__ inline cd rows_stencil(const cd (&u)[P], cd uL, cd uR, double w0, double wL, int q) {
+    const cd up = sel_c(q == 0, uL, u[q == 0 ? 0 : q - 1]);
+    const cd un = sel_c(q == P - 1, uR, u[q == P - 1 ? 0 : q + 1]);
+    const double w = q == P - 1 ? wL : (q == 0 ? w0 : 4.0);
+    return mk(fma(w, u[q].x, up.x) + un.x, fma(w, u[q].y, up.y) + un.y);
+}
+
+// One step's solve A x = d: dF and dS the right-hand sides of slots 0 and
+// P - 1 with the boundary terms in, rhs(q) those between; y the solution
+template <int P, int RW, bool LDSF, class RHS>
+__device__ __forceinline__ void rows_solve(const RowsFac<P, RW, LDSF>& F, cd dF, cd dS, RHS rhs, int t,
+                                           bool dup, cd (&y)[P]) {
+    const cd zero = mk(0, 0);
+    // interior fields in LDS are read anew every step (the compiler would
+    // otherwise keep them in registers across the loop)
+    if (LDSF) asm volatile("" ::: "memory");
+    // chunk interior: w_q = d_q - cp_{q-1} w_{q-1}, y_q = inv_q w_q - cp_q y_{q+1}.
+    // From LDS the coefficients are read kAhead slots before their use,
+    // held there by the scheduling barriers: read at their use, each of
+    // the 2 P reads waited for LDS (2600 of about 6000 cycles a step at P = 12).
+    constexpr int kAhead = P >= 14 ? 2 : 3;
+    if constexpr (P > 1 && !LDSF) {
+        cd w = dF;
+        y[0] = cmul_x(w, F.inv(0));
+#pragma unroll
+        for (int q = 1; q < P - 1; ++q) {
+            w = msub_x(rhs(q), F.cp(q - 1), w);
+            y[q] = cmul_x(w, F.inv(q));
+        }
+#pragma unroll
+        for (int q = P - 3; q >= 0; --q) y[q] = msub_x(y[q], F.cp(q), y[q + 1]);
+    }
+    if constexpr (P > 1 && LDSF) {
+        cd iv[P], cp[P];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) { iv[q] = F.inv(q); cp[q] = F.cp(q); }
+        cd w = dF;
+#pragma unroll
+        for (int q = 0; q < P - 1; ++q) {
+            if (q + kAhead < P - 1) { iv[q + kAhead] = F.inv(q + kAhead); cp[q + kAhead] = F.cp(q + kAhead); }
+            __builtin_amdgcn_sched_barrier(0);
+            if (q > 0) w = msub_x(rhs(q), cp[q - 1], w);
+            y[q] = cmul_x(w, iv[q]);
+        }
+        cd cb[P];
+#pragma unroll
+        for (int q = P - 3; q > P - 3 - 2 * kAhead; --q) cb[q] = F.cp(q);
+#pragma unroll
+        for (int q = P - 3; q >= 0; --q) {
+            if (q - 2 * kAhead >= 0) cb[q - 2 * kAhead] = F.cp(q - 2 * kAhead);
+            __builtin_amdgcn_sched_barrier(0);
+            y[q] = msub_x(y[q], cb[q], y[q + 1]);
+        }
+    }
+    cd D = dS;
+    if (P > 1) {
+        // first real node's value for the left neighbour (a copy's y is zero)
+        cd yF = y[0];
+        if (P == 2) yF = sel_c(dup, zero, yF);
+        if (P > 2) yF = sel_c(dup, y[P > 2 ? 1 : 0], yF);
+        const cd yR = rows_dn1<RW>(yF, t);
+        D = msub_x(msub_x(D, F.ae(), y[P > 1 ? P - 2 : 0]), F.ce(), yR);
+    }
+    const cd X = rows_reduce(F, D, t);
+    if constexpr (P > 1) {
+        cd al[P], ga[P];
+        if (LDSF) {
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) { al[q] = F.al(q); ga[q] = F.ga(q); }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const cd Xm = rows_up1<RW>(X, t);
+#pragma unroll
+        for (int q = 0; q < P - 1; ++q) {
+            if (LDSF) {
+                if (q + kAhead < P - 1) { al[q + kAhead] = F.al(q + kAhead); ga[q + kAhead] = F.ga(q + kAhead); }
+                __builtin_amdgcn_sched_barrier(0);
+                y[q] = madd_x(madd_x(y[q], al[q], Xm), ga[q], X);
+            } else {
+                y[q] = madd_x(madd_x(y[q], F.al(q), Xm), F.ga(q), X);
+            }
+        }
+    }
+    y[P - 1] = X;
+}
+
 // node of slot 0, and whether that slot is a copy of the node to the left
 template <int P, int RW>
 __device__ inline void rows_place(int n, int t, int& s, bool& dup) {

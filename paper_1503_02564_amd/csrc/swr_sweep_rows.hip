@@ -18,8 +18,7 @@ hipError_t launch_sweep_rows(const SweepArgs& a, int kind, int trans, int nitems
     if (pmax < 1 || pmax > k.pmax) return hipErrorInvalidValue;
     if (trans == TR_S02 && (!a.hist || !a.beta)) return hipErrorInvalidValue;
     if ((a.n_begin > 0 || a.n_end < a.nt) && !a.state) return hipErrorInvalidValue;
-    const size_t lds = sizeof(cd) * (kRowsBetaLds / 2 + (size_t)k.waves * kRowsWaveLds +
-                                     (k.lds ? (size_t)rows_fields(pmax, k.RW) * 16 * k.RW : 0));
+    const size_t lds = rows_lds_bytes(k, pmax);
     switch (kind) {
         case 0: return launch_sweep_rows4(a, trans, nitems, lds, st);
         case 1: return launch_sweep_rows1_reg(a, trans, nitems, lds, st);

@@ -37,6 +37,12 @@ namespace swr {
 constexpr int kRowsBetaLds = 324;       // beta_0 .. of the in-super-chunk products
 constexpr int kRowsWaveLds = 4 * kWave; // complex values per wave: logs of v and of the running sums
 
+// LDS of a workgroup: [beta window][logs of each wave][record]
+inline size_t rows_lds_bytes(const RowsKind& k, int pmax) {
+    return sizeof(cd) * (kRowsBetaLds / 2 + (size_t)k.waves * kRowsWaveLds +
+                         (k.lds ? (size_t)rows_fields(pmax, k.RW) * 16 * k.RW : 0));
+}
+
 typedef double rows_f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline void rows_fence() {
@@ -48,19 +54,18 @@ __device__ inline void rows_fence() {
 // History terms q <= n0 of a block's outputs (without the part older than the
 // super-chunk when split) -> ex[end][lane], lane = task slot * T + output.
 template <int RW>
-__device__ inline void rows_far(const SweepArgs& a, int task0, int ntask, int n0, const double* sb,
-                                cd* ex) {
+__device__ inline void rows_far(const cd* hist, const double* beta, int nt, bool split, int task0, int ntask,
+                                int n0, const double* sb, cd* ex) {
     constexpr int SLOTS = 4 / RW, T = 16 * RW, U = 4;
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane & 15, kq = lane >> 4;
     const int part = r & 1, e = (r >> 1) & 1, sc = r >> 2;
     const int sl = sc % SLOTS, sh = sc / SLOTS;      // task slot, 16-step part of the block
-    const bool split = a.far_old != nullptr;
     const int C = n0 - n0 % kFarSuper;
     const int q_lo = split && C > 0 ? C - kWave : 0;
     const int qs = q_lo - 16 * (RW - 1);
     const double* hb = reinterpret_cast<const double*>(
-                           a.hist + ((size_t)(task0 + min(sl, ntask - 1)) * 2 + e) * (a.nt + 1)) + part;
+                           hist + ((size_t)(task0 + min(sl, ntask - 1)) * 2 + e) * (nt + 1)) + part;
     const int qb = 16 * sh + kq;                     // my source of group qg: qg + qb
     const int ab = n0 + 1 + r - kq;                  // my beta index of group qg: ab - qg
     const int ng = (n0 - qs) / 4 + 1;
@@ -72,7 +77,7 @@ __device__ inline void rows_far(const SweepArgs& a, int task0, int ntask, int n0
             const int qg = qs + 4 * (g + u), q = qg + qb, i = max(ab - qg, 0);
             bn[u] = 0.0;
             if (q >= q_lo && q <= n0) bn[u] = hb[2 * q];
-            an[u] = split ? sb[i] : a.beta[i];
+            an[u] = split ? sb[i] : beta[i];
         }
     };
     fetch(0);
@@ -225,7 +230,7 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
         cd accA = zero, accB = zero;
         if (TR == TR_S02) {
             __threadfence_block();
-            rows_far<RW>(a, first + slot0, count - slot0, n0, sb, lg);
+            rows_far<RW>(a.hist, a.beta, nt, a.far_old != nullptr, first + slot0, count - slot0, n0, sb, lg);
             rows_fence();
             accA = lg[lane];
             accB = lg[kWave + lane - t + jr];
@@ -256,17 +261,9 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
         for (int i = 0; i < nb;) {
           const int ie = special ? min(nb, i + until(n0 + i)) : nb;
           for (; i < ie; ++i) {
-            // interior fields in LDS are read anew every step (the compiler
-            // would otherwise keep them in registers across the loop)
-            if (LDSF) asm volatile("" ::: "memory");
             const cd uL = rows_up1<RW>(u[P - 1], t);
             const cd uR = rows_dn1<RW>(rows_front<P>(u, dup), t);
-            auto stencil = [&](int q) {
-                const cd up = sel_c(q == 0, uL, u[q == 0 ? 0 : q - 1]);
-                const cd un = sel_c(q == P - 1, uR, u[q == P - 1 ? 0 : q + 1]);
-                const double w = q == P - 1 ? wL : (q == 0 ? w0 : 4.0);
-                return mk(fma(w, u[q].x, up.x) + un.x, fma(w, u[q].y, up.y) + un.y);
-            };
+            auto stencil = [&](int q) { return rows_stencil<P>(u, uL, uR, w0, wL, q); };
             cd dF = stencil(0), dS = P > 1 ? stencil(P - 1) : zero;
             if (ml) {
                 dF = madd_x(dF, cs, accA);
@@ -277,75 +274,9 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
                 dS = madd_x(dS, cs, accB);
                 lgl[3 * kWave + i] = accB;
             }
-            // chunk interior: w_q = d_q - cp_{q-1} w_{q-1}, y_q = inv_q w_q - cp_q y_{q+1}.
-            // From LDS the coefficients are read kAhead slots before their use,
-            // held there by the scheduling barriers: read at their use, each of
-            // the 2 P reads waited for LDS (2600 of about 6000 cycles a step at P = 12).
-            constexpr int kAhead = P >= 14 ? 2 : 3;
             cd y[P];
-            if constexpr (P > 1 && !LDSF) {
-                cd w = dF;
-                y[0] = cmul_x(w, F.inv(0));
-#pragma unroll
-                for (int q = 1; q < P - 1; ++q) {
-                    w = msub_x(stencil(q), F.cp(q - 1), w);
-                    y[q] = cmul_x(w, F.inv(q));
-                }
-#pragma unroll
-                for (int q = P - 3; q >= 0; --q) y[q] = msub_x(y[q], F.cp(q), y[q + 1]);
-            }
-            if constexpr (P > 1 && LDSF) {
-                cd iv[P], cp[P];
-#pragma unroll
-                for (int q = 0; q < kAhead; ++q) { iv[q] = F.inv(q); cp[q] = F.cp(q); }
-                cd w = dF;
-#pragma unroll
-                for (int q = 0; q < P - 1; ++q) {
-                    if (q + kAhead < P - 1) { iv[q + kAhead] = F.inv(q + kAhead); cp[q + kAhead] = F.cp(q + kAhead); }
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (q > 0) w = msub_x(stencil(q), cp[q - 1], w);
-                    y[q] = cmul_x(w, iv[q]);
-                }
-                cd cb[P];
-#pragma unroll
-                for (int q = P - 3; q > P - 3 - 2 * kAhead; --q) cb[q] = F.cp(q);
-#pragma unroll
-                for (int q = P - 3; q >= 0; --q) {
-                    if (q - 2 * kAhead >= 0) cb[q - 2 * kAhead] = F.cp(q - 2 * kAhead);
-                    __builtin_amdgcn_sched_barrier(0);
-                    y[q] = msub_x(y[q], cb[q], y[q + 1]);
-                }
-            }
-            cd D = dS;
-            if (P > 1) {
-                // first real node's value for the left neighbour (a copy's y is zero)
-                cd yF = y[0];
-                if (P == 2) yF = sel_c(dup, zero, yF);
-                if (P > 2) yF = sel_c(dup, y[P > 2 ? 1 : 0], yF);
-                const cd yR = rows_dn1<RW>(yF, t);
-                D = msub_x(msub_x(D, F.ae(), y[P > 1 ? P - 2 : 0]), F.ce(), yR);
-            }
-            const cd X = rows_reduce(F, D, t);
-            if constexpr (P > 1) {
-                cd al[P], ga[P];
-                if (LDSF) {
-#pragma unroll
-                    for (int q = 0; q < kAhead; ++q) { al[q] = F.al(q); ga[q] = F.ga(q); }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                const cd Xm = rows_up1<RW>(X, t);
-#pragma unroll
-                for (int q = 0; q < P - 1; ++q) {
-                    if (LDSF) {
-                        if (q + kAhead < P - 1) { al[q + kAhead] = F.al(q + kAhead); ga[q + kAhead] = F.ga(q + kAhead); }
-                        __builtin_amdgcn_sched_barrier(0);
-                        y[q] = madd_x(madd_x(y[q], al[q], Xm), ga[q], X);
-                    } else {
-                        y[q] = madd_x(madd_x(y[q], F.al(q), Xm), F.ga(q), X);
-                    }
-                }
-            }
-            y[P - 1] = X;
+            rows_solve(F, dF, dS, stencil, t, dup, y);
+            const cd X = y[P - 1];
 #pragma unroll
             for (int q = 0; q < P; ++q) u[q] = mk(2.0 * y[q].x - u[q].x, 2.0 * y[q].y - u[q].y);
             if (t0) lgl[i] = y[0];
@@ -366,6 +297,11 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
         const cd va = lg[lane], vb = lg[kWave + lane], sa = lg[2 * kWave + lane], sc = lg[3 * kWave + lane];
         rows_fence();
         if (okl && live) {
+            if (fl & T_CKPT) {
+                cd* bs = a.bsum + (size_t)tix * 2 * nt + n0 + t;
+                if (lif) bs[0] = sa;
+                if (rif) bs[nt] = sc;
+            }
             if (TR == TR_S02) {
                 Ha[n0 + 1 + t] = va;
                 Ha[nt + 1 + n0 + 1 + t] = vb;

@@ -470,7 +470,7 @@ __device__ inline void wide_body(const SweepArgs& a, int tix, cd* smem) {
             const int jo = wfirst ? lane : jr;
             if (TR == TR_S02) {
                 __threadfence_block();
-                rows_far<4>(a, tix, 1, n0, nullptr, lg);
+                rows_far<4>(a.hist, a.beta, nt, false, tix, 1, n0, nullptr, lg);
                 rows_fence();
                 acc = lg[(wfirst ? 0 : kWave) + jo];
                 rows_fence();

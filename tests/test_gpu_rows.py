@@ -110,3 +110,47 @@ def test_one_wide_sweep_equals_the_oracle(dev, label, J, trans):
     got2 = to_np(out2)
     assert np.array_equal(got2[0], got[0]) and np.array_equal(got2[1][:, :70], got[1][:, :70])
     pb.close()
+
+
+# the same forms in the adjoint sweep (node counts J + 1 at the edges of their
+# widths); few tasks: one task on the whole wave
+ADJ = [
+    ("whole-wave", [1, 2, 62, 63, 64, 127, 255, 300, 511], 2, True, W.S02),
+    ("one-row", [1, 2, 14, 15, 16, 31, 32, 63, 64, 79, 100, 126, 127], 127, False, W.S02),
+    ("one-row-robin-per-problem", [3, 15, 16, 63, 64, 127], 430, True, W.ROBIN),
+    ("two-rows", [128, 129, 160, 191, 224, 255, 100], 240, False, W.S02),
+    ("two-rows-lds", [256, 288, 320, 384, 447, 480, 511], 350, False, W.S02),
+    ("one-row-lds", [128, 143, 144, 160, 176, 191, 208, 223], 790, False, W.S02),
+]
+
+
+@pytest.mark.parametrize("label,J,B,per_problem,trans", ADJ, ids=[c[0] for c in ADJ])
+def test_adjoint_of_every_form(dev, label, J, B, per_problem, trans):
+    """Gradients against the oracle's monodomain adjoint at the bar of the
+    suite's adjoint tests, over several checkpoint segments with a ragged last
+    one, for an arbitrary upstream gradient."""
+    import torch
+    import oracle as O
+    from paper_1503_02564_amd import swr
+    nt = 70 if trans == W.ROBIN else 150
+    wl = W.small_case(J=J, nt=nt, trans=trans, sigma=2 - 3j, B=B, seed=11, a0=-10.0, b0=10.0)
+    Vs = None
+    if per_problem:
+        Vs = np.stack([(0.5 + b / B) * np.asarray(wl.V) for b in range(B)])
+        wl = W.Workload("pp", wl.a0, wl.b0, wl.J, wl.dt, wl.nt, W.V_STATIC, Vs, trans, wl.sigma, wl.u0)
+    rng = np.random.default_rng(4)
+    gbar = rng.standard_normal((B, wl.nx)) + 1j * rng.standard_normal((B, wl.nx))
+    say("adjoint rows", label, "tasks", B * len(J))
+    pb = make_problem(wl, v_per_problem=per_problem)
+    dV = torch.zeros((B, wl.nx), dtype=torch.float64, device=dev)
+    du0 = torch.zeros((B, wl.nx), dtype=torch.complex128, device=dev)
+    st, info = swr.swr_grad(pb.ctx, to_dev(wl.u0), to_dev(gbar), dV, du0)
+    assert st == swr.SWR_OK
+    for b in (0, 1, B // 2, B - 1):
+        V = wl.V if Vs is None else Vs[b]
+        one = W.Workload("one", wl.a0, wl.b0, wl.J, wl.dt, wl.nt, W.V_STATIC, V, trans, wl.sigma, wl.u0[b:b + 1])
+        dV_ref, du0_ref = O.adjoint_mono(one, one.u0[0], gbar[b])
+        ev, eu = rel(to_np(dV)[b], dV_ref), rel(to_np(du0)[b], du0_ref)
+        say("adjoint rows", label, b, "dV", ev, "du0", eu)
+        assert ev < 1e-10 and eu < 1e-10
+    pb.close()
