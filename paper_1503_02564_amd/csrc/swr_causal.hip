@@ -11,13 +11,14 @@
 // tridiagonal with 2x2 blocks
 //     D_j = [[1, -x1_{j+1}], [-x4_j, 1]],  U_j = [[-x2_{j+1}, 0], [0, 0]],
 //     L_j = [[0, 0], [0, -x3_j]]
-// (x_p^{k} the lag-0 entry of X^{k,p}).  It is reduced by block parallel
-// cyclic reduction, whose multipliers are computed once; the reduction is
-// stable when the system is block diagonally dominant
+// (x_p^{k} the lag-0 entry of X^{k,p}).  Up to 64 interfaces it is reduced by
+// block parallel cyclic reduction on one wave, above by block elimination as
+// two prefix sums over a workgroup; the multipliers are computed once.  Both
+// are stable when the system is block diagonally dominant
 // (max_j ||D_j^{-1}|| (||L_j|| + ||U_j||) < 1), which setup checks.
 //
 // Time is processed in super-blocks of 256 steps (absolute windows) and,
-// inside them, in blocks of kTb steps.  The contribution of every earlier
+// inside them, in blocks of kTb steps (above 64 interfaces 2 to 8).  The contribution of every earlier
 // super-block to the outputs being solved is formed by one block-Toeplitz
 // product on the matrix cores (launch_ltt).  `causal_far_kernel` adds to d that product and
 // the contribution of the earlier blocks of the current super-block (a short
@@ -28,7 +29,11 @@
 // marches through the block on one workgroup per problem: wave 0 runs the
 // per-step PCR solve and adds the lag-1 and lag-2 history, while the other
 // waves gather the lags >= 3 of the step two ahead, from the block's g kept in
-// LDS and the lag coefficients kept in registers.
+// LDS and the lag coefficients kept in registers.  `causal_march_kernel` does
+// the same above 64 interfaces.
+#include <algorithm>
+#include <type_traits>
+
 #include "swr_common.h"
 
 namespace swr {
@@ -140,13 +145,20 @@ struct FarArgs {
     const cd* cols;    // [nv][N][4][nt]
     const cd* d;       // [B][ns][nt]
     const cd* g;       // [B][ns][nt]
-    cd* out;           // [B][ns][kTb]  = d + contribution of steps s < n0
+    cd* out;           // d + contribution of steps s < n0: [B][ns][kTb], or [B][TB][ns] (far_out)
     const cd* facc;    // [nseg][B][ns][kCausalSuper]: contribution of each finished
                        // super-block to steps s_from .. s_from + kCausalSuper - 1
     int nseg;          // number of finished super-blocks (facc null when 0)
     int s_from;        // this kernel sums steps s_from <= s < n0
     int B;             // problems
 };
+
+// where output step i of slot o goes: by slot for the near march of blocks of
+// kTb steps, by step for the general march, whose threads read it by interface
+template <int TB>
+__device__ inline size_t far_out(int b, int ns, int o, int i) {
+    return TB == kTb ? ((size_t)b * ns + o) * TB + i : ((size_t)b * TB + i) * ns + o;
+}
 
 // One workgroup per (subdomain k, PB problems).  Subdomain k feeds the
 // output slots 2k - 2 (if k >= 1) and 2k + 1 (if k <= N - 2); both read the
@@ -240,7 +252,7 @@ __global__ __launch_bounds__(2 * PB * 256) void causal_far_kernel(FarArgs f) {
     __syncthreads();
     if (out_ok && sp == 0) {
         for (int q = 0; q < SPLITS; ++q) r = r + part[h][bb][q][i];
-        f.out[((size_t)b * f.ns + o) * TB + i] = r;
+        f.out[far_out<TB>(b, f.ns, o, i)] = r;
     }
 }
 
@@ -348,7 +360,7 @@ __global__ __launch_bounds__(64) void causal_far_mfma_kernel(FarArgs f) {
                 for (int q2 = 0; q2 < f.nseg; ++q2)
                     acc += reinterpret_cast<const double*>(f.facc + q2 * seg_stride + row * kCausalSuper +
                                                            (n - f.s_from))[part];
-                reinterpret_cast<double*>(f.out + row * TB + i)[part] = acc + v;
+                reinterpret_cast<double*>(f.out + far_out<TB>(bcol, f.ns, o, i))[part] = acc + v;
             }
         }
     }
@@ -699,266 +711,336 @@ hipError_t launch_causal_fast(int N, int nt, int ns, int B, int per_problem, con
 }
 
 // ---------------------------------------------------------------------------
-// General path: up to kGenMaxIf interfaces.  Same algebra as above with the
-// block PCR spread over the workgroup (one thread per interface, exchange
-// through LDS) and a short near block of TB steps (gen_threads / gen_tb).
+// General path: up to kGenMaxIf interfaces.
+//
+// With L_j and U_j of one entry each, block elimination of (I - C_0) from the
+// left keeps one new number per interface.  Write r_j, l_j (= l_{j+1} above) for
+// the unknowns of interface j, x1, x2 for the lag-0 entries of subdomain j + 1
+// and x3, x4 for those of subdomain j:
+//     r_j = b_j + x1 l_j + x2 r_{j+1},   l_j = c_j + x4 r_j + x3 l_{j-1}.
+// Then l_j = A_j r_j + s_j with
+//     A_j = x4 + x3 w_{j-1} A_{j-1} x2_{j-1},   w_j = 1 / (1 - A_j x1),
+//     z_j = (c_j + A_j b_j) + alpha_j z_{j-1},  alpha_j = x3 w_{j-1},  s_j = z_j - A_j b_j,
+//     r_j = w_j b_j + w_j x1 s_j + beta_j r_{j+1},   beta_j = w_j x2.
+// (Block LU; stable where the block system is diagonally dominant, which the
+// set-up checks.)  Both recurrences are prefix sums with fixed multipliers:
+// they run by doubling of the distance, two doublings per exchange, until the
+// product of the multipliers over the distance is at most 2^-60 everywhere.
 // ---------------------------------------------------------------------------
 
-// multipliers [nv][levels][8][ni] then D^{-1} [nv][4][ni] (after the levels).
-// The neighbours' blocks are exchanged through LDS in two rounds (D and L,
-// then U), so 1024 interfaces fit.
+// Set-up, one workgroup per potential, thread j = interface j: record
+// [kMarchRows][ni] (A, w, w x1; per round of the prefix sums the multipliers
+// over 1, 2, 3 distances, left then right; the lag coefficients 1 .. 7 of
+// X^{j+1,1}, X^{j+1,2}, X^{j,3}, X^{j,4}); eta[v]: block dominance, then the
+// largest multiplier over 1, 2, 4, .. interfaces.
 template <int THREADS>
-__global__ __launch_bounds__(THREADS) void causal_pcr_setup_gen_kernel(int N, int nt, const cd* cols,
-                                                                      cd* pcr, int rec, double* eta) {
-    __shared__ C2x2 sA[THREADS], sB[THREADS];
+__global__ __launch_bounds__(THREADS) void causal_march_setup_kernel(int N, int nt, const cd* cols, cd* rec,
+                                                                    double* eta) {
+    __shared__ cd sh[THREADS];
     __shared__ double se[THREADS / kWave];
     const int v = blockIdx.x, j = threadIdx.x;
-    const int ni = N - 1, lv = pcr_levels_for(ni);
+    const int ni = N - 1;
+    const bool act = j < ni;
     const cd* base = cols + (size_t)v * N * 4 * nt;
-    auto col0 = [&](int k, int p) { return base[((size_t)k * 4 + p) * nt]; };
     const cd zero = mk(0, 0), one = mk(1, 0);
-    const C2x2 I = m2(one, zero, zero, one), Z = m2(zero, zero, zero, zero);
-    C2x2 D = I, Lm = Z, U = Z;
-    if (j < ni) {
-        const cd x1 = col0(j + 1, 0);
-        const cd x2 = (j + 1 <= N - 2) ? col0(j + 1, 1) : zero;
-        const cd x3 = (j >= 1) ? col0(j, 2) : zero;
-        const cd x4 = col0(j, 3);
-        D = m2(one, -x1, -x4, one);
-        U = m2(-x2, zero, zero, zero);
-        Lm = m2(zero, zero, zero, -x3);
+    cd x1 = zero, x2 = zero, x3 = zero, x4 = zero;
+    if (act) {
+        x1 = base[((size_t)(j + 1) * 4 + 0) * nt];
+        if (j + 1 <= N - 2) x2 = base[((size_t)(j + 1) * 4 + 1) * nt];
+        if (j >= 1) x3 = base[((size_t)j * 4 + 2) * nt];
+        x4 = base[((size_t)j * 4 + 3) * nt];
     }
-    cd* rec_v = pcr + (size_t)v * rec;
-    // per level: coupling measure and inverse diagonal block of the current
-    // system (eta[v][l], Dinv block l), then one reduction
-#pragma unroll 1
-    for (int l = 0; l <= lv; ++l) {
-        double e = (j < ni) ? norm_inf(inv2(D)) * (norm_inf(Lm) + norm_inf(U)) : 0.0;
+    auto block_max = [&](double e) {
         e = wave_max(e);
         if ((j & (kWave - 1)) == 0) se[j / kWave] = e;
         __syncthreads();
-        if (j == 0) {
-            double m = 0;
-            for (int w = 0; w < THREADS / kWave; ++w) m = fmax(m, se[w]);
-            eta[(size_t)v * (kGenLevelsMax + 1) + l] = m;
-        }
-        if (j < ni) {
-            const C2x2 Di = inv2(D);
-            cd* r = rec_v + ((size_t)lv * 8 + 4 * l) * ni + j;
-            r[0 * ni] = Di.a; r[1 * ni] = Di.b; r[2 * ni] = Di.c; r[3 * ni] = Di.d;
-        }
-        if (l == lv) break;
-        const int d = 1 << l;
-        const bool hm = j - d >= 0, hp = j + d < ni;
-        if (j < ni) { sA[j] = D; sB[j] = Lm; }
+        double m = 0;
+        for (int w = 0; w < THREADS / kWave; ++w) m = fmax(m, se[w]);
         __syncthreads();
-        C2x2 Dm = I, Lmm = Z, Dp = I, Lp = Z, Um = Z, Up = Z;
-        if (j < ni) {
-            if (hm) { Dm = sA[j - d]; Lmm = sB[j - d]; }
-            if (hp) { Dp = sA[j + d]; Lp = sB[j + d]; }
-        }
+        return m;
+    };
+    // value of thread j + d (zero outside)
+    auto shifted = [&](cd x, int d) {
+        sh[j] = x;
         __syncthreads();
-        if (j < ni) sA[j] = U;
+        cd r = zero;
+        if (j + d >= 0 && j + d < THREADS) r = sh[j + d];
         __syncthreads();
-        if (j < ni) {
-            if (hm) Um = sA[j - d];
-            if (hp) Up = sA[j + d];
+        return r;
+    };
+    double* ev = eta + (size_t)v * (kGenLevelsMax + 1);
+    {
+        const double e = act ? norm_inf(inv2(m2(one, -x1, -x4, one))) * (sqrt(abs2(x3)) + sqrt(abs2(x2))) : 0.0;
+        // (fmax drops a NaN: it must reach the host)
+        const int bad = __syncthreads_or(!(e < 1e300));
+        const double m = block_max(e);
+        if (j == 0) ev[0] = bad ? nan("") : m;
+    }
+    // A_j: all j at once, repeated until nothing changes (after m rounds the
+    // first m are final; the recurrence contracts by |alpha beta| a round)
+    cd A = x4;
+    for (int it = 0; it < ni; ++it) {
+        const cd w = inv(one - A * x1);
+        const cd An = x4 + x3 * shifted((w * A) * x2, -1);
+        const bool ch = An.x != A.x || An.y != A.y;
+        A = An;
+        if (!__syncthreads_or(ch)) break;
+    }
+    const cd w = inv(one - A * x1);
+    cd al = x3 * shifted(w, -1), be = w * x2;
+    cd* q = rec + (size_t)v * kMarchRows * ni + j;
+    if (act) {
+        q[0] = A;
+        q[ni] = w;
+        q[(size_t)2 * ni] = w * x1;
+    }
+#pragma unroll 1
+    for (int r = 0; r < kMarchRounds; ++r) {
+        const int d = 1 << (2 * r);
+        const cd al2 = al * shifted(al, -d), al3 = al2 * shifted(al, -2 * d);
+        const cd be2 = be * shifted(be, d), be3 = be2 * shifted(be, 2 * d);
+        if (act) {
+            cd* f = q + (size_t)(3 + 6 * r) * ni;
+            f[0] = al; f[ni] = al2; f[(size_t)2 * ni] = al3;
+            f[(size_t)3 * ni] = be; f[(size_t)4 * ni] = be2; f[(size_t)5 * ni] = be3;
         }
-        C2x2 K1 = Z, K2 = Z;
-        if (j < ni) {
-            K1 = hm ? Lm * inv2(Dm) : Z;
-            K2 = hp ? U * inv2(Dp) : Z;
-            const C2x2 Dn = D - K1 * Um - K2 * Lp;
-            const C2x2 Ln = neg(K1 * Lmm), Un = neg(K2 * Up);
-            D = Dn;
-            Lm = Ln;
-            U = Un;
-            cd* r = rec_v + (size_t)l * 8 * ni + j;
-            r[0 * ni] = K1.a; r[1 * ni] = K1.b; r[2 * ni] = K1.c; r[3 * ni] = K1.d;
-            r[4 * ni] = K2.a; r[5 * ni] = K2.b; r[6 * ni] = K2.c; r[7 * ni] = K2.d;
+        const double m1 = block_max(sqrt(fmax(abs2(al), abs2(be))));
+        const double m2_ = block_max(sqrt(fmax(abs2(al2), abs2(be2))));
+        if (j == 0) { ev[1 + 2 * r] = m1; ev[2 + 2 * r] = m2_; }
+        al = al2 * shifted(al2, -2 * d);
+        be = be2 * shifted(be2, 2 * d);
+    }
+    if (act) {
+        for (int m = 0; m < kMarchTb - 1; ++m) {
+            const int lag = m + 1;
+            cd c0 = zero, c1 = zero, c2 = zero, c3 = zero;
+            if (lag < nt) {
+                c0 = base[((size_t)(j + 1) * 4 + 0) * nt + lag];
+                if (j + 1 <= N - 2) c1 = base[((size_t)(j + 1) * 4 + 1) * nt + lag];
+                if (j >= 1) c2 = base[((size_t)j * 4 + 2) * nt + lag];
+                c3 = base[((size_t)j * 4 + 3) * nt + lag];
+            }
+            cd* f = q + (size_t)(kMarchLag0 + 4 * m) * ni;
+            f[0] = c0; f[ni] = c1; f[(size_t)2 * ni] = c2; f[(size_t)3 * ni] = c3;
         }
-        __syncthreads();
     }
 }
 
-struct NearGenArgs {
-    int N, nt, ns, per_problem;
-    int n0, nb, rec;
-    int levels;        // PCR levels run per step (the rest of the coupling is negligible)
-    const cd* cols;
-    const cd* pcr;     // [nv][rec]
-    const cd* base;    // [B][ns][TB]: d + far part
+struct MarchArgs {
+    int ni, nt, ns, per_problem;
+    int n0, nb;
+    int levels;        // doublings of the prefix sums
+    int inner, halo;   // interfaces per workgroup and on either side of them
+    const cd* rec;     // [nv][kMarchRows][ni]
+    const cd* base;    // [B][TB][ns]: d + far part
     cd* g;             // [B][ns][nt]
 };
 
-// one workgroup per problem; per step: gather the in-block history of every
-// slot (coefficients of lags 1..TB-1 in registers), then block PCR
-// One thread per interface j (slots 2j, 2j+1).  Per step: the right-hand
-// side from the base and the in-block lags (coefficients in registers,
-// earlier solutions in LDS), then the levels of block PCR exchanging through
-// two alternating LDS buffers (one barrier per level), with the multipliers
-// of the next level loaded while the current one runs.
-template <int THREADS, int TB>
-__global__ __launch_bounds__(THREADS) void causal_near_gen_kernel(NearGenArgs a) {
+// One block of TB steps.  A workgroup marches a window of THREADS interfaces,
+// thread by interface: the `inner` ones it answers for and up to `halo` on
+// either side, which it computes as well.  What a step's solution at an
+// interface depends on reaches 2^levels - 1 interfaces within the step and one
+// more through the lags, so with halo = TB 2^levels the inner values are those
+// of the whole system, bit for bit, and no workgroup waits for another.  With
+// the whole system in one window there is no halo.
+//
+// The right-hand sides of the block's steps sit in registers; a solved step
+// adds its share to all later ones (coefficients of the lags in registers).  A
+// step's exchanges go through LDS, one barrier each: the rounds of the two
+// prefix sums (multipliers of the first R in registers, the others in LDS or,
+// LDSC = false, read from memory) and the solution.
+//
+// Bound: the chain of exchanges (about 200 cycles each) and FP64 issue of one
+// to two waves per SIMD; the waves run at raised priority beside the sweeps.
+// Against block PCR on one workgroup (8 multipliers per interface and level
+// read from memory in every step, blocks of 8 steps to 512 interfaces and of 2
+// above, coefficients gathered with a stride at every launch), per block:
+// 255 interfaces, 16 potentials, 2 doublings 31.3 -> 11.6 us; 127 interfaces, 1
+// doubling 14.6 -> 7.2 us; 499 interfaces, 32 problems, 3 doublings 56 -> 21 us;
+// 999 interfaces, 5 doublings 26.8 us for 2 steps -> 18.2 us for 4, the solve on
+// 1000 subdomains over 500 steps 10.7 -> 4.6 ms.
+template <int THREADS, int TB, int R, bool LDSC>
+__global__ __launch_bounds__(THREADS) void causal_march_kernel(MarchArgs a) {
     extern __shared__ cd smem[];
-    const int ns = a.ns, nt = a.nt, n0 = a.n0, nb = a.nb, ni = a.N - 1;
-    cd* gh = smem;                          // [TB][ns]
-    cd* xa = gh + (size_t)TB * ns;          // [ns] exchange, even levels
-    cd* xb = xa + ns;                       // [ns] exchange, odd levels
-    const int b = blockIdx.x, v = a.per_problem ? b : 0;
-    const int j = threadIdx.x;
-    const bool act = j < ni;
-    const bool has_r = j + 1 <= a.N - 2, has_l = j >= 1;
-    const int lv = pcr_levels_for(ni);
+    constexpr int ROW = THREADS + 2;                   // entries tid + 1; both ends zero
+    cd* zb = smem;                                     // [2][ROW] prefix sums
+    cd* xb = smem + 2 * ROW;                           // [2][2][ROW] solution, by step parity
+    cd* sc = smem + 6 * ROW;                           // [rounds - R][6][THREADS]
+    __builtin_amdgcn_s_setprio(3);
+    const int tid = threadIdx.x, b = blockIdx.y, ni = a.ni, nb = a.nb;
+    const int i_lo = blockIdx.x * a.inner, i_hi = min(ni, i_lo + a.inner);
+    const int j = max(i_lo - a.halo, 0) + tid;
+    const bool act = j < ni, mine = j >= i_lo && j < i_hi;
     const cd zero = mk(0, 0);
-    cd* gb = a.g + (size_t)b * ns * nt;
-    const cd* bb = a.base + (size_t)b * ns * TB;
-    const cd* rec = a.pcr + (size_t)v * a.rec;
-    const cd* cb = a.cols + (size_t)v * a.N * 4 * nt;
-    // lag m+1 coefficients: slot 2j <- x1_j (c0), x0_{j+1} (c1);
-    //                       slot 2j+1 <- x1_{j-1} (c2), x0_j (c3)
+    const cd* rec = a.rec + (size_t)(a.per_problem ? b : 0) * kMarchRows * ni + (act ? j : 0);
+    const int rounds = (a.levels + 1) / 2;
+    const bool odd = a.levels & 1;                     // the last round doubles once
+
+    auto get = [&](int row) {
+        cd x = zero;
+        if (act) x = rec[(size_t)row * ni];
+        return x;
+    };
+    cd p[TB], l[TB];                                   // right-hand sides of slots 2j, 2j + 1
+    {
+        const cd* bb = a.base + (size_t)b * TB * a.ns + 2 * (act ? j : 0);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+            p[i] = l[i] = zero;
+            if (act && i < nb) {
+                p[i] = bb[(size_t)i * a.ns];
+                l[i] = bb[(size_t)i * a.ns + 1];
+            }
+        }
+    }
+    const cd A = get(0), W = get(1), O = get(2);
+    cd f[R > 0 ? R : 1][6];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            f[r][q] = zero;
+            if (r < rounds) f[r][q] = get(3 + 6 * r + q);
+        }
     cd c0[TB - 1], c1[TB - 1], c2[TB - 1], c3[TB - 1];
 #pragma unroll
     for (int m = 0; m < TB - 1; ++m) {
-        const int lag = m + 1;
-        c0[m] = c1[m] = c2[m] = c3[m] = zero;
-        if (act && lag < nt) {
-            c0[m] = cb[((size_t)(j + 1) * 4 + 0) * nt + lag];
-            if (has_r) c1[m] = cb[((size_t)(j + 1) * 4 + 1) * nt + lag];
-            if (has_l) c2[m] = cb[((size_t)j * 4 + 2) * nt + lag];
-            c3[m] = cb[((size_t)j * 4 + 3) * nt + lag];
-        }
+        c0[m] = get(kMarchLag0 + 4 * m);
+        c1[m] = get(kMarchLag0 + 4 * m + 1);
+        c2[m] = get(kMarchLag0 + 4 * m + 2);
+        c3[m] = get(kMarchLag0 + 4 * m + 3);
     }
-    const int lev = a.levels;
-    cd di0 = zero, di1 = zero, di2 = zero, di3 = zero;
-    if (act) {
-        const cd* Di = rec + ((size_t)lv * 8 + 4 * lev) * ni + j;
-        di0 = Di[0]; di1 = Di[1 * ni]; di2 = Di[2 * ni]; di3 = Di[3 * ni];
+    if (LDSC) {
+        for (int r = R; r < rounds; ++r)
+#pragma unroll
+            for (int q = 0; q < 6; ++q) sc[((r - R) * 6 + q) * THREADS + tid] = get(3 + 6 * r + q);
     }
-    auto loadK = [rec, ni, j, act](int l, cd (&K)[8]) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) K[q] = act ? rec[((size_t)l * 8 + q) * ni + j] : mk(0, 0);
-    };
-    // the 512-thread form loads the next level's multipliers while the
-    // current level runs; the 1024-thread form (128 registers) loads each
-    // level's when it starts
-    constexpr bool kPrefetch = THREADS <= 512;
-    cd Kc[8], Kn[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) Kc[q] = zero;
-    if (lev > 0) loadK(0, Kc);
-    // base of my two slots for every step of the block -> their entries of
-    // gh (only this thread reads them before its step overwrites them with
-    // the solution); the step loop touches no global memory
-    if (act) {
-        cd t0[TB], t1[TB];
-#pragma unroll
-        for (int i = 0; i < TB; ++i) {
-            t0[i] = zero;
-            t1[i] = zero;
-            if (i < nb) {
-                t0[i] = bb[(size_t)(2 * j) * TB + i];
-                t1[i] = bb[(size_t)(2 * j + 1) * TB + i];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < TB; ++i) {
-            if (i < nb) {
-                gh[(size_t)i * ns + 2 * j] = t0[i];
-                gh[(size_t)i * ns + 2 * j + 1] = t1[i];
-            }
-        }
-    }
+    if (tid < 12) smem[(tid >> 1) * ROW + (tid & 1) * (ROW - 1)] = zero;
 
+    // one prefix sum: dir = -1 from the left (multipliers 0 .. 2), +1 from the
+    // right (3 .. 5); s takes the same additions as z
+    int par = 0;
+    auto scan = [&](cd& z, cd& s, auto right) __attribute__((always_inline)) {
+        constexpr bool RIGHT = decltype(right)::value;
+        auto one_round = [&](int r, cd m1, cd m2, cd m3) __attribute__((always_inline)) {
+            const int d = 1 << (2 * r);
+            cd* buf = zb + par * ROW + tid + 1;
+            par ^= 1;
+            *buf = z;
+            __syncthreads();
+            auto at = [&](int k) {
+                const int o = RIGHT ? min(k * d, THREADS - tid) : max(-k * d, -1 - tid);
+                return buf[o];
+            };
+            cd e = m1 * at(1);
+            if (!(odd && r == rounds - 1)) e = madd(madd(e, m2, at(2)), m3, at(3));
+            z = z + e;
+            s = s + e;
+        };
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r < rounds) one_round(r, f[r][RIGHT ? 3 : 0], f[r][RIGHT ? 4 : 1], f[r][RIGHT ? 5 : 2]);
+        for (int r = R; r < rounds; ++r) {
+            cd m[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int k = q + (RIGHT ? 3 : 0);
+                if (LDSC) m[q] = sc[((r - R) * 6 + k) * THREADS + tid];
+                else m[q] = get(3 + 6 * r + k);
+            }
+            one_round(r, m[0], m[1], m[2]);
+        }
+    };
+    cd* gp = a.g + ((size_t)b * a.ns + 2 * (mine ? j : 0)) * a.nt + a.n0;
 #pragma unroll
     for (int i = 0; i < TB; ++i) {
         if (i < nb) {
-            cd p0 = zero, p1 = zero;
-            if (act) {
-                p0 = gh[(size_t)i * ns + 2 * j];
-                p1 = gh[(size_t)i * ns + 2 * j + 1];
-#pragma unroll
-                for (int m = 0; m < TB - 1; ++m) {
-                    const int lag = m + 1;
-                    if (lag <= i) {
-                        const cd* gs = gh + (size_t)(i - lag) * ns;
-                        p0 = madd(p0, c0[m], gs[2 * j + 1]);
-                        if (has_r) p0 = madd(p0, c1[m], gs[2 * j + 2]);
-                        if (has_l) p1 = madd(p1, c2[m], gs[2 * j - 1]);
-                        p1 = madd(p1, c3[m], gs[2 * j]);
-                    }
-                }
+            cd z = madd(l[i], A, p[i]), s = l[i];
+            scan(z, s, std::false_type{});
+            cd r = madd(W * p[i], O, s), dummy = zero;
+            scan(r, dummy, std::true_type{});
+            const cd x = madd(s, A, r);
+            if (mine) {
+                gp[i] = r;
+                gp[(size_t)a.nt + i] = x;
             }
-            for (int l = 0; l < lev; ++l) {
-                const int d = 1 << l;
-                if (kPrefetch) loadK(l + 1 < lev ? l + 1 : 0, Kn);   // next level (or next step's first)
-                else loadK(l, Kc);
-                cd* ex = (l & 1) ? xb : xa;
-                if (act) { ex[2 * j] = p0; ex[2 * j + 1] = p1; }
+            if (i + 1 < TB && i + 1 < nb) {
+                cd* rb = xb + (i & 1) * 2 * ROW + tid + 1;
+                cd* lb = rb + ROW;
+                *rb = r;
+                *lb = x;
                 __syncthreads();
-                if (act) {
-                    const bool hm = j - d >= 0, hp = j + d < ni;
-                    const cd q0m = hm ? ex[2 * (j - d)] : zero, q1m = hm ? ex[2 * (j - d) + 1] : zero;
-                    const cd q0p = hp ? ex[2 * (j + d)] : zero, q1p = hp ? ex[2 * (j + d) + 1] : zero;
-                    p0 = msub(msub(msub(msub(p0, Kc[0], q0m), Kc[1], q1m), Kc[4], q0p), Kc[5], q1p);
-                    p1 = msub(msub(msub(msub(p1, Kc[2], q0m), Kc[3], q1m), Kc[6], q0p), Kc[7], q1p);
+                const cd rn = rb[1], xp = lb[-1];
+#pragma unroll
+                for (int m = 0; m < TB - 1 - i; ++m) {
+                    p[i + 1 + m] = madd(madd(p[i + 1 + m], c0[m], x), c1[m], rn);
+                    l[i + 1 + m] = madd(madd(l[i + 1 + m], c2[m], xp), c3[m], r);
                 }
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    if (kPrefetch) Kc[q] = Kn[q];
-            }
-            if (act) {
-                const cd x0 = madd(di0 * p0, di1, p1);
-                const cd x1 = madd(di2 * p0, di3, p1);
-                gh[(size_t)i * ns + 2 * j] = x0;
-                gh[(size_t)i * ns + 2 * j + 1] = x1;
-            }
-            __syncthreads();
-        }
-    }
-    // my two slots' solutions of the block -> memory (kept out of the step
-    // loop: its multiplier loads would otherwise wait for these stores)
-    if (act) {
-#pragma unroll
-        for (int i = 0; i < TB; ++i) {
-            if (i < nb) {
-                gb[(size_t)(2 * j) * nt + n0 + i] = gh[(size_t)i * ns + 2 * j];
-                gb[(size_t)(2 * j + 1) * nt + n0 + i] = gh[(size_t)i * ns + 2 * j + 1];
             }
         }
     }
 }
 
-hipError_t launch_causal_pcr_setup_gen(int N, int nt, int nv, const cd* cols, cd* pcr, double* eta,
-                                       hipStream_t st) {
-    if (N - 1 > kGenMaxIf) return hipErrorInvalidValue;
-    if (gen_threads(N) == 512)
-        causal_pcr_setup_gen_kernel<512><<<nv, 512, 0, st>>>(N, nt, cols, pcr, pcr_rec_gen(N), eta);
-    else
-        causal_pcr_setup_gen_kernel<1024><<<nv, 1024, 0, st>>>(N, nt, cols, pcr, pcr_rec_gen(N), eta);
+// How a system is marched.  Up to 256 interfaces, one workgroup of one wave per
+// SIMD takes the whole of it; up to 512, two.  Above, windows of 512 with halos
+// of at most 128, i.e. blocks of 8 steps for up to 4 doublings and of 4 for 5
+// (the halves that the halos cost are other CUs' time); with more doublings
+// the halos would leave nothing, and one workgroup of 1024 threads, with
+// registers for two steps, takes the system.  More than 6 doublings' multipliers
+// do not fit in LDS beside blocks of 8 steps.
+struct MarchPlan { int threads, tb, inner, halo; };
+static MarchPlan march_plan(int ni, int levels) {
+    if (ni <= 256) return {256, 8, ni, 0};
+    if (ni <= 512) return {512, levels <= 6 ? 8 : 4, ni, 0};
+    if (levels <= 5) {
+        const int tb = levels <= 4 ? 8 : 4, halo = tb << levels;
+        return {512, tb, 512 - 2 * halo, halo};
+    }
+    return {1024, 2, ni, 0};
+}
+int march_tb(int N, int levels) { return march_plan(N - 1, levels).tb; }
+
+hipError_t launch_causal_march_setup(int N, int nt, int nv, const cd* cols, cd* rec, double* eta,
+                                     hipStream_t st) {
+    if (N < 2 || N - 1 > kGenMaxIf) return hipErrorInvalidValue;
+    if (N - 1 <= 256) causal_march_setup_kernel<256><<<nv, 256, 0, st>>>(N, nt, cols, rec, eta);
+    else if (N - 1 <= 512) causal_march_setup_kernel<512><<<nv, 512, 0, st>>>(N, nt, cols, rec, eta);
+    else causal_march_setup_kernel<1024><<<nv, 1024, 0, st>>>(N, nt, cols, rec, eta);
     return hipGetLastError();
 }
 
-hipError_t launch_causal_gen(int N, int nt, int ns, int B, int per_problem, const cd* cols,
-                             const cd* pcr, int levels, const cd* d, cd* base, cd* g, int n_lo,
-                             int n_hi, const cd* facc, int s_from, hipStream_t st) {
-    const size_t shm = gen_shm(N);
-    const int tb = gen_tb(N), threads = gen_threads(N);
-    if (N - 1 > kGenMaxIf || N - 1 > threads || ns != 2 * (N - 1) || shm > 160 * 1024)
+template <int THREADS, int TB, int R, bool LDSC>
+static hipError_t launch_march(const MarchArgs& a, int B, hipStream_t st) {
+    const int rounds = (a.levels + 1) / 2, more = LDSC ? std::max(0, rounds - R) : 0;
+    const size_t lds = sizeof(cd) * (6 * (size_t)(THREADS + 2) + (size_t)more * 6 * THREADS);
+    if (lds > 160 * 1024) return hipErrorInvalidValue;
+    // (the halos may reach past the window's threads only where nothing is left)
+    const int wins = (a.ni + a.inner - 1) / a.inner;
+    if (wins > 1 && a.inner + 2 * a.halo > THREADS) return hipErrorInvalidValue;
+    if (wins == 1 && a.ni > THREADS) return hipErrorInvalidValue;
+    causal_march_kernel<THREADS, TB, R, LDSC><<<dim3(wins, B), THREADS, lds, st>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_causal_gen(int N, int nt, int ns, int B, int per_problem, const cd* cols, const cd* rec,
+                             int levels, const cd* d, cd* base, cd* g, int n_lo, int n_hi, const cd* facc,
+                             int s_from, hipStream_t st) {
+    if (N < 2 || N - 1 > kGenMaxIf || ns != 2 * (N - 1) || levels < 0 || levels > kGenLevelsMax)
         return hipErrorInvalidValue;
-    if (levels < 0 || levels > pcr_levels_for(N - 1)) return hipErrorInvalidValue;
+    const MarchPlan pl = march_plan(N - 1, levels);
+    const int tb = pl.tb;
     if (n_lo % tb != 0 || n_lo < 0 || n_hi > nt || s_from < 0 || s_from > n_lo)
         return hipErrorInvalidValue;
     for (int n0 = n_lo; n0 < n_hi; n0 += tb) {
         const int nb = min(tb, n_hi - n0);
-        hipError_t e = (tb == 8)
-            ? launch_causal_far<8>(N, nt, ns, B, per_problem, n0, nb, cols, d, g, base, facc, s_from, st)
-            : launch_causal_far<2>(N, nt, ns, B, per_problem, n0, nb, cols, d, g, base, facc, s_from, st);
+        auto far = tb == 8 ? launch_causal_far<8> : tb == 4 ? launch_causal_far<4> : launch_causal_far<2>;
+        hipError_t e = far(N, nt, ns, B, per_problem, n0, nb, cols, d, g, base, facc, s_from, st);
         if (e != hipSuccess) return e;
-        NearGenArgs na{N, nt, ns, per_problem, n0, nb, pcr_rec_gen(N), levels, cols, pcr, base, g};
-        if (tb == 8) causal_near_gen_kernel<512, 8><<<B, 512, shm, st>>>(na);
-        else causal_near_gen_kernel<1024, 2><<<B, 1024, shm, st>>>(na);
-        e = hipGetLastError();
+        MarchArgs m{N - 1, nt, ns, per_problem, n0, nb, levels, pl.inner, pl.halo, rec, base, g};
+        if (pl.threads == 256) e = launch_march<256, 8, 1, true>(m, B, st);
+        else if (pl.threads == 512 && tb == 8) e = launch_march<512, 8, 1, true>(m, B, st);
+        else if (pl.threads == 512) e = launch_march<512, 4, 3, true>(m, B, st);
+        else e = launch_march<1024, 2, 1, false>(m, B, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -44,12 +44,12 @@ struct Iface {
     int ntasks = 0;
     int nv = 1;
     bool dirty = true;      // columns rebuilt since the causal setup
-    int path = 0;           // causal solver: 1 = one-wave block PCR, 2 = workgroup block
-                            // PCR, 3 = dense inverse, 0 = not offered (valid once !dirty)
-    cd* pcr = nullptr;
+    int path = 0;           // causal solver: 1 = one-wave block PCR, 2 = prefix sums on a
+                            // workgroup, 3 = dense inverse, 0 = not offered (valid once !dirty)
+    cd* pcr = nullptr;      // record of path 1 or 2
     size_t pcr_size = 0;
     double* eta = nullptr;
-    int levels = 0;         // PCR levels run per step (coupling left <= 2^-60)
+    int levels = 0;         // levels (doublings) run per step (coupling left <= 2^-60)
     double eta0 = 0;        // block dominance measure of (I - C_0)
     cd* Minv = nullptr;
     cd* Mwork = nullptr;
@@ -1250,7 +1250,7 @@ static swr_status run_bicgstab(swr_ctx* c, const Op& A, const cd* rhs, cd* x, in
 }
 
 // The causal solve needs the per-step block system (I - C_0) in a form it
-// can solve quickly: block PCR on one wave or one workgroup, or a dense
+// can solve quickly: block elimination on one wave or on workgroups, or a dense
 // inverse for at most kDenseMaxSlots slots.  Beyond that it is not offered:
 // (I - L) g = d is solved by BiCGStab on the same operator instead, and P^{-1}
 // of the preconditioned iterations by an inner BiCGStab (the paper's own way
@@ -1261,10 +1261,10 @@ constexpr double kInnerTol = 1e-13;
 // for this system; the caller switches to BiCGStab
 constexpr swr_status kCausalOff = static_cast<swr_status>(7);
 
-// block PCR on one wave (fast) or on one workgroup (general)
+// block PCR on one wave (fast) or prefix sums on workgroups (general)
 static bool causal_fast_ok(const swr_ctx* c) { return c->ns <= kNearSlots && c->N - 1 <= kWave; }
 static bool causal_gen_ok(const swr_ctx* c) {
-    return c->N - 1 <= kGenMaxIf && gen_shm(c->N) <= 160 * 1024;
+    return c->N >= 2 && c->N - 1 <= kGenMaxIf;
 }
 
 static bool causal_sized(const swr_ctx* c) {
@@ -1308,9 +1308,9 @@ static swr_status apply_inverse(swr_ctx* c, Iface& I, const cd* rhs, cd* x) {
 }
 
 // causal forward substitution in time for (I - L) g = d with the operator I
-// (exact up to rounding).  Block PCR per step when the block system is
+// (exact up to rounding).  Block elimination per step when the block system is
 // certified diagonally dominant: on one wave for N - 1 <= 64 interfaces, on
-// a workgroup up to kGenMaxIf; otherwise (at most kDenseMaxSlots slots) a
+// workgroups up to kGenMaxIf; otherwise (at most kDenseMaxSlots slots) a
 // dense (I - C_0)^{-1} by Gauss-Jordan with partial pivoting.
 static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream_t st,
                              int n_lo, int n_hi) {
@@ -1326,31 +1326,33 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
         I.built_version = ver;
         I.path = 3;
         if (fast_ok || gen_ok) {
-            const size_t rec = fast_ok ? causal_fast_rec() : (size_t)pcr_rec_gen(c->N);
+            const size_t rec = fast_ok ? causal_fast_rec() : (size_t)kMarchRows * ni;
             if (!I.pcr || I.pcr_size < rec * I.nv) {
                 ALLOC_LIVE(I.pcr, rec * I.nv);
                 I.pcr_size = rec * I.nv;
             }
-            // eta[v][l]: ||D_l^{-1}|| (||L_l|| + ||U_l||) of the system before level l
+            // eta[v][l]: ||D_l^{-1}|| (||L_l|| + ||U_l||) of the system before level l;
+            // general path: that of the system itself, then the largest product of
+            // the prefix sums' multipliers over 2^l interfaces, l = 0 ..
             const int ld = fast_ok ? kPcrLevels + 1 : kGenLevelsMax + 1;
-            const int L = fast_ok ? kPcrLevels : pcr_levels_for(ni);
+            const int L = fast_ok ? kPcrLevels : kGenLevelsMax, l0 = fast_ok ? 0 : 1;
             if (!I.eta) ALLOC_LIVE(I.eta, (size_t)I.nv * (kGenLevelsMax + 1));
             if (fast_ok) HIPCHK(launch_causal_pcr_setup(c->N, nt, I.nv, I.cols, I.pcr, I.eta, st));
-            else HIPCHK(launch_causal_pcr_setup_gen(c->N, nt, I.nv, I.cols, I.pcr, I.eta, st));
+            else HIPCHK(launch_causal_march_setup(c->N, nt, I.nv, I.cols, I.pcr, I.eta, st));
             std::vector<double> eta((size_t)I.nv * ld);
             HIPCHK(hipMemcpyAsync(eta.data(), I.eta, sizeof(double) * eta.size(), hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
-            // block diagonal dominance (eta_0 < 1) makes block PCR stable and
-            // squares the coupling every level; levels past the first l with
-            // eta_l <= 2^-60 change no FP64 result and are skipped
+            // block diagonal dominance (eta_0 < 1) makes block PCR and block
+            // elimination stable, and the coupling falls from level to level: those
+            // past the first with a measure <= 2^-60 change no FP64 result
             bool ok = true;
             int lev = 0;
             for (int v = 0; v < I.nv; ++v) {
                 const double* ev = eta.data() + (size_t)v * ld;
                 ok = ok && std::isfinite(ev[0]) && ev[0] < 1.0;
                 int lv = L;
-                for (int l = 0; l <= L; ++l)
-                    if (std::isfinite(ev[l]) && ev[l] <= kPcrNegligible) { lv = l; break; }
+                for (int l = 0; l0 + l < ld && l <= L; ++l)
+                    if (std::isfinite(ev[l0 + l]) && ev[l0 + l] <= kPcrNegligible) { lv = l; break; }
                 lev = std::max(lev, lv);
             }
             I.levels = lev;
@@ -1372,7 +1374,7 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
     }
     if (I.path == 0) return kCausalOff;
     if (I.path == 1 || I.path == 2) {
-        const int tb = I.path == 1 ? kNearTb : gen_tb(c->N);
+        const int tb = I.path == 1 ? kNearTb : march_tb(c->N, I.levels);
         if (!c->dBase || c->base_tb < tb) {
             ALLOC_LIVE(c->dBase, (size_t)B * ns * tb);
             c->base_tb = tb;
