@@ -146,9 +146,9 @@ struct FarArgs {
     const cd* d;       // [B][ns][nt]
     const cd* g;       // [B][ns][nt]
     cd* out;           // d + contribution of steps s < n0: [B][ns][kTb], or [B][TB][ns] (far_out)
-    const cd* facc;    // [nseg][B][ns][kCausalSuper]: contribution of each finished
-                       // super-block to steps s_from .. s_from + kCausalSuper - 1
-    int nseg;          // number of finished super-blocks (facc null when 0)
+    const cd* facc;    // [nseg][B][ns][kCausalSuper]: contributions of the finished
+                       // super-blocks to steps s_from .. s_from + kCausalSuper - 1
+    int nseg;          // partials they come in (facc null when 0)
     int s_from;        // this kernel sums steps s_from <= s < n0
     int B;             // problems
 };
@@ -666,12 +666,12 @@ hipError_t launch_causal_pcr_setup(int N, int nt, int nv, const cd* cols, cd* pc
 template <int TB>
 static hipError_t launch_causal_far(int N, int nt, int ns, int B, int per_problem, int n0, int nb,
                                     const cd* cols, const cd* d, const cd* g, cd* out,
-                                    const cd* facc, int s_from, hipStream_t st) {
+                                    const cd* facc, int nseg, int s_from, hipStream_t st) {
     // the staged rows hold less than one super-block of sources
     if (n0 - s_from < 0 || n0 - s_from >= kCausalSuper) return hipErrorInvalidValue;
     if (ns != 2 * (N - 1)) return hipErrorInvalidValue;
     FarArgs f{N, nt, ns, per_problem, n0, nb, cols, d, g, out, facc,
-              facc ? s_from / kCausalSuper : 0, s_from, B};
+              facc ? nseg : 0, s_from, B};
     if constexpr (TB == 8 || TB == 32) {
         if (!per_problem && B >= kFarMfmaB) {
             causal_far_mfma_kernel<TB><<<dim3(N, (B + kFarMfmaB - 1) / kFarMfmaB), 64, 0, st>>>(f);
@@ -696,13 +696,13 @@ hipError_t launch_causal_near(int N, int nt, int ns, int B, int per_problem, int
 // the whole forward substitution: far part then near march, block by block
 hipError_t launch_causal_fast(int N, int nt, int ns, int B, int per_problem, const cd* cols,
                               const cd* pcr, int levels, const cd* d, cd* base, cd* g, int n_lo,
-                              int n_hi, const cd* facc, int s_from, hipStream_t st) {
+                              int n_hi, const cd* facc, int nseg, int s_from, hipStream_t st) {
     if (n_lo % kTb != 0 || n_lo < 0 || n_hi > nt || s_from < 0 || s_from > n_lo)
         return hipErrorInvalidValue;
     for (int n0 = n_lo; n0 < n_hi; n0 += kTb) {
         const int nb = min(kTb, n_hi - n0);
         hipError_t e = launch_causal_far<kTb>(N, nt, ns, B, per_problem, n0, nb, cols, d, g, base,
-                                              facc, s_from, st);
+                                              facc, nseg, s_from, st);
         if (e != hipSuccess) return e;
         e = launch_causal_near(N, nt, ns, B, per_problem, n0, nb, cols, pcr, levels, base, g, st);
         if (e != hipSuccess) return e;
@@ -1024,7 +1024,7 @@ static hipError_t launch_march(const MarchArgs& a, int B, hipStream_t st) {
 
 hipError_t launch_causal_gen(int N, int nt, int ns, int B, int per_problem, const cd* cols, const cd* rec,
                              int levels, const cd* d, cd* base, cd* g, int n_lo, int n_hi, const cd* facc,
-                             int s_from, hipStream_t st) {
+                             int nseg, int s_from, hipStream_t st) {
     if (N < 2 || N - 1 > kGenMaxIf || ns != 2 * (N - 1) || levels < 0 || levels > kGenLevelsMax)
         return hipErrorInvalidValue;
     const MarchPlan pl = march_plan(N - 1, levels);
@@ -1034,7 +1034,7 @@ hipError_t launch_causal_gen(int N, int nt, int ns, int B, int per_problem, cons
     for (int n0 = n_lo; n0 < n_hi; n0 += tb) {
         const int nb = min(tb, n_hi - n0);
         auto far = tb == 8 ? launch_causal_far<8> : tb == 4 ? launch_causal_far<4> : launch_causal_far<2>;
-        hipError_t e = far(N, nt, ns, B, per_problem, n0, nb, cols, d, g, base, facc, s_from, st);
+        hipError_t e = far(N, nt, ns, B, per_problem, n0, nb, cols, d, g, base, facc, nseg, s_from, st);
         if (e != hipSuccess) return e;
         MarchArgs m{N - 1, nt, ns, per_problem, n0, nb, levels, pl.inner, pl.halo, rec, base, g};
         if (pl.threads == 256) e = launch_march<256, 8, 1, true>(m, B, st);

@@ -453,6 +453,7 @@ hipError_t launch_finalize_snaps(int N, int nx, int B, int S, const int* off, co
 hipError_t launch_beta(int n, double* beta, hipStream_t st);
 // launchers (swr_iface.hip)
 hipError_t launch_ltt(const LttArgs& a, hipStream_t st);
+int ltt_seg_blocks(int ns, int B, bool per_problem, int nblk);
 hipError_t launch_lincomb(const cd* x0, const cd* x1, const cd* x2, const cd* coef, cd* z, long M,
                           int B, hipStream_t st);
 hipError_t launch_multidot(const cd* basis, int nv, const cd* w, long M, int B, double* partial,
@@ -490,7 +491,7 @@ hipError_t launch_causal_pcr_setup(int N, int nt, int nv, const cd* cols, cd* pc
                                    hipStream_t st);
 hipError_t launch_causal_fast(int N, int nt, int ns, int B, int per_problem, const cd* cols,
                               const cd* pcr, int levels, const cd* d, cd* base, cd* g, int n_lo,
-                              int n_hi, const cd* facc, int s_from, hipStream_t st);
+                              int n_hi, const cd* facc, int nseg, int s_from, hipStream_t st);
 // general causal solve for up to kGenMaxIf interfaces (causal_march_kernel)
 constexpr int kCausalSuper = 256;    // causal solve super-block (time steps)
 constexpr int kGenMaxIf = 1024;
@@ -507,7 +508,7 @@ hipError_t launch_causal_march_setup(int N, int nt, int nv, const cd* cols, cd* 
                                      hipStream_t st);
 hipError_t launch_causal_gen(int N, int nt, int ns, int B, int per_problem, const cd* cols,
                              const cd* pcr, int levels, const cd* d, cd* base, cd* g, int n_lo,
-                             int n_hi, const cd* facc, int s_from, hipStream_t st);
+                             int n_hi, const cd* facc, int nseg, int s_from, hipStream_t st);
 struct AdjArgs {
     int N, nt, B, nx, ns, Jc;
     int pstride;                 // record stride of checkpoints, segments and state, as SweepArgs

@@ -1391,23 +1391,26 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
         for (int a0 = n_lo; a0 < n_hi;) {
             const int S = a0 / kCausalSuper * kCausalSuper;
             const int a1 = std::min(n_hi, S + kCausalSuper);
+            int nseg = 0;
             if (S > 0) {
-                // one partial per finished super-block (split over the sources)
+                // in partials of a few finished super-blocks each (split over the sources)
+                const int nblk = S / kCausalSuper, per = ltt_seg_blocks(ns, B, I.nv > 1, nblk);
+                nseg = (nblk + per - 1) / per;
                 LttArgs l{};
                 l.N = c->N; l.nt = nt; l.ns = ns; l.B = B; l.per_problem = I.nv > 1;
                 l.cols = I.cols; l.x = g; l.y = c->dFacc + (a0 - S); l.base = nullptr;
                 l.sign = 1.0; l.n_lo = a0; l.n_hi = a1; l.s_lo = 0; l.s_hi = S;
-                l.y_ld = kCausalSuper; l.s_seg = kCausalSuper;
+                l.y_ld = kCausalSuper; l.s_seg = per * kCausalSuper;
                 l.y_seg_stride = (size_t)B * ns * kCausalSuper;
                 HIPCHK(launch_ltt(l, st));
             }
             const cd* facc = S > 0 ? c->dFacc : nullptr;
             if (I.path == 1)
                 HIPCHK(launch_causal_fast(c->N, nt, ns, B, I.nv > 1, I.cols, I.pcr, I.levels, d,
-                                          c->dBase, g, a0, a1, facc, S, st));
+                                          c->dBase, g, a0, a1, facc, nseg, S, st));
             else
                 HIPCHK(launch_causal_gen(c->N, nt, ns, B, I.nv > 1, I.cols, I.pcr, I.levels, d,
-                                         c->dBase, g, a0, a1, facc, S, st));
+                                         c->dBase, g, a0, a1, facc, nseg, S, st));
             a0 = a1;
         }
         return SWR_OK;

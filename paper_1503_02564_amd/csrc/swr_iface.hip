@@ -30,56 +30,61 @@ __device__ inline void slot_sources(int o, int N, int& k, int& pl, int& pr, int&
 // of y on targets n = n_lo + 16 I + row from sources s = s_lo + 16 J + kk is
 //     y_I += T_{I-J} x_J,   T_m[row][kk] = c[delta + 16 m + row - kk],
 // delta = n_lo - s_lo: every 16 x 16 block of a lower-triangular Toeplitz
-// matrix is itself Toeplitz, fixed by the lag block m = I - J.  One wave owns
-// 16 consecutive target blocks I0 .. I0+15 (256 outputs) as the columns of a
-// 16 x 16 accumulator and, for each lag block m, multiplies T_m (A operand,
-// 16 x 16 in four k-slices of 4) by the 16 source blocks I0+col-m (B
-// operand) with v_mfma_f64_16x16x4_f64.  Complex products use the real
-// embedding: Re y += Re T Re x - Im T Im x, Im y += Re T Im x + Im T Re x.
-// Lags < 0 (s > n) and sources outside [s_lo, s_hi) enter as zeros.
+// matrix is itself Toeplitz, fixed by the lag block m = I - J.  The columns of
+// a product are (target block, real or imaginary part of x): eight target
+// blocks I0 .. I0+7 (128 outputs) meet, for each lag block m, their source
+// blocks I - m (B operand) with T_m (A operand, 16 x 16 in four k-slices of 4)
+// by v_mfma_f64_16x16x4_f64.  Two accumulators collect Re T [Re x | Im x] and
+// Im T [Re x | Im x], combined at the end between neighbouring lanes (Re y = Re
+// T Re x - Im T Im x, Im y = Re T Im x + Im T Re x).  Lags < 0 (s > n) and
+// sources outside [s_lo, s_hi) enter as zeros.
 // Operand layout of the instruction (wave64): lane l supplies A[l%16][l/16]
 // and B[l/16][l%16]; accumulator register q of lane l is D[l/16+4q][l%16]
 // (checked on the device against a host product).
+//
+// One workgroup takes 256 outputs of one slot; its four waves are (half of the
+// outputs, left or right source row).  The lag blocks are walked upwards, i.e.
+// the sources backwards, 16 at a time: the 271 coefficients and 31 source
+// blocks that 16 lag blocks touch are staged in LDS, the next stage's loads in
+// flight meanwhile.  Of the Jn + 7 lag blocks of a half, Jn do full work: 94 %
+// for 7 finished super-blocks of 256 sources walked at once, where products of
+// one super-block each with 16 target blocks as columns had 52 %.  The terms of
+// an output and their order depend on s_lo and s_hi only, never on the range of
+// outputs, so splitting that range changes no result bit.
+//
+// Bound: the matrix cores (64 cycles an instruction per SIMD).  Before (one
+// super-block at a time, 16 target blocks as columns; longer ranges on one wave
+// per 256 outputs, operands from memory) and now: 16 potentials, 510 slots, 256
+// outputs from on average 3.5 super-blocks 1180 -> 582 us (52 TFLOP/s of useful
+// work); the whole operator on 62 slots and 800 steps 136 -> 20 us.
 // ---------------------------------------------------------------------------
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 __device__ inline d4 mfma16(double a, double b, d4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
+__device__ inline double swap_pair(double v) {   // the value of lane l ^ 1
+    int2 t = *reinterpret_cast<int2*>(&v);
+    t.x = __builtin_amdgcn_mov_dpp(t.x, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
+    t.y = __builtin_amdgcn_mov_dpp(t.y, 0xB1, 0xf, 0xf, false);
+    return *reinterpret_cast<double*>(&t);
+}
 
-// With one 256-step target tile and a source range of at most 256 steps (the
-// causal solve's history products), the workgroup first stages the sources
-// and the coefficient window they meet (at most 511 lags) in LDS with
-// coalesced loads by all four waves, so the lag-block loop reads its operands
-// from LDS instead of waiting on memory every block.  The four waves then
-// share the tile: wave w takes k-slice w (sources 4w .. 4w+3 of every
-// 16-step source block) of every lag block, with one accumulator pair per
-// side (four independent MFMA chains), and the partial sums are added in a
-// fixed order (sides, then waves).  For a given output the terms and their
-// order do not depend on the output range of the call, so splitting a range
-// changes no result bit; the rounding differs from the one-wave form used
-// for longer ranges by the order of the sum.
 constexpr int kLttStage = 256;
-
-// staged sources: entry e at e + e / 16, so the 16 B-operand lanes of one
-// instruction (sources 16 apart) fall in different LDS banks
-__device__ inline int ltt_xpad(int e) { return e + (e >> 4); }
+constexpr int kLttCoef = 272;     // staged lags of 16 lag blocks (271 used)
+constexpr int kLttSrc = 31;       // staged source blocks
+constexpr int kLttPad = 20;       // entries per source block: eight blocks' operands in all LDS banks
 
 __global__ __launch_bounds__(256) void ltt_mfma_kernel(LttArgs a) {
-    __shared__ cd st_x[2][kLttStage + kLttStage / 16], st_c[2][2 * kLttStage];
-    __shared__ d4 red[4][2][kWave];               // staged form: the waves' accumulators
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const int tile = blockIdx.x * 4 + w;
+    __shared__ cd st_c[2][kLttCoef], st_x[2][kLttSrc * kLttPad];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    const int half = w & 1, side = w >> 1;
     const int o = blockIdx.y;
     const int b = a.s_seg > 0 ? blockIdx.z % a.B : blockIdx.z;
     const int seg = a.s_seg > 0 ? blockIdx.z / a.B : 0;
-    const int nlen = a.n_hi - a.n_lo;
-    const int s_lo0 = a.s_seg > 0 ? a.s_lo + seg * a.s_seg : a.s_lo;
-    const int s_hi0 = a.s_seg > 0 ? min(a.s_hi, s_lo0 + a.s_seg) : a.s_hi;
-    const bool staged = nlen <= kLttStage && s_hi0 - s_lo0 <= kLttStage;   // uniform per workgroup
-    if (!staged && tile * 256 >= nlen) return;       // whole wave leaves together
-    const int s_lo = s_lo0;
-    const int s_hi = s_hi0;
+    const int n_lo = a.n_lo + blockIdx.x * 256, nlen = min(256, a.n_hi - n_lo);
+    const int s_lo = a.s_seg > 0 ? a.s_lo + seg * a.s_seg : a.s_lo;
+    const int s_hi = a.s_seg > 0 ? min(a.s_hi, s_lo + a.s_seg) : a.s_hi;
     int k, pl, pr, sl, sr;
     slot_sources(o, a.N, k, pl, pr, sl, sr);
     const int v = a.per_problem ? b : 0;
@@ -87,137 +92,105 @@ __global__ __launch_bounds__(256) void ltt_mfma_kernel(LttArgs a) {
     const cd* cr = a.cols + ((size_t)(v * a.N + k) * 4 + pr) * a.nt;
     const cd* xl = sl >= 0 ? a.x + ((size_t)b * a.ns + sl) * a.nt + s_lo : nullptr;
     const cd* xr = sr >= 0 ? a.x + ((size_t)b * a.ns + sr) * a.nt + s_lo : nullptr;
-    // staged form: sources s_lo + [0, slen) and lags lag0 + [0, nlen + slen - 1)
-    const int lag0 = a.n_lo - s_hi + 1;
-    if (staged) {
-        const int slen0 = s_hi - s_lo, nlag = nlen + slen0 - 1;
-        for (int e = threadIdx.x; e < kLttStage; e += blockDim.x) {
-            cd x0 = mk(0, 0), x1 = mk(0, 0);
-            if (xl && e < slen0) x0 = xl[e];
-            if (xr && e < slen0) x1 = xr[e];
-            st_x[0][ltt_xpad(e)] = x0;
-            st_x[1][ltt_xpad(e)] = x1;
-        }
-        for (int e = threadIdx.x; e < 2 * kLttStage; e += blockDim.x) {
-            const int lag = lag0 + e;
-            const bool ok = e < nlag && lag >= 0 && lag < a.nt;
-            cd c0 = mk(0, 0), c1 = mk(0, 0);
-            if (xl && ok) c0 = cl[lag];
-            if (xr && ok) c1 = cr[lag];
-            st_c[0][e] = c0;
-            st_c[1][e] = c1;
-        }
-        __syncthreads();
-    }
     const int r = lane & 15, kq = lane >> 4;
-    const int I0 = staged ? 0 : tile * 16;
-    const int slen = s_hi - s_lo;
-    const int Jn = (slen + 15) / 16;
-    const int delta = a.n_lo - s_lo;
+    const int slen = s_hi - s_lo, Jn = (slen + 15) / 16, In = (nlen + 15) / 16;
+    const int delta = n_lo - s_lo;
     // lag blocks that can meet a source block J in [0, Jn) and a lag >= 0
-    const int q = -delta - 15;
-    const int m_lag = q >= 0 ? (q + 15) / 16 : -((-q) / 16);
-    const int m_lo = max(I0 - (Jn - 1), m_lag);
-    const int m_hi = slen > 0 ? I0 + 15 : m_lo - 1;
-    d4 yr = {0, 0, 0, 0}, yi = {0, 0, 0, 0};
-    // the lag-block loop of the one-wave form, operands from memory
-    auto blocks = [&](auto opA, auto opB) {
-        for (int m = m_lo; m <= m_hi; ++m) {
-            const int J = I0 + r - m;               // source block of B column r
+    const int q0 = -delta - 15;
+    const int m_lag = q0 >= 0 ? (q0 + 15) / 16 : -((-q0) / 16);
+    const int m_lo = max(1 - Jn, m_lag), m_hi = slen > 0 ? In - 1 : m_lo - 1;
+    const int h_lo = max(m_lo, 8 * half + 1 - Jn), h_hi = 8 * half < In ? min(m_hi, 8 * half + 7) : h_lo - 1;
+
+    // stage of the lag blocks mc .. mc + 15: lag delta + 16 mc - 15 + e at e,
+    // source block J at J + mc + 15
+    constexpr int kIc = (2 * kLttCoef + 255) / 256, kIx = 2 * kLttSrc * 16 / 256 + 1;
+    cd tc[kIc], tx[kIx];
+    auto fetch = [&](int mc) {
 #pragma unroll
-            for (int kc = 0; kc < 4; ++kc) {
-                const int kk = 4 * kc + kq;
-                const int lag = delta + 16 * m + r - kk;
-                const int si = 16 * J + kk;
-                const bool sok = J >= 0 && si < slen;
+        for (int u = 0; u < kIc; ++u) {
+            const int i = u * 256 + tid, sd = i >= kLttCoef, lag = delta + 16 * mc - 15 + i - sd * kLttCoef;
+            tc[u] = mk(0, 0);
+            if (i < 2 * kLttCoef && (sd ? xr : xl) && lag >= 0 && lag < a.nt) tc[u] = (sd ? cr : cl)[lag];
+        }
 #pragma unroll
-                for (int side = 0; side < 2; ++side) {
-                    if (side == 0 ? !xl : !xr) continue;
-                    const cd av = opA(side, lag);
-                    cd bv = mk(0, 0);
-                    if (sok) bv = opB(side, si);
-                    yr = mfma16(av.x, bv.x, yr);
-                    yr = mfma16(-av.y, bv.y, yr);
-                    yi = mfma16(av.x, bv.y, yi);
-                    yi = mfma16(av.y, bv.x, yi);
-                }
-            }
+        for (int u = 0; u < kIx; ++u) {
+            const int i = u * 256 + tid, sd = i >= kLttSrc * 16, e = i - sd * kLttSrc * 16;
+            const int si = 16 * (-mc - 15) + e;
+            const cd* x = sd ? xr : xl;
+            tx[u] = mk(0, 0);
+            if (i < 2 * kLttSrc * 16 && x && si >= 0 && si < slen) tx[u] = x[si];
         }
     };
-    if (staged) {
-        // a lag outside the window pairs only with sources outside [0, slen)
-        // or outputs past nlen, i.e. with a zero operand or a dropped result
-        const int kk = 4 * w + kq;
-        d4 ar0 = {0, 0, 0, 0}, ai0 = {0, 0, 0, 0}, ar1 = {0, 0, 0, 0}, ai1 = {0, 0, 0, 0};
-        for (int m = m_lo; m <= m_hi; ++m) {
-            const int J = I0 + r - m;               // source block of B column r
-            const int le = delta + 16 * m + r - kk - lag0;
-            const int si = 16 * J + kk;
-            const bool sok = J >= 0 && si < slen;
-            const bool lok = le >= 0 && le < 2 * kLttStage;
-            if (xl) {
-                cd av = mk(0, 0), bv = mk(0, 0);
-                if (lok) av = st_c[0][le];
-                if (sok) bv = st_x[0][ltt_xpad(si)];
-                ar0 = mfma16(av.x, bv.x, ar0);
-                ar0 = mfma16(-av.y, bv.y, ar0);
-                ai0 = mfma16(av.x, bv.y, ai0);
-                ai0 = mfma16(av.y, bv.x, ai0);
-            }
-            if (xr) {
-                cd av = mk(0, 0), bv = mk(0, 0);
-                if (lok) av = st_c[1][le];
-                if (sok) bv = st_x[1][ltt_xpad(si)];
-                ar1 = mfma16(av.x, bv.x, ar1);
-                ar1 = mfma16(-av.y, bv.y, ar1);
-                ai1 = mfma16(av.x, bv.y, ai1);
-                ai1 = mfma16(av.y, bv.x, ai1);
-            }
-        }
-        red[w][0][lane] = ar0 + ar1;
-        red[w][1][lane] = ai0 + ai1;
-        __syncthreads();
-        if (w != 0) return;
-        yr = red[0][0][lane];
-        yi = red[0][1][lane];
+    d4 d1[2], d2[2];
 #pragma unroll
-        for (int u = 1; u < 4; ++u) {
-            yr = yr + red[u][0][lane];
-            yi = yi + red[u][1][lane];
+    for (int i = 0; i < 2; ++i) d1[i] = d2[i] = d4{0.0, 0.0, 0.0, 0.0};
+    // operands: row r, source kk = 4 kc + kq; column r = (target block r / 2, part)
+    const cd* ac = st_c[side] + r - kq + 15;
+    const double* bx = reinterpret_cast<const double*>(st_x[side] + (8 * half + (r >> 1) + 15) * kLttPad + kq) + (r & 1);
+    if (m_lo <= m_hi) fetch(m_lo);
+    for (int mc = m_lo; mc <= m_hi; mc += 16) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kIc; ++u) {
+            const int i = u * 256 + tid;
+            if (i < 2 * kLttCoef) (&st_c[0][0])[i] = tc[u];
         }
-    } else {
-        blocks([&](int side, int lag) {
-                   cd c = mk(0, 0);
-                   if (lag >= 0 && lag < a.nt) c = (side ? cr : cl)[lag];
-                   return c;
-               },
-               [&](int side, int si) { return (side ? xr : xl)[si]; });
+#pragma unroll
+        for (int u = 0; u < kIx; ++u) {
+            const int i = u * 256 + tid;
+            if (i < 2 * kLttSrc * 16) (&st_x[0][0])[(i >> 4) * kLttPad + (i & 15)] = tx[u];
+        }
+        __syncthreads();
+        if (mc + 16 <= m_hi) fetch(mc + 16);
+        const int m1 = min(mc + 15, h_hi);
+        for (int m = max(mc, h_lo); m <= m1; ++m) {
+            const cd* am = ac + 16 * (m - mc);
+            const double* bm = bx - 2 * (m - mc) * kLttPad;
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc) {
+                const cd av = am[-4 * kc];
+                const double bv = bm[8 * kc];
+                d1[kc & 1] = mfma16(av.x, bv, d1[kc & 1]);
+                d2[kc & 1] = mfma16(av.y, bv, d2[kc & 1]);
+            }
+        }
     }
-    const size_t yb = ((size_t)b * a.ns + o) * a.y_ld + (size_t)seg * a.y_seg_stride;
+    // the sides' sums meet in LDS: right + left
+    __syncthreads();
+    double* red = reinterpret_cast<double*>(&st_x[0][0]);      // [half][q][64]
+    double y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double own = d1[0][q] + d1[1][q], im = d2[0][q] + d2[1][q], other = swap_pair(im);
+        y[q] = (r & 1) ? own + other : own - other;
+        if (side) red[(half * 4 + q) * kWave + lane] = y[q];
+    }
+    __syncthreads();
+    if (side) return;
+    const size_t yb = ((size_t)b * a.ns + o) * a.y_ld + (size_t)seg * a.y_seg_stride + blockIdx.x * 256;
     const cd* base = a.s_seg > 0 ? nullptr : a.base;
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq) {
-        const int nrel = 16 * (I0 + r) + kq + 4 * qq;
+    for (int q = 0; q < 4; ++q) {
+        const int nrel = 16 * (8 * half + (r >> 1)) + kq + 4 * q;
         if (nrel < nlen) {
-            cd out = mk(a.sign * yr[qq], a.sign * yi[qq]);
-            if (base) out = out + base[yb + nrel];
-            a.y[yb + nrel] = out;
+            double out = a.sign * (y[q] + red[(half * 4 + q) * kWave + lane]);
+            if (base) out += reinterpret_cast<const double*>(base + yb + nrel)[r & 1];
+            reinterpret_cast<double*>(a.y + yb + nrel)[r & 1] = out;
         }
     }
 }
 
 // ---------------------------------------------------------------------------
-// Batched form of the staged product (at most 256 outputs and 256 sources per
-// segment, one potential for the whole batch): the problems of the batch,
-// which share every coefficient, fill the instruction's N dimension instead
-// of the output blocks.  A workgroup takes one slot, one segment and eight
+// Batched form (at most 256 outputs and 256 sources per segment, one
+// potential for the whole batch): the problems of the batch, which share every
+// coefficient, fill the instruction's N dimension instead of the output blocks.  A workgroup takes one slot, one segment and eight
 // problems; the columns are (problem, real / imaginary part of x), and two
 // accumulators per 16-output block collect Re T [Re x | Im x] and
 // Im T [Re x | Im x], combined at the end (Re y = Re T Re x - Im T Im x, Im y
 // = Re T Im x + Im T Re x) between neighbouring lanes.  Every (output block,
 // source block) pair does useful work, where the one-problem form's columns
-// (output blocks) meet a lag block's sources only partly (about half of its
-// products are zero operands on a 256 x 256 tile).  The workgroup stages the
+// (output blocks) meet a lag block's sources only partly at both ends of the
+// sources' range.  The workgroup stages the
 // sources of its eight problems (2 sides x 256 x 16 doubles) and the
 // coefficient window (2 x 512) in LDS (80 KiB); wave w takes the output blocks
 // 4w .. 4w+3.  The sources sit at the end of their 16-aligned block (zeros
@@ -230,13 +203,6 @@ __global__ __launch_bounds__(256) void ltt_mfma_kernel(LttArgs a) {
 constexpr int kLttBatch = 8;      // problems per workgroup of the batched form
 static_assert(2 * kLttBatch == 16, "the 16 columns of a tile are 8 problems x (re, im)");
 constexpr int kLttScLen = 2 * kLttStage;   // coefficient window per side
-
-__device__ inline double swap_pair(double v) {   // the value of lane l ^ 1
-    int2 t = *reinterpret_cast<int2*>(&v);
-    t.x = __builtin_amdgcn_mov_dpp(t.x, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
-    t.y = __builtin_amdgcn_mov_dpp(t.y, 0xB1, 0xf, 0xf, false);
-    return *reinterpret_cast<double*>(&t);
-}
 
 __global__ __launch_bounds__(256) void ltt_batch_kernel(LttArgs a) {
     extern __shared__ double lds[];
@@ -336,20 +302,36 @@ __global__ __launch_bounds__(256) void ltt_batch_kernel(LttArgs a) {
     }
 }
 
+// the batched form: one potential, at least kLttBatch problems, short ranges
+static bool ltt_batched(const LttArgs& a) {
+    const int slen = a.s_seg > 0 ? std::min(a.s_seg, a.s_hi - a.s_lo) : a.s_hi - a.s_lo;
+    return a.B >= kLttBatch && !a.per_problem && a.n_hi - a.n_lo <= kLttStage && slen <= kLttStage;
+}
+
+// Super-blocks of sources per partial of a causal solve's history product.
+// The one-problem form walks as many as it is given with no loss between them,
+// so it takes them all where the slots and problems alone fill the GPU, and
+// fewer, for kLttFill workgroups, where they do not; the batched form stages
+// one at a time.
+constexpr int kLttFill = 512;
+int ltt_seg_blocks(int ns, int B, bool per_problem, int nblk) {
+    if (B >= kLttBatch && !per_problem) return 1;
+    const int parts = std::min(nblk, std::max(1, (kLttFill + ns * B - 1) / (ns * B)));
+    return (nblk + parts - 1) / parts;
+}
+
 hipError_t launch_ltt(const LttArgs& a, hipStream_t st) {
     if (a.ns == 0 || a.n_hi <= a.n_lo) return hipSuccess;
     if (a.s_lo < 0 || a.s_hi > a.nt || a.n_lo < 0 || a.n_hi > a.nt) return hipErrorInvalidValue;
-    const int tiles = (a.n_hi - a.n_lo + 255) / 256;
     const int nseg = a.s_seg > 0 ? (a.s_hi - a.s_lo + a.s_seg - 1) / a.s_seg : 1;
     if ((size_t)a.B * nseg > 65535) return hipErrorInvalidValue;
-    const int slen_max = a.s_seg > 0 ? std::min(a.s_seg, a.s_hi - a.s_lo) : a.s_hi - a.s_lo;
-    if (a.B >= kLttBatch && !a.per_problem && a.n_hi - a.n_lo <= kLttStage && slen_max <= kLttStage) {
+    if (ltt_batched(a)) {
         const size_t lds = sizeof(double) * 2 * kLttStage * 16 + sizeof(cd) * 2 * kLttScLen;
         dim3 grid(a.ns, (a.B + kLttBatch - 1) / kLttBatch, nseg);
         ltt_batch_kernel<<<grid, 256, lds, st>>>(a);
         return hipGetLastError();
     }
-    dim3 grid((tiles + 3) / 4, a.ns, a.B * nseg);
+    dim3 grid((a.n_hi - a.n_lo + 255) / 256, a.ns, a.B * nseg);
     ltt_mfma_kernel<<<grid, 256, 0, st>>>(a);
     return hipGetLastError();
 }
