@@ -167,9 +167,10 @@ typedef struct {
  * bound; the GMRES restart changes the iterate, not the tolerance met). */
 typedef struct {
     int pipeline;     /* pipeline chunk of the static causal solve, 0 = staged */
-    int help_max;     /* S0^2 sweeps of V(t,x) and |u|^2: launches of at most this many tasks give
-                         every task a second wave that sums the far boundary history (static
-                         potentials form it on the matrix cores inside the sweep) */
+    int help_max;     /* S0^2 sweeps of V(t,x) that refactor in every step (more than 240 tasks):
+                         launches of at most this many tasks give every task a second wave that
+                         sums the far boundary history (the other sweeps form it on the matrix
+                         cores themselves) */
     int restart;      /* GMRES restart length */
     int pair_from;    /* 1 or more; kept and reported, no launch depends on it (the static sweep
                          chooses how many tasks share a wave from the problem's sizes) */

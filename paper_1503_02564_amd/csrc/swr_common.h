@@ -247,6 +247,21 @@ constexpr int kLongMaxQ = 8192;
 // 176 ms with 512-step chunks)
 constexpr int kHelpMaxTasks = 512;
 constexpr int kPipeChunk = 256;
+// V(t,x) with Robin or S0^2: up to this many (problem, subdomain) tasks the
+// sweeps read each step's factor record from memory (swr_sweep_rows_time.hip),
+// above they refactor in every step.  A workgroup of the former fills a compute
+// unit, so from 256 tasks on it runs in two rounds, and the latter's chain is the
+// same up to 1024.  One sweep of 256 steps with all records built for it, against
+// refactoring: 128 x 256 cells 0.57 / 1.09 ms, 256 x 256 0.99 / 1.10, 320 x 256
+// 1.37 / 1.13, 256 x 500 1.42 / 1.40 (a solve builds them once for 10 to 40 sweeps).
+constexpr int kTimeRecordTasks = 240;
+// ... and the memory of the records; longer windows are factored piece by piece
+constexpr size_t kTimeRecordBytes = (size_t)4 << 30;
+// sweeps of V(t,x) and |u|^2 in the row form sum their S0^2 history in one
+// piece up to this many steps: 64 cycles of matrix instructions per 4 past
+// steps and block of 64 outputs, which passes the cost of the split (a product
+// and a launch per 256 steps, about 30 us) near 1000 past steps
+constexpr int kUnsplitSteps = 2048;
 // schedule parameters of launch forms that no longer exist; still validated,
 // saved and reported (bounds and defaults)
 constexpr int kPairFrom = kMaxP + 1;
@@ -361,6 +376,8 @@ struct SweepArgs {
     const int4* items;
     const cd* rfac;              // row-form and wide-form records and their strides
     size_t rstride;
+    const cd* tfac;              // V(t,x): row-form records [step - tfac_begin][N][rstride]
+    int tfac_begin;
     const cd* wfac;
     size_t wstride;
 };
@@ -388,6 +405,7 @@ struct FactorArgs {
     const int* J;
     const int* off;
     const double* V;             // [nv][nx] static potential (nullptr = 0)
+    bool steps;                  // row form: V is rows of V(t,x), record v from their mean over step v
     cd* fac;
     const cd* pade;              // Pade strategy: [2][m+1] coefficients a, d
     int pade_m;
@@ -432,10 +450,11 @@ hipError_t launch_sweep_static_pade(const SweepArgs& a, hipStream_t st);
 hipError_t launch_sweep_long(const SweepArgs& a, int trans, int vk, hipStream_t st);
 hipError_t launch_factor_long(const FactorArgs& a, int Q, hipStream_t st);
 hipError_t launch_sweep_time(const SweepArgs& a, int trans, hipStream_t st);
-hipError_t launch_sweep_cubic(const SweepArgs& a, int trans, hipStream_t st);
+hipError_t launch_sweep_cubic_hi(const SweepArgs& a, int trans, hipStream_t st);
 // static potential, Robin or S0^2 (swr_sweep_rows*.hip): the workgroups a.items[0 .. nitems - 1] of
 // one kind, records a.fac with stride a.fstride; pmax: their widest
-hipError_t launch_sweep_rows(const SweepArgs& a, int kind, int trans, int nitems, int pmax, hipStream_t st);
+hipError_t launch_sweep_rows(const SweepArgs& a, int kind, int trans, int vk, int nitems, int pmax,
+                             hipStream_t st);
 // row-form records of the subdomains with RW rows (a.Pk: P + 32 RW per subdomain)
 hipError_t launch_rows_factor(const FactorArgs& a, int RW, int pmax, hipStream_t st);
 // static potential, Robin or S0^2, subdomains of more than 64 * kMaxP nodes

@@ -196,6 +196,10 @@ struct swr_ctx {
     int gm_check = 4;            // GMRES: read the residual estimates back every this many steps
     double* dResHist = nullptr;  // GMRES: [restart][B] residual estimate after every inner step
     std::vector<double> hResHist;
+    // V(t,x) in the row form: records of tsteps steps (whole window: built once
+    // per call, else piece by piece)
+    cd* dTfac = nullptr;
+    int tsteps = 0;
     int v_version = 0;           // bumped whenever the potential changes
     // the captured solve and the arguments it was captured with
     hipGraph_t g_graph = nullptr;
@@ -380,12 +384,13 @@ static bool conv_hist(int tr) { return tr != SWR_ROBIN && tr <= SWR_S14; }
 // (old part precomputed on the matrix cores; far_sum_s02, launch_widths).
 // Static potentials always do (every static form then sums alike); V(t,x)
 // and |u|^2 contexts only when their sweeps fill the GPU with one-wave tasks
-// -- with few tasks the S0^2 helper wave already sums the far history beside
-// the sweep, and the extra launches of the split cost more than they save
-// (|u|^2 on 128 x 256 cells, 4000 steps: 815 ms split, 750 ms not).
+// -- with few tasks the extra launches of the split cost more than they save
+// (V(t,x) sweeps that refactor sum the far history on a helper wave) -- or when
+// their window is long (kUnsplitSteps).
 // Contexts with long-chunk subdomains sum it in one piece.
 static bool far_split(const swr_ctx* c) {
-    return c->tr == SWR_S02 && !c->Qlong && (c->vk == SWR_V_STATIC || c->nSub > kHelpMaxTasks);
+    return c->tr == SWR_S02 && !c->Qlong &&
+           (c->vk == SWR_V_STATIC || c->nSub > kHelpMaxTasks || c->nt > kUnsplitSteps);
 }
 
 // Pade strategy (Sec. 2.2): sqrt(z) ~ sum_{s=0}^m a_s - sum_{s=1}^m a_s d_s/(z + d_s)
@@ -575,13 +580,11 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     by_width(sub, c->runs_sub);
     by_width(imp0, c->runs_L0);
     if (tr == SWR_ROBIN || tr == SWR_S02) {
-        rows_plan(c, vk == SWR_V_STATIC ? build.size() + sub.size() : imp0.size(), vk == SWR_V_STATIC && nv == 1 ? B : 0);
-        if (vk == SWR_V_STATIC) {
-            rows_items(c, build, c->rows_build);
-            rows_items(c, sub, c->rows_sub);
-        } else {
-            rows_items(c, imp0, c->rows_L0);
-        }
+        // (V(t,x), |u|^2: one task per wave, the form that their sweeps have)
+        rows_plan(c, vk == SWR_V_STATIC ? build.size() + sub.size() : 0, vk == SWR_V_STATIC && nv == 1 ? B : 0);
+        if (vk == SWR_V_STATIC) rows_items(c, build, c->rows_build);
+        else rows_items(c, imp0, c->rows_L0);
+        rows_items(c, sub, c->rows_sub);
     }
     c->nBuild = (int)build.size();
     // default schedule; a tuning cache entry for this problem replaces it
@@ -652,12 +655,23 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     if (vk != SWR_V_STATIC) {
         c->L0.nv = 1;
         c->L0.ntasks = (int)imp0.size();
-        ALLOC(c->L0.fac, (size_t)N * fields * kWave);
+        if (tr > SWR_S02) ALLOC(c->L0.fac, (size_t)N * fields * kWave);
         if (c->rstride) ALLOC(c->L0.rfac, (size_t)N * c->rstride);
         if (c->wstride) ALLOC(c->L0.wfac, (size_t)N * c->wstride);
         ALLOC(c->L0.cols, (size_t)N * 4 * nt);
         if (c->Qlong) ALLOC(c->L0.lfac, (size_t)N * c->lfstride);
         ALLOC(c->L0.tasks, imp0.size());
+    }
+    if (vk == SWR_V_TIME && c->rstride && !c->Qlong && c->nSub <= kTimeRecordTasks) {
+        const size_t rec = (size_t)N * c->rstride * sizeof(cd);
+        const size_t fit = kTimeRecordBytes / rec / kWave * kWave;
+        c->tsteps = (int)std::min((size_t)nt, std::max(fit, (size_t)kWave));
+        // (without room for them the sweeps refactor)
+        if (dalloc(c, &c->dTfac, (size_t)c->tsteps * N * c->rstride) != SWR_OK) {
+            c->dTfac = nullptr;
+            c->tsteps = 0;
+        }
+        if (c->dTfac && c->tsteps < nt && !far_split(c)) ALLOC(c->dStateF, sub.size() * 2 * c->P * kWave);
     }
     // S0^2 sweeps carry their state across super-chunk launches and read the
     // old far-history parts of their super-chunk (see launch_widths)
@@ -845,27 +859,47 @@ static swr_status run_factor64(swr_ctx* c, const double* V, int nv, Iface& I) {
     return SWR_OK;
 }
 
+static FactorArgs rows_factor_args(const swr_ctx* c) {
+    FactorArgs f{};
+    f.N = c->N; f.nx = c->nx; f.h = c->h; f.dt = c->dt;
+    f.sigma = c->sigma; f.J = c->dJ; f.off = c->dOff;
+    f.Pk = c->dRows;
+    f.fstride = c->rstride;
+    return f;
+}
+
+// V(t,x): the records of steps n_lo+1 .. n_hi
+static hipError_t factor_steps(const swr_ctx* c, int n_lo, int n_hi, hipStream_t st) {
+    FactorArgs f = rows_factor_args(c);
+    f.nf = (n_hi - n_lo) * c->N;
+    f.V = c->dV + (size_t)n_lo * c->nx;
+    f.steps = true;
+    f.fac = c->dTfac;
+    int pmax = 0;
+    for (int key : c->rows) pmax = std::max(pmax, key % 32);
+    return launch_rows_factor(f, 4, pmax, st);
+}
+
 // the records that the sweeps of the operator's contexts read
 static swr_status run_factor(swr_ctx* c, const double* V, int nv, Iface& I, bool impulses) {
-    // (V(t,x) and |u|^2: the row and wide forms serve the impulse sweeps of L_0 only)
-    if ((I.rfac || I.wfac) && (c->vk == SWR_V_STATIC || impulses)) {
-        FactorArgs f{};
-        f.N = c->N; f.nx = c->nx; f.nf = nv * c->N; f.h = c->h; f.dt = c->dt;
-        f.sigma = c->sigma; f.J = c->dJ; f.off = c->dOff; f.V = V;
+    // (V(t,x) and |u|^2: the wide form serves the impulse sweeps of L_0 only)
+    if (I.rfac || I.wfac) {
+        FactorArgs f = rows_factor_args(c);
+        f.nf = nv * c->N;
+        f.V = V;
         int pmax[5] = {}, waves[9] = {};
         for (int key : c->rows) pmax[key / 32] = std::max(pmax[key / 32], key % 32);
         for (int key : c->wide) waves[key / 32] = 1;
         f.fac = I.rfac;
-        f.Pk = c->dRows;
-        f.fstride = c->rstride;
         for (int RW : {1, 2, 4})
             if (pmax[RW]) HIPCHK(launch_rows_factor(f, RW, pmax[RW], c->st));
         f.fac = I.wfac;
         f.Pk = c->dWide;
         f.fstride = c->wstride;
         for (int NW : {2, 4, 8})
-            if (waves[NW]) HIPCHK(launch_wide_factor(f, NW, c->st));
-        if (c->vk == SWR_V_STATIC && !c->stream_static) return SWR_OK;
+            if (waves[NW] && (c->vk == SWR_V_STATIC || impulses)) HIPCHK(launch_wide_factor(f, NW, c->st));
+        if (c->dTfac && c->tsteps == c->nt) HIPCHK(factor_steps(c, 0, c->nt, c->st));
+        if (!c->Qlong || (c->vk == SWR_V_STATIC && !c->stream_static)) return SWR_OK;
     }
     return run_factor64(c, V, nv, I);
 }
@@ -925,13 +959,13 @@ static const RowsList& rows_of(const swr_ctx* c, const Task* tasks) {
 }
 
 // all tasks of a's list (a.task0 = 0, a.ntasks = the whole list), in order on
-// one stream; *launches counts them per chunk width (plain: per task).  Static
-// potential with Robin or S0^2: the row form, one launch for all widths of a
-// kind (plain: one per task).  Else one launch per chunk width.
+// one stream; *launches counts them per chunk width (plain: per task).  Robin or
+// S0^2: the row form, one launch for all widths of a kind (plain: one per task),
+// except V(t,x) that refactors.  Else one launch per chunk width.
 static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hipStream_t st, bool plain,
                                       int* launches) {
     const int tr = ktr(c);
-    const bool rows = vk == SWR_V_STATIC && (tr == TR_S02 || tr == TR_ROBIN);
+    const bool rows = (tr == TR_S02 || tr == TR_ROBIN) && (vk != SWR_V_TIME || c->dTfac);
     if (rows) {
         const RowsList& l = rows_of(c, a.tasks);
         SweepArgs r = a;
@@ -941,7 +975,7 @@ static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hip
             r.items = l.dev + run.start;
             const int per = plain ? 1 : run.count;
             for (int i = 0; i < run.count; i += per, r.items += per) {
-                const hipError_t e = launch_sweep_rows(r, run.kind, tr, per, run.pmax, st);
+                const hipError_t e = launch_sweep_rows(r, run.kind, tr, vk, per, run.pmax, st);
                 if (e != hipSuccess) return e;
             }
         }
@@ -953,7 +987,7 @@ static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hip
         hipError_t e;
         if (r.P > kMaxP) {
             // subdomains beyond 64 * kMaxP nodes: one launch
-            const int NW = rows ? wide_waves(r.P) : 0;
+            const int NW = rows && vk == SWR_V_STATIC ? wide_waves(r.P) : 0;
             if (NW) {
                 SweepArgs w = a;
                 w.fac = a.wfac;
@@ -978,20 +1012,23 @@ static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hip
 // far-history parts (far_old_kernel); the sweeps carry their state across
 // the pieces in the list's state buffer.  Every S0^2 sweep of a context goes
 // through here, so all its forms sum the far history alike.
+// V(t,x) whose records do not all fit: pieces of the steps that do, each
+// factored first.
 static hipError_t launch_widths(const swr_ctx* c, SweepArgs a, int vk, hipStream_t st, bool plain,
                                 int* launches = nullptr) {
     cd* fo = far_split(c) ? far_old_of(c, a.tasks) : nullptr;
-    if (!fo) {
-        a.far_old = nullptr;
-        return launch_widths_range(c, a, vk, st, plain, launches);
-    }
+    const bool rec = vk == SWR_V_TIME && c->dTfac;
+    const int per = rec && c->tsteps < c->nt ? c->tsteps : c->nt;
+    a.far_old = fo;
+    a.tfac = rec ? c->dTfac : nullptr;
+    if (!fo && per == c->nt) return launch_widths_range(c, a, vk, st, plain, launches);
     if (!a.state) a.state = state_of(c, a.tasks);
     if (!a.state) return hipErrorInvalidValue;
-    a.far_old = fo;
     const int n1 = a.n_end;
     for (int s0 = a.n_begin; s0 < n1;) {
-        const int s1 = std::min(n1, (s0 / kFarSuper + 1) * kFarSuper);
-        if (s0 > 0 && s0 % kFarSuper == 0) {
+        int s1 = std::min(n1, (s0 / per + 1) * per);
+        if (fo) s1 = std::min(s1, (s0 / kFarSuper + 1) * kFarSuper);
+        if (fo && s0 > 0 && s0 % kFarSuper == 0) {
             FarOldArgs f{};
             f.hist = a.hist;
             f.beta = a.beta;
@@ -1001,6 +1038,11 @@ static hipError_t launch_widths(const swr_ctx* c, SweepArgs a, int vk, hipStream
             f.C = s0;
             const hipError_t e = launch_far_old(f, st);
             if (e != hipSuccess) return e;
+        }
+        if (per < c->nt) {
+            const hipError_t e = factor_steps(c, s0, s1, st);
+            if (e != hipSuccess) return e;
+            a.tfac_begin = s0;
         }
         a.n_begin = s0;
         a.n_end = s1;

@@ -37,7 +37,11 @@ __device__ inline void rows_factor_body(const FactorArgs& a, int f) {
     bool dup;
     rows_place<P, RW>(n, t, s, dup);
     const double* V = a.V ? a.V + (size_t)v * a.nx + o : nullptr;
-    auto W = [&](int i) { return (V && i >= 0 && i < n) ? V[i] : 0.0; };
+    // (V(t,x): the mean of the step's two rows, eq. CNS_L)
+    auto W = [&](int i) {
+        if (!V || i < 0 || i >= n) return 0.0;
+        return a.steps ? 0.5 * (V[a.nx + i] + V[i]) : V[i];
+    };
     const cd zero = mk(0, 0), one = mk(1, 0);
     // node i: minus its couplings to i - 1 and i + 1, and the sum of its row
     auto row = [&](int i, cd& cl, cd& cr, cd& ex) {

@@ -173,7 +173,7 @@ hipError_t launch_factor(const FactorArgs& a, hipStream_t st) {
 
 static hipError_t launch_sweep_once(const SweepArgs& a, int trans, int vk, hipStream_t st) {
     if (vk == VK_TIME) return launch_sweep_time(a, trans, st);
-    if (vk == VK_CUBIC) return launch_sweep_cubic(a, trans, st);
+    if (vk == VK_CUBIC) return launch_sweep_cubic_hi(a, trans, st);
     return launch_sweep_static(a, trans, st);
 }
 

@@ -152,8 +152,8 @@ __device__ inline void gen_end_coef(int tr, double W, double dW, double dt, cd c
 template <int P, int TR, int VK, bool HELP = false>
 __global__ __launch_bounds__(sweep_threads(HELP)) void sweep_kernel(SweepArgs a) {
     static_assert(!HELP || TR == TR_S02, "the helper wave serves S0^2");
-    static_assert(VK != VK_STATIC || (TR == TR_GEN || TR == TR_PADE),
-                  "static potential with Robin or S0^2: the row form");
+    static_assert(VK == VK_TIME || (TR == TR_GEN || TR == TR_PADE),
+                  "static potential and |u|^2 with Robin or S0^2: the row form");
     __shared__ double sbeta[2 * kWave];       // beta_0 .. beta_127
     __shared__ cd ffa[2][kWave], ffb[2][kWave];   // S0^2: far sums from the helper wave
     __shared__ cd sha[kWave], shb[kWave];     // staged chunk of the boundary history

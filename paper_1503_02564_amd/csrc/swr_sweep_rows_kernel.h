@@ -30,6 +30,8 @@
 // potentials on 256 x 64 cells 148 -> 111 ms, one problem on 64 x 256 cells 3.59
 // -> 3.1 ms, one Robin iteration on 4 x 100 cells over 500 steps 0.367 -> 0.275 ms.
 #pragma once
+#include <type_traits>
+
 #include "swr_rows.h"
 
 namespace swr {
@@ -96,8 +98,9 @@ __device__ inline void rows_far(const cd* hist, const double* beta, int nt, bool
 
 // The tasks first .. first + count - 1 (at most SLOTS per wave of the
 // workgroup), all of P nodes per lane; with LDSF all of one factor record.
-template <int P, int RW, bool LDSF, int NW, int TR>
+template <int P, int RW, bool LDSF, int NW, int TR, int VK = VK_STATIC>
 __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* smem) {
+    static_assert(VK == VK_STATIC || (RW == 4 && !LDSF && NW == 1), "V(t,x), |u|^2: one task per wave");
     constexpr int T = 16 * RW, SLOTS = 4 / RW;
     constexpr bool WRAP = P == 1;
     const int lane = threadIdx.x & (kWave - 1);
@@ -137,12 +140,12 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
 
     RowsFac<P, RW, LDSF> F;
     F.lds = sfac + t;
-    F.load(a.fac + (size_t)task.f * a.fstride + t);
+    if (VK != VK_TIME) F.load(a.fac + (size_t)task.f * a.fstride + t);
 
     const int nbeg = a.n_begin, nend = a.n_end;
     const bool begins = nbeg == 0, last = nend == nt;
     cd* stp = a.state ? a.state + (size_t)tix * 2 * a.pstride * kWave + t : nullptr;
-    cd u[P];
+    cd u[P], vlast[P];                                // vlast: v_n, where |u|^2's inner iteration starts
     if (begins) {
         const cd* u0 = a.u0 + (size_t)b * a.nx + o;
 #pragma unroll
@@ -153,6 +156,14 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
     } else {
 #pragma unroll
         for (int q = 0; q < P; ++q) u[q] = stp[q * T];
+    }
+    int nl_worst = 0, nl_fail = 0;
+    if (VK == VK_CUBIC) {
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            vlast[q] = u[q];
+            if (!begins) vlast[q] = stp[(a.pstride + q) * kWave];
+        }
     }
     // node weights of the mass stencil: 4, and 2 at the two end nodes
     const double w0 = t0 ? 2.0 : 4.0;
@@ -261,6 +272,10 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
         for (int i = 0; i < nb;) {
           const int ie = special ? min(nb, i + until(n0 + i)) : nb;
           for (; i < ie; ++i) {
+            if constexpr (VK == VK_TIME) {
+                __syncthreads();                      // this step's record is in LDS (time_helper)
+                F.load(sfac + ((n0 + i - nbeg) & 1) * (rows_fields(P, RW) * T) + t);
+            }
             const cd uL = rows_up1<RW>(u[P - 1], t);
             const cd uR = rows_dn1<RW>(rows_front<P>(u, dup), t);
             auto stencil = [&](int q) { return rows_stencil<P>(u, uL, uR, w0, wL, q); };
@@ -275,7 +290,50 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
                 lgl[3 * kWave + i] = accB;
             }
             cd y[P];
-            rows_solve(F, dF, dS, stencil, t, dup, y);
+            if constexpr (VK == VK_CUBIC) {
+                // inner fixed point of eq. AvMNL from zeta^0 = v_{n-1}:
+                // (cM - S - sigma E) zeta^{s+1} = rhs - M_{|zeta^s|^2} zeta^s, over
+                // i kappa; the generalised mass (nodal weight |zeta|^2, the element
+                // matrix of M_W) is h / 12 times ((f_{i-1} + f_i) zeta_{i-1} +
+                // (f_{i-1} + 6 f_i + f_{i+1}) zeta_i + (f_i + f_{i+1}) zeta_{i+1}),
+                // 3 f_i at an end node
+                cd d[P];
+#pragma unroll
+                for (int q = 0; q < P; ++q) d[q] = stencil(q);
+                d[0] = dF;
+                d[P - 1] = dS;
+                const double gk = a.h / 12.0 * ik;
+                int it = 1;
+                bool conv = false;
+                for (; it <= a.nl_maxit; ++it) {
+                    const cd zL = rows_up1<RW>(vlast[P - 1], t);
+                    const cd zR = rows_dn1<RW>(rows_front<P>(vlast, dup), t);
+                    auto rhs = [&](int q) {
+                        const cd zm = sel_c(q == 0, zL, vlast[q == 0 ? 0 : q - 1]);
+                        const cd zp = sel_c(q == P - 1, zR, vlast[q == P - 1 ? 0 : q + 1]);
+                        const double w = q == P - 1 ? wL : (q == 0 ? w0 : 4.0);
+                        const double fm = abs2(zm), fi = abs2(vlast[q]), fp = abs2(zp);
+                        const double c0 = fma(1.5 * w, fi, fm + fp), cm = fm + fi, cp = fi + fp;
+                        const double sx = fma(cm, zm.x, fma(c0, vlast[q].x, cp * zp.x));
+                        const double sy = fma(cm, zm.y, fma(c0, vlast[q].y, cp * zp.y));
+                        return mk(fma(-gk, sy, d[q].x), fma(gk, sx, d[q].y));
+                    };
+                    rows_solve(F, rhs(0), P > 1 ? rhs(P - 1) : rhs(0), rhs, t, dup, y);
+                    double dm = 0.0, zm2 = 0.0;
+#pragma unroll
+                    for (int q = 0; q < P; ++q) {
+                        dm = fmax(dm, abs2(y[q] - vlast[q]));
+                        zm2 = fmax(zm2, abs2(vlast[q]));
+                        vlast[q] = y[q];
+                    }
+                    const double dmax = sqrt(wave_max(dm)), zmax = sqrt(wave_max(zm2));
+                    if (dmax <= a.nl_tol * fmax(1.0, zmax)) { conv = true; break; }
+                }
+                if (!conv) nl_fail = 1;
+                nl_worst = max(nl_worst, conv ? it : a.nl_maxit);
+            } else {
+                rows_solve(F, dF, dS, stencil, t, dup, y);
+            }
             const cd X = y[P - 1];
 #pragma unroll
             for (int q = 0; q < P; ++q) u[q] = mk(2.0 * y[q].x - u[q].x, 2.0 * y[q].y - u[q].y);
@@ -333,7 +391,10 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
 
     if (!last && stp && live) {
 #pragma unroll
-        for (int q = 0; q < P; ++q) stp[q * T] = u[q];
+        for (int q = 0; q < P; ++q) {
+            stp[q * T] = u[q];
+            if (VK == VK_CUBIC) stp[(a.pstride + q) * kWave] = vlast[q];
+        }
     }
     if ((fl & T_OUT_UT) && last) {
         cd* uT = a.uT + (size_t)b * a.nx + o;
@@ -348,6 +409,10 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
         maxd = wave_max(maxd);
         if (lane == 0 && maxd > 0.0)
             atomicMax(a.maxdiff, (unsigned long long)__double_as_longlong(maxd));
+    }
+    if (VK == VK_CUBIC && lane == 0 && a.nl_stats) {
+        atomicMax(&a.nl_stats[0], nl_worst);
+        if (nl_fail) atomicMax(&a.nl_stats[1], 1);
     }
 }
 

@@ -154,3 +154,58 @@ def test_adjoint_of_every_form(dev, label, J, B, per_problem, trans):
         say("adjoint rows", label, b, "dV", ev, "du0", eu)
         assert ev < 1e-10 and eu < 1e-10
     pb.close()
+
+
+WIDTHS = [1, 2, 40, 62, 63, 64, 100, 127, 128, 190, 255, 256, 320, 383, 384, 447, 448, 511]
+
+
+@pytest.mark.parametrize("vk,trans,J,nt", [
+    (W.V_TIME, W.S02, WIDTHS, 135), (W.V_TIME, W.ROBIN, WIDTHS, 64), (W.V_TIME, W.S02, [5, 70, 7], 2100),
+    (W.V_CUBIC, W.S02, WIDTHS, 135), (W.V_CUBIC, W.ROBIN, WIDTHS, 65), (W.V_CUBIC, W.S02, [5, 70, 7], 2100),
+    (W.V_TIME, W.S02, [9, 8], 1), (W.V_CUBIC, W.S02, [9, 8], 1),
+])
+def test_sweeps_of_moving_potentials(dev, vk, trans, J, nt):
+    """V(t,x) with its records read step by step and |u|^2 with its inner
+    iteration, in every width and past the window where the history is split:
+    one sweep against the oracle's, 1e-11 (|u|^2: 1e-10, the inner iteration
+    stops at 1e-12 of the largest value in either)."""
+    import torch
+    import oracle as O
+    from paper_1503_02564_amd import swr
+    wl = W.small_case(J=J, nt=nt, vkind=vk, trans=trans, sigma=2 - 3j, B=1, seed=5, a0=-10.0, b0=10.0)
+    rng = np.random.default_rng(2)
+    ns = 2 * len(J) - 2
+    g = 0.3 * (rng.standard_normal((1, ns, nt)) + 1j * rng.standard_normal((1, ns, nt)))
+    say("moving", vk, trans, len(J), nt)
+    pb = make_problem(wl)
+    out = torch.zeros((1, ns, nt), dtype=torch.complex128, device=dev)
+    uT = torch.zeros((1, wl.nx), dtype=torch.complex128, device=dev)
+    swr.swr_apply_R(pb.ctx, to_dev(wl.u0), to_dev(g), out, uT)
+    uref, ref = O.local_solution(wl, wl.u0[0], g[0])
+    bar = 1e-10 if vk == W.V_CUBIC else 1e-11
+    assert rel(to_np(out)[0], ref) < bar and rel(to_np(uT)[0], uref) < bar
+    pb.close()
+
+
+def test_records_in_pieces_equal_refactoring(dev):
+    """V(t,x) whose records do not all fit at once (240 subdomains of 500 cells:
+    384 steps) against two problems with the same data, above the task count of
+    the records: both sweeps carry one rounding chain of 390 steps, 1e-11."""
+    import torch
+    from paper_1503_02564_amd import swr
+    N, nt = 240, 390
+    wl = W.small_case(J=[500] * N, nt=nt, vkind=W.V_TIME, B=1, seed=5, a0=-100.0, b0=100.0)
+    rng = np.random.default_rng(2)
+    g = 0.3 * (rng.standard_normal((1, 2 * N - 2, nt)) + 1j * rng.standard_normal((1, 2 * N - 2, nt)))
+    res = []
+    for B in (1, 2):
+        w2 = W.Workload("p", wl.a0, wl.b0, wl.J, wl.dt, nt, wl.vkind, wl.V, wl.trans, wl.sigma,
+                        np.repeat(wl.u0, B, axis=0))
+        pb = make_problem(w2)
+        gd = to_dev(np.repeat(g, B, axis=0))
+        out = torch.zeros_like(gd)
+        uT = torch.zeros((B, wl.nx), dtype=torch.complex128, device=dev)
+        swr.swr_apply_R(pb.ctx, to_dev(w2.u0), gd, out, uT)
+        res.append((to_np(out)[0], to_np(uT)[0]))
+        pb.close()
+    assert rel(res[0][0], res[1][0]) < 1e-11 and rel(res[0][1], res[1][1]) < 1e-11
