@@ -22,7 +22,7 @@
 // super-block to the outputs being solved is formed by one block-Toeplitz
 // product on the matrix cores (launch_ltt).  `causal_far_kernel` adds to d that product and
 // the contribution of the earlier blocks of the current super-block (a short
-// rectangle, one workgroup per subdomain and pair of problems; for a batch of
+// rectangle, one workgroup per subdomain and problem; for a batch of
 // eight or more problems with one potential `causal_far_mfma_kernel`, one
 // wave per subdomain and eight problems on the matrix cores);
 // `causal_near_kernel` then
@@ -160,99 +160,152 @@ __device__ inline size_t far_out(int b, int ns, int o, int i) {
     return TB == kTb ? ((size_t)b * ns + o) * TB + i : ((size_t)b * TB + i) * ns + o;
 }
 
-// One workgroup per (subdomain k, PB problems).  Subdomain k feeds the
-// output slots 2k - 2 (if k >= 1) and 2k + 1 (if k <= N - 2); both read the
-// same two source rows, g of slots 2k - 1 and 2k, and with one potential the
-// problems read the same coefficients, so each row is staged in LDS once for
-// all its readers.  Thread (h, bb, split, i): output step n0 + i of slot
-// 2k - 2 (h = 0) or 2k + 1 (h = 1) for problem b0 + bb, inputs s in the
-// split's share of [s_from, n0).  out = d + the finished super-blocks'
-// partials + that contribution.  The source rows over [s_from, n0) and the
-// coefficient window they meet (lags 1 .. n0 + TB - s_from) are staged with
-// coalesced loads (the range is less than one 256-step super-block).  Per
-// output, the source split, the order of terms in each partial sum and the
-// order in which the partials are added depend on TB and the range only.
-// PB problems per workgroup: 2, or 1 for a single problem (no idle half)
-template <int TB, int PB>
-__global__ __launch_bounds__(2 * PB * 256) void causal_far_kernel(FarArgs f) {
-    constexpr int SPLITS = 256 / TB;
-    constexpr int kWin = kCausalSuper + TB;
-    constexpr int NT = 2 * PB * 256;
-    __shared__ cd part[2][PB][SPLITS][TB];
-    __shared__ cd sg[2][PB][kCausalSuper];
-    __shared__ cd sc[PB][4][kWin];       // [problem or 0][coefficient row p][lag]
-    const int k = blockIdx.x, b0 = blockIdx.y * PB, t = threadIdx.x;
-    const int i = t % TB, sp = (t / TB) % SPLITS, bb = (t / 256) % PB, h = t / (256 * PB);
+// One workgroup of NW waves per (subdomain k, problem).  Subdomain k feeds the
+// output slots 2k - 2 (if k >= 1) and 2k + 1 (if k <= N - 2) from the same two
+// source rows, g of slots 2k - 1 and 2k.  The source rows over [s_from, n0) and
+// the coefficient rows over the lags they meet are staged in LDS.  A lane takes R
+// consecutive output steps of one slot and a share of the sources, four at a
+// time: each coefficient read serves R products (the next source meets the same
+// coefficients one step on).  The shares are summed over lanes, then waves.  out = d + the finished
+// super-blocks' partials + that contribution.  Which sources a share has, the
+// order of terms in it and the order in which the shares are added depend on TB,
+// NW and the range only.
+//
+// Bound: the round of memory latency of the staging and the launch.  Before (one
+// output per lane, 1024 threads for two problems, two workgroups per compute
+// unit and so four rounds of staging) and now, per launch: 16 potentials on 256
+// subdomains, blocks of 8, beside the sweeps 41 -> 27.5 us; one problem on 64
+// subdomains, blocks of 32: 7.5 -> 6.5 us.  One wave each from kFarWaves pairs on,
+// where one wave per SIMD is there; with fewer, four waves shorten the chain (128
+// subdomains, blocks of 8: 4.1 us).
+// sum over the lanes of a wave that are equal modulo G, on the first G lanes
+template <int G>
+__device__ inline double far_lanes(double v) {
+    if (G <= 2) v += dpp_shift<0x122>(v);              // row_ror:2
+    if (G <= 4) v += dpp_shift<0x124>(v);
+    if (G <= 8) v += dpp_shift<0x128>(v);
+    const RowPair r = swap16(v);
+    v = r.first + r.second;
+    const RowPair h = swap32(v);
+    return h.first + h.second;
+}
+
+template <int TB, int NW>
+__global__ __launch_bounds__(NW * kWave) void causal_far_kernel(FarArgs f) {
+    constexpr int NT = NW * kWave, R = TB < 4 ? TB : 4, GROUPS = 2 * TB / R, SPLITS = NT / GROUPS;
+    constexpr int kWin = kCausalSuper + TB, kPad = 4;   // coefficient rows: kPad zeros first
+    constexpr int OUT = 2 * TB;
+    __shared__ cd sx[2][kCausalSuper + kPad];           // zeros from len on
+    __shared__ cd sc[4][kPad + kWin];
+    static_assert(NW * OUT <= 4 * (kPad + kWin) && GROUPS <= 16 && GROUPS > 1, "shares: lanes, then waves");
+    const int k = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
     const bool hasl = k >= 1, hasr = k <= f.N - 2;      // source rows 2k - 1, 2k
-    const bool act = h == 0 ? hasl : hasr;              // output slot exists
-    const int o = h == 0 ? 2 * k - 2 : 2 * k + 1;
-    const int b = b0 + bb;
     const int len = f.n0 - f.s_from;                    // < kCausalSuper
-    const int n = f.n0 + i;
-    const bool out_ok = act && b < f.B && i < f.nb;
-    // d plus the finished super-blocks' partials, in that order, loaded
-    // before the staging so their latency overlaps it
-    cd r = mk(0, 0);
-    if (out_ok && sp == 0) {
-        r = f.d[((size_t)b * f.ns + o) * f.nt + n];
-        const size_t seg_stride = (size_t)f.B * f.ns * kCausalSuper;
-        const cd* fp = f.facc + ((size_t)b * f.ns + o) * kCausalSuper + (n - f.s_from);
-        for (int q = 0; q < f.nseg; ++q) r = r + fp[q * seg_stride];
-    }
-    // sources: thread t stages entry e of row q for problem bq (one each);
-    // coefficients: row p of subdomain k (p = 0, 1: slot 2k - 2 with the left,
-    // right source; p = 2, 3: slot 2k + 1), one copy per problem if each has
-    // its own potential.  All loads are issued before any store.
-    static_assert(kCausalSuper == 256 && TB <= 256, "far kernel staging: one source entry per thread");
-    constexpr int kCoef = PB * 4 * kWin, kCoefTrips = (kCoef + NT - 1) / NT;
-    const int nc = f.per_problem ? kCoef : 4 * kWin;
-    cd x = mk(0, 0), c[kCoefTrips];
-    {
-        const int q = t / (PB * 256), bq = (t / 256) % PB, e = t % 256;
-        if ((q == 0 ? hasl : hasr) && b0 + bq < f.B && e < len)
-            x = f.g[((size_t)(b0 + bq) * f.ns + 2 * k - 1 + q) * f.nt + f.s_from + e];
-    }
+    const cd zero = mk(0, 0);
+    // rows of coefficients: p = 0, 1: slot 2k - 2 with the left, right source;
+    // p = 2, 3: slot 2k + 1
+    const int v = f.per_problem ? b : 0;
+    const cd* cr = f.cols + (size_t)(v * f.N + k) * 4 * f.nt;
+    const cd* xr = f.g + ((size_t)b * f.ns + 2 * k - 1) * f.nt + f.s_from;
+    // every load is in flight before the first is stored
+    constexpr int kCt = (kWin + NT - 1) / NT, kXt = (kCausalSuper + NT - 1) / NT;
+    cd c[4][kCt], x[2][kXt];
 #pragma unroll
-    for (int m = 0; m < kCoefTrips; ++m) {
-        const int u = t + m * NT, cb = u / (4 * kWin), p = (u / kWin) % 4, e = u % kWin;
-        const bool row_ok = (p == 0 || p == 2 ? hasl : hasr) && (p < 2 ? hasl : hasr);
-        const int v = f.per_problem ? b0 + cb : 0;
-        c[m] = mk(0, 0);
-        if (u < nc && row_ok && e < len + TB && e < f.nt && (!f.per_problem || v < f.B))
-            c[m] = f.cols[((size_t)(v * f.N + k) * 4 + p) * f.nt + e];
-    }
-    (&sg[0][0][0])[t] = x;
+    for (int p = 0; p < 4; ++p) {
+        const bool ok = (p == 0 || p == 2 ? hasl : hasr) && (p < 2 ? hasl : hasr);
 #pragma unroll
-    for (int m = 0; m < kCoefTrips; ++m) {
-        const int u = t + m * NT;
-        if (u < nc) (&sc[0][0][0])[u] = c[m];
-    }
-    __syncthreads();
-    const int per = (len + SPLITS - 1) / SPLITS;
-    const int s_lo = f.s_from + sp * per, s_hi = min(f.n0, s_lo + per);
-    const cd* cl = sc[f.per_problem ? bb : 0][2 * h];
-    const cd* cr = sc[f.per_problem ? bb : 0][2 * h + 1];
-    double ax = 0, ay = 0;
-    if (out_ok) {
-        for (int s = s_lo; s < s_hi; ++s) {
-            const int e = s - f.s_from, lag = n - s;
-            if (hasl) {
-                const cd cc = cl[lag], xx = sg[0][bb][e];
-                ax += cc.x * xx.x - cc.y * xx.y;
-                ay += cc.x * xx.y + cc.y * xx.x;
-            }
-            if (hasr) {
-                const cd cc = cr[lag], xx = sg[1][bb][e];
-                ax += cc.x * xx.x - cc.y * xx.y;
-                ay += cc.x * xx.y + cc.y * xx.x;
-            }
+        for (int m = 0; m < kCt; ++m) {
+            const int e = t + m * NT;
+            c[p][m] = zero;
+            if (ok && e < len + TB && e < f.nt) c[p][m] = cr[(size_t)p * f.nt + e];
         }
     }
-    part[h][bb][sp][i] = mk(ax, ay);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int m = 0; m < kXt; ++m) {
+            const int e = t + m * NT;
+            x[q][m] = zero;
+            if ((q == 0 ? hasl : hasr) && e < len) x[q][m] = xr[(size_t)q * f.nt + e];
+        }
+    // outputs: lane o (< OUT) of the last step
+    const int oh = t / TB, oi = t % TB, on = f.n0 + oi;
+    const int oslot = oh == 0 ? 2 * k - 2 : 2 * k + 1;
+    const bool out_ok = t < OUT && (oh == 0 ? hasl : hasr) && oi < f.nb;
+    cd r = zero;
+    if (out_ok) {
+        r = f.d[((size_t)b * f.ns + oslot) * f.nt + on];
+        const size_t seg_stride = (size_t)f.B * f.ns * kCausalSuper;
+        const cd* fp = f.facc + ((size_t)b * f.ns + oslot) * kCausalSuper + (on - f.s_from);
+        for (int q = 0; q < f.nseg; ++q) r = r + fp[q * seg_stride];
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        if (t < kPad) sc[p][t] = zero;
+#pragma unroll
+        for (int m = 0; m < kCt; ++m) {
+            const int e = t + m * NT;
+            if (e < kWin) sc[p][kPad + e] = c[p][m];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (t < kPad) sx[q][kCausalSuper + t] = zero;
+#pragma unroll
+        for (int m = 0; m < kXt; ++m) {
+            const int e = t + m * NT;
+            if (e < kCausalSuper) sx[q][e] = x[q][m];
+        }
+    }
     __syncthreads();
-    if (out_ok && sp == 0) {
-        for (int q = 0; q < SPLITS; ++q) r = r + part[h][bb][q][i];
-        f.out[far_out<TB>(b, f.ns, o, i)] = r;
+    const int grp = t % GROUPS, sp = t / GROUPS;
+    const int h = grp / (TB / R), i0 = grp % (TB / R) * R;
+    const int per = (len + 4 * SPLITS - 1) / (4 * SPLITS) * 4;
+    const int e_lo = sp * per, e_hi = min(len, e_lo + per);
+    cd acc[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) acc[q] = zero;
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        // output i0 + q meets source e at lag len + i0 + q - e
+        const cd* cw = sc[2 * h + side] + kPad + len + i0;
+        const cd* xw = sx[side];
+        cd w[R + 3];                                    // lags of outputs 0 .. R - 1 and sources e .. e + 3
+#pragma unroll
+        for (int q = 0; q < R - 1; ++q) w[q + 4] = e_lo < e_hi ? cw[q + 1 - e_lo] : zero;
+        for (int e = e_lo; e < e_hi; e += 4) {
+            cd xs[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                w[3 - j] = cw[-e - j];
+                xs[j] = xw[e + j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int q = 0; q < R; ++q) acc[q] = madd(acc[q], w[3 + q - j], xs[j]);
+#pragma unroll
+            for (int q = R - 2; q >= 0; --q) w[q + 4] = w[q];
+        }
+    }
+    // the wave's shares: lanes of a group are GROUPS apart
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        acc[q].x = far_lanes<GROUPS>(acc[q].x);
+        acc[q].y = far_lanes<GROUPS>(acc[q].y);
+    }
+    __syncthreads();
+    cd* part = &sc[0][0];                               // [wave][output]
+    if (t % kWave < GROUPS) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) part[t / kWave * OUT + h * TB + i0 + q] = acc[q];
+    }
+    __syncthreads();
+    if (out_ok) {
+        cd y = part[t];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) y = y + part[q * OUT + t];
+        f.out[far_out<TB>(b, f.ns, oslot, oi)] = r + y;
     }
 }
 
@@ -282,6 +335,7 @@ static __device__ inline double far_swap_pair(double v) {   // the value of lane
     return *reinterpret_cast<double*>(&t);
 }
 constexpr int kFarMfmaB = 8;    // problems per wave of the matrix-core form
+constexpr size_t kFarWaves = 1024;
 
 template <int TB>
 __global__ __launch_bounds__(64) void causal_far_mfma_kernel(FarArgs f) {
@@ -678,8 +732,8 @@ static hipError_t launch_causal_far(int N, int nt, int ns, int B, int per_proble
             return hipGetLastError();
         }
     }
-    if (B == 1) causal_far_kernel<TB, 1><<<dim3(N, 1), 2 * 256, 0, st>>>(f);
-    else causal_far_kernel<TB, 2><<<dim3(N, (B + 1) / 2), 2 * 2 * 256, 0, st>>>(f);
+    if ((size_t)N * B >= kFarWaves) causal_far_kernel<TB, 1><<<dim3(N, B), kWave, 0, st>>>(f);
+    else causal_far_kernel<TB, 4><<<dim3(N, B), 4 * kWave, 0, st>>>(f);
     return hipGetLastError();
 }
 
