@@ -262,6 +262,11 @@ constexpr size_t kTimeRecordBytes = (size_t)4 << 30;
 // steps and block of 64 outputs, which passes the cost of the split (a product
 // and a launch per 256 steps, about 30 us) near 1000 past steps
 constexpr int kUnsplitSteps = 2048;
+// static sweeps with the higher-order or Pade operators: all chunk widths of a
+// list of at most this many tasks run in one launch, one wave per SIMD (24 uneven
+// subdomains of three widths, 1000 steps: 5.3 -> 2.2 ms a solve); longer
+// lists take a launch per width, whose narrow widths run more waves per SIMD
+constexpr int kAnyMaxTasks = 1024;
 // schedule parameters of launch forms that no longer exist; still validated,
 // saved and reported (bounds and defaults)
 constexpr int kPairFrom = kMaxP + 1;
@@ -450,6 +455,7 @@ hipError_t launch_sweep_static_pade(const SweepArgs& a, hipStream_t st);
 hipError_t launch_sweep_long(const SweepArgs& a, int trans, int vk, hipStream_t st);
 hipError_t launch_factor_long(const FactorArgs& a, int Q, hipStream_t st);
 hipError_t launch_sweep_time(const SweepArgs& a, int trans, hipStream_t st);
+hipError_t launch_sweep_any(const SweepArgs& a, int trans, hipStream_t st);
 hipError_t launch_sweep_cubic_hi(const SweepArgs& a, int trans, hipStream_t st);
 // static potential, Robin or S0^2 (swr_sweep_rows*.hip): the workgroups a.items[0 .. nitems - 1] of
 // one kind, records a.fac with stride a.fstride; pmax: their widest

@@ -961,7 +961,8 @@ static const RowsList& rows_of(const swr_ctx* c, const Task* tasks) {
 // all tasks of a's list (a.task0 = 0, a.ntasks = the whole list), in order on
 // one stream; *launches counts them per chunk width (plain: per task).  Robin or
 // S0^2: the row form, one launch for all widths of a kind (plain: one per task),
-// except V(t,x) that refactors.  Else one launch per chunk width.
+// except V(t,x) that refactors.  Higher-order and Pade operators of a static
+// potential: one launch for a short list.  Else one launch per chunk width.
 static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hipStream_t st, bool plain,
                                       int* launches) {
     const int tr = ktr(c);
@@ -980,7 +981,14 @@ static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hip
             }
         }
     }
-    for (const WidthRun& r : runs_of(c, a.tasks)) {
+    const std::vector<WidthRun>& runs = runs_of(c, a.tasks);
+    const bool any = (tr == TR_GEN || tr == TR_PADE) && vk == SWR_V_STATIC && !plain && runs.size() > 1 &&
+                     a.ntasks <= kAnyMaxTasks;
+    if (any) {
+        const hipError_t e = launch_sweep_any(a, tr, st);
+        if (e != hipSuccess) return e;
+    }
+    for (const WidthRun& r : runs) {
         a.P = r.P;
         a.task0 = r.start;
         a.ntasks = r.count;
@@ -998,7 +1006,7 @@ static hipError_t launch_widths_range(const swr_ctx* c, SweepArgs a, int vk, hip
                 e = launch_sweep_long(a, tr, vk, st);
             }
         } else {
-            e = rows ? hipSuccess : launch_sweep(a, tr, vk, st, plain);
+            e = rows || any ? hipSuccess : launch_sweep(a, tr, vk, st, plain);
         }
         if (e != hipSuccess) return e;
         if (launches) *launches += plain && r.P <= kMaxP ? r.count : 1;

@@ -149,15 +149,24 @@ __device__ inline void gen_end_coef(int tr, double W, double dW, double dt, cd c
 // dependent (rows rebuilt and refactored every step from the streamed V rows)
 // or |u|^2 (V-free factors, inner fixed point of eq. AvMNL every step).
 // ---------------------------------------------------------------------------
+struct SweepShared {
+    double sbeta[2 * kWave];         // beta_0 .. beta_127
+    cd ffa[2][kWave], ffb[2][kWave]; // S0^2: far sums from the helper wave
+    cd sha[kWave], shb[kWave];       // staged chunk of the boundary history
+    double sb[2 * kWave];            // beta window of that chunk
+};
+
 template <int P, int TR, int VK, bool HELP = false>
-__global__ __launch_bounds__(sweep_threads(HELP)) void sweep_kernel(SweepArgs a) {
+__device__ __forceinline__ void sweep_body(const SweepArgs& a, SweepShared& sh) {
     static_assert(!HELP || TR == TR_S02, "the helper wave serves S0^2");
     static_assert(VK == VK_TIME || (TR == TR_GEN || TR == TR_PADE),
                   "static potential and |u|^2 with Robin or S0^2: the row form");
-    __shared__ double sbeta[2 * kWave];       // beta_0 .. beta_127
-    __shared__ cd ffa[2][kWave], ffb[2][kWave];   // S0^2: far sums from the helper wave
-    __shared__ cd sha[kWave], shb[kWave];     // staged chunk of the boundary history
-    __shared__ double sb[2 * kWave];          // beta window of that chunk
+    double* const sbeta = sh.sbeta;
+    cd (*const ffa)[kWave] = sh.ffa;
+    cd (*const ffb)[kWave] = sh.ffb;
+    cd* const sha = sh.sha;
+    cd* const shb = sh.shb;
+    double* const sb = sh.sb;
     const int t = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x / kWave;     // 1: the S0^2 helper wave
     const int tix = a.task0 + blockIdx.x;   // task index (per-task buffers)
@@ -238,7 +247,8 @@ __global__ __launch_bounds__(sweep_threads(HELP)) void sweep_kernel(SweepArgs a)
     cd* pst = (TR == TR_PADE && a.pstate) ? a.pstate + (size_t)tix * 6 * kWave + t : nullptr;
     const cd pcc = mk(0.0, 2.0 / a.dt);
     auto pade_sum = [&](int e) {
-        const cd p = pw[e][0] * pphi[e][0] + pw[e][1] * pphi[e][1];
+        // (roundings spelled out: formed at a launch's start and after a step)
+        const cd p = madd_x(cmul_x(pw[e][0], pphi[e][0]), pw[e][1], pphi[e][1]);
         return mk(wave_sum(p.x), wave_sum(p.y));
     };
     // r_s = 1/(c + W + d_s), c r_s, w_s = i a_s d_s c r_s at end e for the
@@ -878,6 +888,29 @@ __global__ __launch_bounds__(sweep_threads(HELP)) void sweep_kernel(SweepArgs a)
     if (VK == VK_CUBIC && t == 0 && a.nl_stats) {
         atomicMax(&a.nl_stats[0], nl_worst);
         if (nl_fail) atomicMax(&a.nl_stats[1], 1);
+    }
+}
+
+template <int P, int TR, int VK, bool HELP = false>
+__global__ __launch_bounds__(sweep_threads(HELP)) void sweep_kernel(SweepArgs a) {
+    __shared__ SweepShared sh;
+    sweep_body<P, TR, VK, HELP>(a, sh);
+}
+
+// every chunk width of a task list in one launch: the widths of an uneven
+// decomposition, launched one by one, ran one after the other on the stream
+template <int TR>
+__global__ __launch_bounds__(kWave) void sweep_any_kernel(SweepArgs a) {
+    __shared__ SweepShared sh;
+    switch ((a.J[a.tasks[a.task0 + blockIdx.x].k] + kWave) / kWave) {
+        case 1: sweep_body<1, TR, VK_STATIC>(a, sh); break;
+        case 2: sweep_body<2, TR, VK_STATIC>(a, sh); break;
+        case 3: sweep_body<3, TR, VK_STATIC>(a, sh); break;
+        case 4: sweep_body<4, TR, VK_STATIC>(a, sh); break;
+        case 5: sweep_body<5, TR, VK_STATIC>(a, sh); break;
+        case 6: sweep_body<6, TR, VK_STATIC>(a, sh); break;
+        case 7: sweep_body<7, TR, VK_STATIC>(a, sh); break;
+        case 8: sweep_body<8, TR, VK_STATIC>(a, sh); break;
     }
 }
 

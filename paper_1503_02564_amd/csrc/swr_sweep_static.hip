@@ -10,6 +10,17 @@ static void launch_p(const SweepArgs& a, hipStream_t st) {
     sweep_kernel<P, TR_GEN, VK_STATIC><<<a.ntasks, sweep_threads(false), 0, st>>>(a);
 }
 
+hipError_t launch_sweep_any_gen(const SweepArgs& a, hipStream_t st);
+hipError_t launch_sweep_any_pade(const SweepArgs& a, hipStream_t st);
+
+hipError_t launch_sweep_any(const SweepArgs& a, int trans, hipStream_t st) {
+    if (a.ntasks == 0) return hipSuccess;
+    if (!a.endc) return hipErrorInvalidValue;
+    if (trans == TR_GEN) return launch_sweep_any_gen(a, st);
+    if (trans == TR_PADE && a.pade && a.pade_m >= 1 && a.pade_m <= kPadeMax) return launch_sweep_any_pade(a, st);
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_sweep_static(const SweepArgs& a, int trans, hipStream_t st) {
     if (trans == TR_PADE) return launch_sweep_static_pade(a, st);
     if (trans != TR_GEN || !a.endc) return hipErrorInvalidValue;
