@@ -479,6 +479,15 @@ hipError_t launch_beta(int n, double* beta, hipStream_t st);
 // launchers (swr_iface.hip)
 hipError_t launch_ltt(const LttArgs& a, hipStream_t st);
 int ltt_seg_blocks(int ns, int B, bool per_problem, int nblk);
+// BiCGStab's scalars of one problem, and the stages of an iteration (bicg_kernel)
+struct BicgState {
+    cd rho, rho_new, alpha, omega;
+    double bn, rel;              // |rhs|; relative residual of the last iteration
+    int act, half, bad;          // still iterating; |s| already small; a norm was not finite
+};
+enum { kBicgInit, kBicgBeta, kBicgAlpha, kBicgHalf, kBicgOmega, kBicgEnd };
+hipError_t launch_bicg(int stage, const cd* u, const cd* w, long M, int B, double* partial, BicgState* st,
+                       cd* coef, double tol, hipStream_t stream);
 hipError_t launch_lincomb(const cd* x0, const cd* x1, const cd* x2, const cd* coef, cd* z, long M,
                           int B, hipStream_t st);
 hipError_t launch_multidot(const cd* basis, int nv, const cd* w, long M, int B, double* partial,

@@ -150,8 +150,8 @@ struct swr_ctx {
     double* dRes = nullptr;
     int* dAct = nullptr;
     cd* dBi = nullptr;        // BiCGStab work vectors r, r^, p, v, s, t: [6][B][ns][nt]
-    cd* dCoef = nullptr;      // [B][3] per-problem coefficients of lincomb
-    cd* dDot = nullptr;       // [B] complex dot products
+    cd* dCoef = nullptr;      // [2][B][3] per-problem coefficients of lincomb
+    BicgState* dBicg = nullptr;
     cd* dFar = nullptr;       // causal dense path
     cd* dFacc = nullptr;      // causal PCR paths: [seg][B][ns][256] contribution of each
                               // finished super-block to the current one
@@ -1211,87 +1211,53 @@ static swr_status run_bicgstab(swr_ctx* c, const Op& A, const cd* rhs, cd* x, in
     hipStream_t st = c->st;
     if (!c->dBi) {
         ALLOC_LIVE(c->dBi, 6 * vec);
-        ALLOC_LIVE(c->dCoef, (size_t)3 * B);
-        ALLOC_LIVE(c->dDot, (size_t)B);
+        ALLOC_LIVE(c->dCoef, (size_t)6 * B);
+        ALLOC_LIVE(c->dBicg, (size_t)B);
     }
     cd *r = c->dBi, *rh = r + vec, *p = rh + vec, *v = p + vec, *s = v + vec, *t = s + vec;
-    std::vector<cd> coef(3 * (size_t)B), dot(B), rho(B, mk(1, 0)), alpha(B, mk(1, 0)), omega(B, mk(1, 0)),
-        rho_new(B);
-    std::vector<double> bn(B), nr(B);
-    std::vector<char> act(B), half(B);
-    auto dots = [&](const cd* u, const cd* w) -> swr_status {   // dot[b] = <u_b, w_b>
-        HIPCHK(launch_multidot(u, 1, w, M, B, c->dPart, c->dDot, 1, 0, st));
-        HIPCHK(hipMemcpyAsync(dot.data(), c->dDot, sizeof(cd) * B, hipMemcpyDeviceToHost, st));
+    std::vector<BicgState> state(B);
+    auto stage = [&](int k, const cd* u, const cd* w) {
+        return launch_bicg(k, u, w, M, B, c->dPart, c->dBicg, c->dCoef, tol, st);
+    };
+    auto comb = [&](const cd* x0, const cd* x1, const cd* x2, cd* z, int set = 0) {
+        return launch_lincomb(x0, x1, x2, c->dCoef + (size_t)3 * B * set, z, M, B, st);
+    };
+    // the scalars live on the device; the host reads them once an iteration
+    auto read = [&]() -> swr_status {
+        HIPCHK(hipMemcpyAsync(state.data(), c->dBicg, sizeof(BicgState) * B, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         return SWR_OK;
     };
-    auto norms = [&](const cd* w, std::vector<double>& out) -> swr_status {
-        HIPCHK(launch_norm(w, M, B, c->dPart, c->dNrm, st));
-        HIPCHK(hipMemcpyAsync(out.data(), c->dNrm, sizeof(double) * B, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        return SWR_OK;
-    };
-    auto comb = [&](const cd* x0, const cd* x1, const cd* x2, cd* z) -> swr_status {
-        HIPCHK(hipMemcpyAsync(c->dCoef, coef.data(), sizeof(cd) * 3 * B, hipMemcpyHostToDevice, st));
-        HIPCHK(launch_lincomb(x0, x1, x2, c->dCoef, z, M, B, st));
-        return SWR_OK;
-    };
-    auto set = [&](int b, cd a0, cd a1, cd a2) { coef[3 * b] = a0; coef[3 * b + 1] = a1; coef[3 * b + 2] = a2; };
-    const cd one = mk(1, 0), zero = mk(0, 0);
     HIPCHK(hipMemsetAsync(x, 0, vec * sizeof(cd), st));
     HIPCHK(hipMemsetAsync(p, 0, vec * sizeof(cd), st));
     HIPCHK(hipMemsetAsync(v, 0, vec * sizeof(cd), st));
     HIPCHK(hipMemcpyAsync(r, rhs, vec * sizeof(cd), hipMemcpyDeviceToDevice, st));
     HIPCHK(hipMemcpyAsync(rh, rhs, vec * sizeof(cd), hipMemcpyDeviceToDevice, st));
-    CHK(norms(rhs, bn));
+    HIPCHK(stage(kBicgInit, nullptr, rhs));
+    CHK(read());
     bool any = false;
-    for (int b = 0; b < B; ++b) { act[b] = bn[b] > 0; any |= act[b] != 0; }
+    for (const BicgState& q : state) any |= q.act != 0;
     int its = 0;
     while (any && its < max_iter) {
         ++its;
-        CHK(dots(rh, r));
-        for (int b = 0; b < B; ++b) {
-            rho_new[b] = dot[b];
-            if (act[b]) {
-                const cd beta = (rho_new[b] * inv(rho[b])) * (alpha[b] * inv(omega[b]));
-                set(b, one, beta, -(beta * omega[b]));
-            } else {
-                set(b, zero, one, zero);
-            }
-        }
-        CHK(comb(r, p, v, p));                                   // p = r + beta (p - omega v)
+        HIPCHK(stage(kBicgBeta, rh, r));
+        HIPCHK(comb(r, p, v, p));                                // p = r + beta (p - omega v)
         CHK(A(p, v));
-        CHK(dots(rh, v));
-        for (int b = 0; b < B; ++b) {
-            alpha[b] = act[b] ? rho_new[b] * inv(dot[b]) : zero;
-            set(b, one, -alpha[b], zero);
-        }
-        CHK(comb(r, v, nullptr, s));                             // s = r - alpha v
-        CHK(norms(s, nr));
-        for (int b = 0; b < B; ++b) {
-            if (!std::isfinite(nr[b])) return SWR_ENAN;
-            half[b] = act[b] && nr[b] <= tol * bn[b];
-        }
+        HIPCHK(stage(kBicgAlpha, rh, v));
+        HIPCHK(comb(r, v, nullptr, s));                          // s = r - alpha v
+        HIPCHK(stage(kBicgHalf, nullptr, s));
         CHK(A(s, t));
-        CHK(dots(t, s));
-        std::vector<cd> ts = dot;
-        CHK(dots(t, t));
-        for (int b = 0; b < B; ++b) {
-            omega[b] = (act[b] && !half[b]) ? ts[b] * inv(dot[b]) : zero;
-            set(b, one, act[b] ? alpha[b] : zero, omega[b]);
-        }
-        CHK(comb(x, p, s, x));                                   // x += alpha p + omega s
-        for (int b = 0; b < B; ++b) set(b, one, -omega[b], zero);
-        CHK(comb(s, t, nullptr, r));                             // r = s - omega t
-        CHK(norms(r, nr));
+        HIPCHK(stage(kBicgOmega, s, t));                         // <s, t>, <t, t> (t follows s)
+        HIPCHK(comb(x, p, s, x));                                // x += alpha p + omega s
+        HIPCHK(comb(s, t, nullptr, r, 1));                       // r = s - omega t
+        HIPCHK(stage(kBicgEnd, nullptr, r));
+        CHK(read());
         any = false;
         double worst = 0;
-        for (int b = 0; b < B; ++b) {
-            if (!std::isfinite(nr[b])) return SWR_ENAN;
-            if (act[b] && bn[b] > 0) worst = std::max(worst, (half[b] ? 0.0 : nr[b]) / bn[b]);
-            if (half[b] || nr[b] <= tol * bn[b]) act[b] = 0;
-            any |= act[b] != 0;
-            rho[b] = rho_new[b];
+        for (const BicgState& q : state) {
+            if (q.bad) return SWR_ENAN;
+            worst = std::max(worst, q.rel);
+            any |= q.act != 0;
         }
         if (record) c->hist.push_back(worst);
     }

@@ -567,6 +567,77 @@ hipError_t launch_lincomb(const cd* x0, const cd* x1, const cd* x2, const cd* co
     return hipGetLastError();
 }
 
+// Scalars of BiCGStab on the device, one wave per problem: each stage sums the
+// partials of the inner products or the norm just formed and sets the
+// coefficients of the vector update that follows.  (Brought to the host one by
+// one, they cost five round trips an iteration, more than its products.)
+__global__ __launch_bounds__(kWave) void bicg_kernel(int stage, const double* partial, int nblk, BicgState* st,
+                                                     cd* coef, int B, double tol) {
+    const int b = blockIdx.x;
+    const cd one = mk(1, 0), zero = mk(0, 0);
+    const int nv = stage == kBicgOmega ? 2 : 1;
+    const bool norm = stage == kBicgInit || stage == kBicgHalf || stage == kBicgEnd;
+    cd d[2] = {zero, zero};
+    for (int i = 0; i < nv; ++i) {
+        double sx = 0, sy = 0;
+        for (int k = threadIdx.x; k < nblk; k += kWave) {
+            if (norm) sx += partial[(size_t)b * nblk + k];
+            else {
+                const double* pp = partial + (((size_t)b * nblk + k) * nv + i) * 2;
+                sx += pp[0];
+                sy += pp[1];
+            }
+        }
+        d[i] = mk(wave_sum(sx), wave_sum(sy));
+    }
+    if (threadIdx.x) return;
+    BicgState& s = st[b];
+    cd* c = coef + 3 * b;
+    auto set = [](cd* q, cd a0, cd a1, cd a2) { q[0] = a0; q[1] = a1; q[2] = a2; };
+    const double nrm = sqrt(d[0].x);
+    if (stage == kBicgInit) {
+        s.rho = s.alpha = s.omega = one;
+        s.bn = nrm;
+        s.act = nrm > 0;
+        s.bad = s.half = 0;
+    } else if (stage == kBicgBeta) {               // p = r + beta (p - omega v)
+        s.rho_new = d[0];
+        if (s.act) {
+            const cd beta = (d[0] * inv(s.rho)) * (s.alpha * inv(s.omega));
+            set(c, one, beta, -(beta * s.omega));
+        } else {
+            set(c, zero, one, zero);
+        }
+    } else if (stage == kBicgAlpha) {              // s = r - alpha v
+        s.alpha = s.act ? s.rho_new * inv(d[0]) : zero;
+        set(c, one, -s.alpha, zero);
+    } else if (stage == kBicgHalf) {               // |s|
+        s.bad |= !isfinite(nrm);
+        s.half = s.act && nrm <= tol * s.bn;
+    } else if (stage == kBicgOmega) {              // <s, t>, <t, t>: x += alpha p + omega s, r = s - omega t
+        s.omega = (s.act && !s.half) ? conjc(d[0]) * inv(d[1]) : zero;
+        set(c, one, s.act ? s.alpha : zero, s.omega);
+        set(c + 3 * (size_t)B, one, -s.omega, zero);
+    } else {                                       // |r|
+        s.bad |= !isfinite(nrm);
+        s.rel = (s.act && s.bn > 0) ? (s.half ? 0.0 : nrm) / s.bn : 0.0;
+        if (s.half || nrm <= tol * s.bn) s.act = 0;
+        s.rho = s.rho_new;
+    }
+}
+
+// inner products <u_i, w> (nv = 2 for kBicgOmega, u_2 after u_1) or the norm of
+// w, then the stage
+hipError_t launch_bicg(int stage, const cd* u, const cd* w, long M, int B, double* partial, BicgState* st,
+                       cd* coef, double tol, hipStream_t stream) {
+    if (stage == kBicgInit || stage == kBicgHalf || stage == kBicgEnd)
+        norm2_kernel<<<dim3(kRedBlocks, B), kRedThreads, 0, stream>>>(w, M, partial);
+    else
+        multidot_kernel<<<dim3(kRedBlocks, B), kRedThreads, 0, stream>>>(u, stage == kBicgOmega ? 2 : 1, w, M, B, partial);
+    bicg_kernel<<<B, kWave, 0, stream>>>(stage, partial, kRedBlocks, st, coef, B, tol);
+    return hipGetLastError();
+}
+
 hipError_t launch_multidot(const cd* basis, int nv, const cd* w, long M, int B, double* partial,
                            cd* out, int out_ld, int accumulate, hipStream_t st) {
     multidot_kernel<<<dim3(kRedBlocks, B), kRedThreads, 0, st>>>(basis, nv, w, M, B, partial);
