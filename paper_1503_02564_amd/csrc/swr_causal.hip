@@ -23,7 +23,7 @@
 // product on the matrix cores (launch_ltt).  `causal_far_kernel` adds to d that product and
 // the contribution of the earlier blocks of the current super-block (a short
 // rectangle, one workgroup per subdomain and problem; for a batch of
-// eight or more problems with one potential `causal_far_mfma_kernel`, one
+// problems with one potential `causal_far_mfma_kernel`, one
 // wave per subdomain and eight problems on the matrix cores);
 // `causal_near_kernel` then
 // marches through the block on one workgroup per problem: wave 0 runs the
@@ -309,8 +309,8 @@ __global__ __launch_bounds__(NW * kWave) void causal_far_kernel(FarArgs f) {
     }
 }
 
-// Matrix-core form of the same sums for a batch with one potential (at least
-// 8 problems, TB = 8 or 32).  One wave per (subdomain k, 8 problems): the
+// Matrix-core form of the same sums for a large batch with one potential
+// (batch_form; TB = 8 or 32).  One wave per (subdomain k, 8 problems): the
 // rows of the product are the block's TB outputs of the two slots subdomain
 // k feeds (slot 2k - 2, then slot 2k + 1: 2 TB rows in 16-row blocks), the
 // columns the 8 problems' real and imaginary parts, and K runs over the
@@ -727,7 +727,7 @@ static hipError_t launch_causal_far(int N, int nt, int ns, int B, int per_proble
     FarArgs f{N, nt, ns, per_problem, n0, nb, cols, d, g, out, facc,
               facc ? nseg : 0, s_from, B};
     if constexpr (TB == 8 || TB == 32) {
-        if (!per_problem && B >= kFarMfmaB) {
+        if (batch_form(N, B, per_problem)) {
             causal_far_mfma_kernel<TB><<<dim3(N, (B + kFarMfmaB - 1) / kFarMfmaB), 64, 0, st>>>(f);
             return hipGetLastError();
         }

@@ -477,8 +477,18 @@ hipError_t launch_finalize_snaps(int N, int nx, int B, int S, const int* off, co
                                  cd* snaps, hipStream_t st);
 hipError_t launch_beta(int n, double* beta, hipStream_t st);
 // launchers (swr_iface.hip)
+// Batches of at least eight problems with one potential: from this many
+// (problem, subdomain) pairs on, the interface products take eight problems as the
+// columns of a matrix instruction (no zero operands, eight times fewer waves);
+// below, the one-problem forms, which fill the GPU.  768 steps, 100 cells each,
+// one-problem / batched: 32 subdomains x 8 problems 1.90 / 2.61 ms, 64 x 32 3.16 /
+// 3.78, 300 x 8 4.78 / 4.98, 100 x 32 4.57 / 4.53, 300 x 16 6.81 / 6.27 ms.
+constexpr size_t kBatchFrom = 3072;
+inline bool batch_form(int N, int B, bool per_problem) {
+    return B >= 8 && !per_problem && (size_t)N * B >= kBatchFrom;
+}
 hipError_t launch_ltt(const LttArgs& a, hipStream_t st);
-int ltt_seg_blocks(int ns, int B, bool per_problem, int nblk);
+int ltt_seg_blocks(int N, int B, bool per_problem, int nblk);
 // BiCGStab's scalars of one problem, and the stages of an iteration (bicg_kernel)
 struct BicgState {
     cd rho, rho_new, alpha, omega;

@@ -1410,7 +1410,7 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
             int nseg = 0;
             if (S > 0) {
                 // in partials of a few finished super-blocks each (split over the sources)
-                const int nblk = S / kCausalSuper, per = ltt_seg_blocks(ns, B, I.nv > 1, nblk);
+                const int nblk = S / kCausalSuper, per = ltt_seg_blocks(c->N, B, I.nv > 1, nblk);
                 nseg = (nblk + per - 1) / per;
                 LttArgs l{};
                 l.N = c->N; l.nt = nt; l.ns = ns; l.B = B; l.per_problem = I.nv > 1;

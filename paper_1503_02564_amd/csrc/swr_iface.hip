@@ -302,10 +302,10 @@ __global__ __launch_bounds__(256) void ltt_batch_kernel(LttArgs a) {
     }
 }
 
-// the batched form: one potential, at least kLttBatch problems, short ranges
+// the batched form: short ranges
 static bool ltt_batched(const LttArgs& a) {
     const int slen = a.s_seg > 0 ? std::min(a.s_seg, a.s_hi - a.s_lo) : a.s_hi - a.s_lo;
-    return a.B >= kLttBatch && !a.per_problem && a.n_hi - a.n_lo <= kLttStage && slen <= kLttStage;
+    return batch_form(a.N, a.B, a.per_problem) && a.n_hi - a.n_lo <= kLttStage && slen <= kLttStage;
 }
 
 // Super-blocks of sources per partial of a causal solve's history product.
@@ -314,8 +314,9 @@ static bool ltt_batched(const LttArgs& a) {
 // fewer, for kLttFill workgroups, where they do not; the batched form stages
 // one at a time.
 constexpr int kLttFill = 512;
-int ltt_seg_blocks(int ns, int B, bool per_problem, int nblk) {
-    if (B >= kLttBatch && !per_problem) return 1;
+int ltt_seg_blocks(int N, int B, bool per_problem, int nblk) {
+    if (batch_form(N, B, per_problem)) return 1;
+    const int ns = 2 * N - 2;
     const int parts = std::min(nblk, std::max(1, (kLttFill + ns * B - 1) / (ns * B)));
     return (nblk + parts - 1) / parts;
 }

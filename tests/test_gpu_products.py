@@ -57,7 +57,8 @@ def test_product_equals_the_convolution(dev, nt, B, per_problem):
 
 
 @pytest.mark.parametrize("N,B,per_problem,nt", [(4, 1, False, 1300), (40, 2, True, 1100), (40, 8, False, 800),
-                                               (120, 5, True, 700), (40, 26, True, 300)])
+                                               (120, 5, True, 700), (40, 26, True, 300),
+                                               (100, 31, False, 300), (64, 48, False, 300)])
 def test_causal_solution_meets_the_convolution(dev, N, B, per_problem, nt):
     """(I - L) g = d over several super-blocks: certified residual, u(T) against the
     monodomain oracle at the bar of the suite's solves, and the staged solve equal
