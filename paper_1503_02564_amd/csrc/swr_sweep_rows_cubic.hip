@@ -4,8 +4,8 @@
 //
 // Bound: the chain of an inner iteration (nodal weights, chunk solve, reduction
 // over the lanes, convergence maxima), one wave per task.  128 x 256 cells, 600
-// steps: 4.1 ms a sweep in the 64-lane form with history on a second wave, 2.9 ms
-// now; the solve 44.1 -> 33.0 ms.
+// steps: 4.1 ms a sweep in the 64-lane form with history on a second wave, 2.6 ms
+// now; the solve 44.1 -> 30.6 ms.
 #include "swr_sweep_rows_kernel.h"
 
 namespace swr {

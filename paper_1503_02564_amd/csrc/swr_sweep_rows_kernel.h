@@ -302,7 +302,7 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
                 for (int q = 0; q < P; ++q) d[q] = stencil(q);
                 d[0] = dF;
                 d[P - 1] = dS;
-                const double gk = a.h / 12.0 * ik;
+                const double gk = a.h / 12.0 * ik, tol2 = a.nl_tol * a.nl_tol;
                 int it = 1;
                 bool conv = false;
                 for (; it <= a.nl_maxit; ++it) {
@@ -326,8 +326,10 @@ __device__ inline void rows_body(const SweepArgs& a, int first, int count, cd* s
                         zm2 = fmax(zm2, abs2(vlast[q]));
                         vlast[q] = y[q];
                     }
-                    const double dmax = sqrt(wave_max(dm)), zmax = sqrt(wave_max(zm2));
-                    if (dmax <= a.nl_tol * fmax(1.0, zmax)) { conv = true; break; }
+                    // max |x - z| <= tol max(1, max |z|) on the squares; the maxima are the
+                    // same bits on every lane
+                    const bool done = wave_max(dm) <= tol2 * fmax(1.0, wave_max(zm2));
+                    if (__builtin_amdgcn_readfirstlane(done)) { conv = true; break; }
                 }
                 if (!conv) nl_fail = 1;
                 nl_worst = max(nl_worst, conv ? it : a.nl_maxit);
