@@ -26,9 +26,10 @@
 // (P) plus 130 to 190 that do not depend on P; a wave carries 4 / RW tasks, so
 // batches take fewer rows per task (rule in swr_host.hip).  Against one wave per
 // task with a 64-lane reduction and one launch per width (before): 32 problems on
-// 500 uneven subdomains over 2000 steps 103.5 -> 75 ms per solve, gradient of 16
-// potentials on 256 x 64 cells 148 -> 111 ms, one problem on 64 x 256 cells 3.59
-// -> 3.1 ms, one Robin iteration on 4 x 100 cells over 500 steps 0.367 -> 0.275 ms.
+// 500 uneven subdomains over 2000 steps 103.5 -> 75 ms per solve (67 with the
+// interface products' later forms), gradient of 16 potentials on 256 x 64 cells 148
+// -> 111 ms, one problem on 64 x 256 cells 3.59 -> 3.1 ms, one Robin iteration on 4
+// x 100 cells over 500 steps 0.367 -> 0.275 ms.
 #pragma once
 #include <type_traits>
 
@@ -72,25 +73,56 @@ __device__ inline void rows_far(const cd* hist, const double* beta, int nt, bool
     const int ab = n0 + 1 + r - kq;                  // my beta index of group qg: ab - qg
     const int ng = (n0 - qs) / 4 + 1;
     rows_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    double an[U], bn[U];
-    auto fetch = [&](int g) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int qg = qs + 4 * (g + u), q = qg + qb, i = max(ab - qg, 0);
-            bn[u] = 0.0;
-            if (q >= q_lo && q <= n0) bn[u] = hb[2 * q];
-            an[u] = split ? sb[i] : beta[i];
-        }
+    // groups that meet a source outside [q_lo, n0]: the first H and those from g1
+    // on, their reads issued first; the ones between come in fours, without tests
+    // and at constant offsets (with them the loop took 20 instructions a group: one
+    // sweep of 32 problems on 500 uneven subdomains, 512 steps, 6.5 -> 5.8 ms)
+    constexpr int H = 4 * (RW - 1);
+    const int g0 = min(H, ng), g1 = max((n0 - 16 * (RW - 1) - qs) / 4, g0);
+    double vh[H + 1], vt[H + 1];
+    auto edge = [&](int g) {
+        const int q = qs + 4 * g + qb;
+        double v = 0.0;
+        if (q >= q_lo && q <= n0) v = hb[2 * q];
+        return v;
     };
-    fetch(0);
-    for (int g = 0; g < ng; g += U) {
-        double ac[U], bc[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) { ac[u] = an[u]; bc[u] = bn[u]; }
-        if (g + U < ng) fetch(g + U);
+    for (int u = 0; u < H; ++u) vh[u] = edge(u);
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ac[u], bc[u], acc, 0, 0, 0);
-    }
+    for (int u = 0; u <= H; ++u) vt[u] = edge(g1 + u);
+    auto sum = [&](const double* wt) {
+        auto add = [&](int g, double v) {
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(wt[max(ab - qs - 4 * g, 0)], v, acc, 0, 0, 0);
+        };
+        double an[U], bn[U];
+        const double* hp = hb + 2 * (qs + 4 * g0 + qb);
+        const double* wp = wt + (ab - qs - 4 * (g0 + U - 1));
+        auto fetch = [&]() {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                bn[u] = hp[8 * u];
+                an[u] = wp[4 * (U - 1 - u)];
+            }
+            hp += 8 * U;
+            wp -= 4 * U;
+        };
+        if (g0 < g1) fetch();
+#pragma unroll
+        for (int u = 0; u < H; ++u) add(u, vh[u]);
+        for (int g = g0; g < g1; g += U) {
+            double ac[U], bc[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) { ac[u] = an[u]; bc[u] = bn[u]; }
+            if (g + U < g1) fetch();
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ac[u], bc[u], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u <= H; ++u) add(g1 + u, vt[u]);
+    };
+    // (one pointer to either would make the reads of the beta window flat ones)
+    if (split) sum(sb);
+    else sum(beta);
     double* o = reinterpret_cast<double*>(ex + e * kWave + sl * T + 16 * sh) + part;
 #pragma unroll
     for (int k = 0; k < 4; ++k) o[2 * (kq + 4 * k)] = acc[k];
