@@ -28,9 +28,12 @@
 // block before, and every step's newest value for the current block, are
 // added by the sweeping wave with one fused multiply-add per lane each.
 //
-// The kernel template itself is in swr_sweep_kernel.h; swr_sweep_static.hip,
-// swr_sweep_time.hip and swr_sweep_cubic.hip
-// instantiate it.
+// The kernel template itself is in swr_sweep_kernel.h; swr_sweep_static*.hip and
+// swr_sweep_any_*.hip (higher-order and Pade operators), swr_sweep_time*.hip
+// (V(t,x) that refactors in every step) and swr_sweep_cubic_hi*.hip instantiate
+// it.  The other sweeps with Robin or S0^2 have the row form
+// (swr_sweep_rows_kernel.h), above 512 nodes the wide form (swr_sweep_wide.hip,
+// static) and the streaming one (swr_sweep_long.hip).
 #include "swr_lane.h"
 
 namespace swr {

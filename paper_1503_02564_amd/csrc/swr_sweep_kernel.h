@@ -1,6 +1,6 @@
 // swr_sweep_kernel.h -- the subdomain sweep kernel template (see the
-// description at the top of swr_sweep.hip).  Included by the three
-// translation units that instantiate it for one potential kind each, so
+// description at the top of swr_sweep.hip).  Included by the
+// translation units that instantiate it for a potential kind and a width each, so
 // the instantiations compile in parallel.
 #pragma once
 #include "swr_lane.h"
