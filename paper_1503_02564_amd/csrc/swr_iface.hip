@@ -76,6 +76,7 @@ constexpr int kLttSrc = 31;       // staged source blocks
 constexpr int kLttPad = 20;       // entries per source block: eight blocks' operands in all LDS banks
 
 __global__ __launch_bounds__(256) void ltt_mfma_kernel(LttArgs a) {
+    __builtin_amdgcn_s_setprio(2);
     __shared__ cd st_c[2][kLttCoef], st_x[2][kLttSrc * kLttPad];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     const int half = w & 1, side = w >> 1;
@@ -205,6 +206,7 @@ static_assert(2 * kLttBatch == 16, "the 16 columns of a tile are 8 problems x (r
 constexpr int kLttScLen = 2 * kLttStage;   // coefficient window per side
 
 __global__ __launch_bounds__(256) void ltt_batch_kernel(LttArgs a) {
+    __builtin_amdgcn_s_setprio(2);
     extern __shared__ double lds[];
     double* sx = lds;                                            // [2][256][16]
     cd* sc = reinterpret_cast<cd*>(lds + 2 * kLttStage * 16);    // [2][kLttScLen]
