@@ -385,12 +385,13 @@ static bool conv_hist(int tr) { return tr != SWR_ROBIN && tr <= SWR_S14; }
 // Static potentials always do (every static form then sums alike); V(t,x)
 // and |u|^2 contexts only when their sweeps fill the GPU with one-wave tasks
 // -- with few tasks the extra launches of the split cost more than they save
-// (V(t,x) sweeps that refactor sum the far history on a helper wave) -- or when
-// their window is long (kUnsplitSteps).
+// (V(t,x) sweeps that refactor sum the far history on a helper wave) -- or, in
+// the row form, when their window is long (kUnsplitSteps).
 // Contexts with long-chunk subdomains sum it in one piece.
 static bool far_split(const swr_ctx* c) {
     return c->tr == SWR_S02 && !c->Qlong &&
-           (c->vk == SWR_V_STATIC || c->nSub > kHelpMaxTasks || c->nt > kUnsplitSteps);
+           (c->vk == SWR_V_STATIC || c->nSub > kHelpMaxTasks ||
+            (c->nt > kUnsplitSteps && (c->vk == SWR_V_CUBIC || c->nSub <= kTimeRecordTasks)));
 }
 
 // Pade strategy (Sec. 2.2): sqrt(z) ~ sum_{s=0}^m a_s - sum_{s=1}^m a_s d_s/(z + d_s)
