@@ -144,7 +144,8 @@ struct swr_ctx {
     cd* dHp = nullptr;
     cd* dHp2 = nullptr;
     cd* dY = nullptr;
-    double* dPart = nullptr;
+    double* dPart = nullptr;  // partial sums of the reductions: [B][kRedBlocks] x part_out outputs
+    int part_out = 0;
     double* dNrm = nullptr;
     double* dBn = nullptr;
     double* dRes = nullptr;
@@ -635,7 +636,8 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     ALLOC(c->dZero, vec);
     ALLOC(c->dMax, 1);
     ALLOC(c->dNl, 2);
-    ALLOC(c->dPart, (size_t)B * kRedBlocks * 2 * (o.restart + 2));
+    c->part_out = c->o.restart + 2;   // (the schedule's restart, where a cache entry set one)
+    ALLOC(c->dPart, (size_t)B * kRedBlocks * 2 * c->part_out);
     ALLOC(c->dNrm, B);
     ALLOC(c->dBn, B);
     ALLOC(c->dRes, B);
@@ -1114,6 +1116,13 @@ static swr_status run_gmres(swr_ctx* c, const Op& A, const cd* rhs, cd* x, int* 
     const int m = c->o.restart, B = c->B;
     const long M = (long)c->ns * c->nt;
     if (c->gm_m != m) {
+        // (a schedule may raise the restart after setup)
+        if (c->part_out < m + 2) {
+            double* part;
+            ALLOC_LIVE(part, (size_t)B * kRedBlocks * 2 * (m + 2));
+            c->dPart = part;
+            c->part_out = m + 2;
+        }
         ALLOC_LIVE(c->dBasis, (size_t)(m + 1) * B * M);
         ALLOC_LIVE(c->dW, (size_t)B * M);
         ALLOC_LIVE(c->dH, (size_t)B * (m + 1) * m);
