@@ -39,7 +39,9 @@
  *     stderr (call, source line, HIP error name) before SWR_EDEVICE is returned;
  *     with SWR_DEBUG_POISON set, every device buffer the library allocates is
  *     filled with all-ones bytes (NaN as a double) when it is allocated, so a
- *     read before the first write shows in the results.
+ *     read before the first write shows in the results; with
+ *     SWR_DEBUG_ALLOC_LIMIT=n set, a context that would hold more than n bytes
+ *     of device memory meets the failure of a full device.
  *   - Errors are status codes; nothing is thrown across the ABI.  After any
  *     status other than SWR_OK or SWR_ENOCONV the context remains valid for
  *     swr_destroy.

@@ -255,7 +255,9 @@ constexpr int kPipeChunk = 256;
 // refactoring: 128 x 256 cells 0.57 / 1.09 ms, 256 x 256 0.99 / 1.10, 320 x 256
 // 1.37 / 1.13, 256 x 500 1.42 / 1.40 (a solve builds them once for 10 to 40 sweeps).
 constexpr int kTimeRecordTasks = 240;
-// ... and the memory of the records; longer windows are factored piece by piece
+// ... and the memory of the records (at most a quarter of what is free, given
+// back when another buffer of the context needs it); longer windows are factored
+// piece by piece
 constexpr size_t kTimeRecordBytes = (size_t)4 << 30;
 // sweeps of V(t,x) and |u|^2 in the row form sum their S0^2 history in one
 // piece up to this many steps: 64 cycles of matrix instructions per 4 past

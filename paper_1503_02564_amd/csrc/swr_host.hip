@@ -201,6 +201,7 @@ struct swr_ctx {
     // per call, else piece by piece)
     cd* dTfac = nullptr;
     int tsteps = 0;
+    bool tfac_shown = false;     // a caller's graph may hold launches that read them: they stay
     int v_version = 0;           // bumped whenever the potential changes
     // the captured solve and the arguments it was captured with
     hipGraph_t g_graph = nullptr;
@@ -227,7 +228,8 @@ struct swr_ctx {
     double* hRes = nullptr;
     int* hAct = nullptr;
     hipEvent_t ev[6] = {};
-    std::vector<void*> allocs;
+    std::vector<std::pair<void*, size_t>> allocs;   // device memory and its bytes
+    size_t held = 0;                                // ... in all
 };
 
 // with SWR_DEBUG set in the environment, a failing HIP call is reported on
@@ -250,28 +252,59 @@ static void report_hip_error(hipError_t e, const char* what, const char* file, i
         if (s_ != SWR_OK) return s_;                   \
     } while (0)
 
+// device memory, null without room
+static void* raw_alloc(const swr_ctx* c, size_t bytes) {
+    // SWR_DEBUG_ALLOC_LIMIT: past that many bytes in a context the runtime is
+    // asked for more than any device has, so that it refuses as a full device does
+    if (const char* e = std::getenv("SWR_DEBUG_ALLOC_LIMIT"))
+        if (c->held + bytes > std::strtoull(e, nullptr, 10)) bytes = (size_t)1 << 50;
+    void* q = nullptr;
+    if (hipMalloc(&q, bytes) == hipSuccess) return q;
+    (void)hipGetLastError();   // the failure must not surface in a later error check
+    return nullptr;
+}
+
+static void dfree(swr_ctx* c, void* p) {
+    for (auto it = c->allocs.begin(); it != c->allocs.end(); ++it)
+        if (it->first == p) {
+            hipFree(p);
+            c->held -= it->second;
+            c->allocs.erase(it);
+            return;
+        }
+}
+
+// the records of V(t,x) make room: the sweeps refactor from here on
+static swr_status drop_records(swr_ctx* c) {
+    if (!c->dTfac) return SWR_OK;
+    HIPCHK(hipStreamSynchronize(c->st));
+    dfree(c, c->dTfac);
+    c->dTfac = nullptr;
+    c->tsteps = 0;
+    return SWR_OK;
+}
+
 template <class T>
 static swr_status dalloc(swr_ctx* c, T** p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
-    void* q = nullptr;
-    if (hipMalloc(&q, count * sizeof(T)) != hipSuccess) return SWR_ENOMEM;
-    c->allocs.push_back(q);
+    const size_t bytes = count * sizeof(T);
+    void* q = raw_alloc(c, bytes);
+    if (!q && c->dTfac && !c->tfac_shown) {
+        CHK(drop_records(c));
+        q = raw_alloc(c, bytes);
+    }
+    if (!q) return SWR_ENOMEM;
+    c->allocs.emplace_back(q, bytes);
+    c->held += bytes;
     // SWR_DEBUG_POISON: every buffer starts as all-ones bytes (NaN as a
     // double), so a read before the first write shows up in the results
     static const bool poison = std::getenv("SWR_DEBUG_POISON") != nullptr;
-    if (poison && hipMemset(q, 0xff, count * sizeof(T)) != hipSuccess) return SWR_EDEVICE;
+    if (poison && hipMemset(q, 0xff, bytes) != hipSuccess) return SWR_EDEVICE;
     *p = static_cast<T*>(q);
     return SWR_OK;
 }
-// setup-time allocation: a failure releases the half-built context
 #define ALLOC(p, n)                                     \
-    do {                                                \
-        swr_status s_ = dalloc(c, &(p), (size_t)(n));   \
-        if (s_ != SWR_OK) { swr_destroy(c); return s_; } \
-    } while (0)
-// allocation inside a call on a live context: report, keep the context
-#define ALLOC_LIVE(p, n)                                \
     do {                                                \
         swr_status s_ = dalloc(c, &(p), (size_t)(n));   \
         if (s_ != SWR_OK) return s_;                    \
@@ -494,6 +527,8 @@ static void rows_items(const swr_ctx* c, const std::vector<Task>& list, RowsList
     }
 }
 
+static swr_status fill_context(swr_ctx* c, const int* J, const double* V);
+
 extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, double dt, double T,
                                 int vk, const double* V, int tr, double s_re, double s_im,
                                 const swr_opts* opts, void* stream, swr_ctx** out) {
@@ -551,6 +586,22 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     c->c2 = mk(std::cos(-M_PI / 4) * std::sqrt(2.0 / dt), std::sin(-M_PI / 4) * std::sqrt(2.0 / dt));
     // S0^2: the implicit coefficient of c2 sum beta_{n-s} v_s is c2 beta_0 = c2
     c->sigma = (tr == SWR_ROBIN) ? mk(s_re, s_im) : c->c2;
+    swr_status s;
+    try {
+        s = fill_context(c, J, V);
+    } catch (const std::exception&) {   // host memory
+        s = SWR_ENOMEM;
+    }
+    // a failure releases what there is of the context
+    if (s != SWR_OK) { swr_destroy(c); return s; }
+    *out = c;
+    return SWR_OK;
+}
+
+// the rest of swr_setup on a context whose scalars are set
+static swr_status fill_context(swr_ctx* c, const int* J, const double* V) {
+    const swr_opts& o = c->o;
+    const int N = c->N, vk = c->vk, tr = c->tr;
     c->J.assign(J, J + N);
     c->off.resize(N);
     for (int k = 0, acc = 0; k < N; ++k) { c->off[k] = acc; acc += J[k]; }
@@ -665,17 +716,6 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
         if (c->Qlong) ALLOC(c->L0.lfac, (size_t)N * c->lfstride);
         ALLOC(c->L0.tasks, imp0.size());
     }
-    if (vk == SWR_V_TIME && c->rstride && !c->Qlong && c->nSub <= kTimeRecordTasks) {
-        const size_t rec = (size_t)N * c->rstride * sizeof(cd);
-        const size_t fit = kTimeRecordBytes / rec / kWave * kWave;
-        c->tsteps = (int)std::min((size_t)nt, std::max(fit, (size_t)kWave));
-        // (without room for them the sweeps refactor)
-        if (dalloc(c, &c->dTfac, (size_t)c->tsteps * N * c->rstride) != SWR_OK) {
-            c->dTfac = nullptr;
-            c->tsteps = 0;
-        }
-        if (c->dTfac && c->tsteps < nt && !far_split(c)) ALLOC(c->dStateF, sub.size() * 2 * c->P * kWave);
-    }
     // S0^2 sweeps carry their state across super-chunk launches and read the
     // old far-history parts of their super-chunk (see launch_widths)
     if (far_split(c)) {
@@ -698,11 +738,13 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
         else HIPCHK(hipMemsetAsync(c->dV, 0, vn * sizeof(double), c->st));
     }
     if (hipHostMalloc(&c->hRes, sizeof(double) * B) != hipSuccess ||
-        hipHostMalloc(&c->hAct, sizeof(int) * B) != hipSuccess) { swr_destroy(c); return SWR_ENOMEM; }
+        hipHostMalloc(&c->hAct, sizeof(int) * B) != hipSuccess) {
+        (void)hipGetLastError();
+        return SWR_ENOMEM;
+    }
     for (auto& e : c->ev)
         if (const hipError_t er = hipEventCreate(&e); er != hipSuccess) {
             report_hip_error(er, "hipEventCreate", __FILE__, __LINE__);
-            swr_destroy(c);
             return SWR_EDEVICE;
         }
     HIPCHK(hipMemcpyAsync(c->dJ, c->J.data(), N * sizeof(int), hipMemcpyHostToDevice, c->st));
@@ -724,7 +766,23 @@ extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, doubl
     if (c->dPade)
         HIPCHK(hipMemcpyAsync(c->dPade, pade.data(), pade.size() * sizeof(cd), hipMemcpyHostToDevice, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
-    *out = c;
+    // V(t,x) in the row form: factor records, in at most a quarter of what the
+    // buffers above left; without room for 64 steps the sweeps refactor, as they
+    // do once a later buffer needs the room (dalloc)
+    if (vk == SWR_V_TIME && c->rstride && !c->Qlong && c->nSub <= kTimeRecordTasks) {
+        const size_t rec = (size_t)N * c->rstride * sizeof(cd);
+        size_t free_bytes = 0, total = 0;
+        if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
+            (void)hipGetLastError();
+            free_bytes = 0;
+        }
+        const size_t fit = std::min(kTimeRecordBytes, free_bytes / 4) / rec / kWave * kWave;
+        const int steps = (int)std::min((size_t)nt, fit);
+        if (steps > 0 && dalloc(c, &c->dTfac, (size_t)steps * N * c->rstride) == SWR_OK) c->tsteps = steps;
+        if (c->tsteps > 0 && c->tsteps < nt && !c->dStateF &&
+            dalloc(c, &c->dStateF, sub.size() * 2 * c->P * kWave) != SWR_OK)
+            CHK(drop_records(c));
+    }
     return SWR_OK;
 }
 
@@ -737,7 +795,7 @@ extern "C" void swr_destroy(swr_ctx* c) {
     if (c->gs) hipStreamDestroy(c->gs);
     if (c->s2) hipStreamSynchronize(c->s2);
     if (c->s3) hipStreamSynchronize(c->s3);
-    for (void* p : c->allocs) hipFree(p);
+    for (auto& a : c->allocs) hipFree(a.first);
     if (c->hRes) hipHostFree(c->hRes);
     if (c->hAct) hipHostFree(c->hAct);
     for (auto& e : c->ev)
@@ -1119,20 +1177,20 @@ static swr_status run_gmres(swr_ctx* c, const Op& A, const cd* rhs, cd* x, int* 
         // (a schedule may raise the restart after setup)
         if (c->part_out < m + 2) {
             double* part;
-            ALLOC_LIVE(part, (size_t)B * kRedBlocks * 2 * (m + 2));
+            ALLOC(part, (size_t)B * kRedBlocks * 2 * (m + 2));
             c->dPart = part;
             c->part_out = m + 2;
         }
-        ALLOC_LIVE(c->dBasis, (size_t)(m + 1) * B * M);
-        ALLOC_LIVE(c->dW, (size_t)B * M);
-        ALLOC_LIVE(c->dH, (size_t)B * (m + 1) * m);
-        ALLOC_LIVE(c->dCs, (size_t)B * m);
-        ALLOC_LIVE(c->dSn, (size_t)B * m);
-        ALLOC_LIVE(c->dE, (size_t)B * (m + 1));
-        ALLOC_LIVE(c->dHp, (size_t)B * (m + 1));
-        ALLOC_LIVE(c->dHp2, (size_t)B * (m + 1));
-        ALLOC_LIVE(c->dY, (size_t)B * (m + 1));
-        ALLOC_LIVE(c->dResHist, (size_t)B * m);
+        ALLOC(c->dBasis, (size_t)(m + 1) * B * M);
+        ALLOC(c->dW, (size_t)B * M);
+        ALLOC(c->dH, (size_t)B * (m + 1) * m);
+        ALLOC(c->dCs, (size_t)B * m);
+        ALLOC(c->dSn, (size_t)B * m);
+        ALLOC(c->dE, (size_t)B * (m + 1));
+        ALLOC(c->dHp, (size_t)B * (m + 1));
+        ALLOC(c->dHp2, (size_t)B * (m + 1));
+        ALLOC(c->dY, (size_t)B * (m + 1));
+        ALLOC(c->dResHist, (size_t)B * m);
         c->hResHist.assign((size_t)B * m, 0.0);
         c->gm_m = m;
     }
@@ -1220,9 +1278,9 @@ static swr_status run_bicgstab(swr_ctx* c, const Op& A, const cd* rhs, cd* x, in
     const size_t vec = (size_t)B * M;
     hipStream_t st = c->st;
     if (!c->dBi) {
-        ALLOC_LIVE(c->dBi, 6 * vec);
-        ALLOC_LIVE(c->dCoef, (size_t)6 * B);
-        ALLOC_LIVE(c->dBicg, (size_t)B);
+        ALLOC(c->dBi, 6 * vec);
+        ALLOC(c->dCoef, (size_t)6 * B);
+        ALLOC(c->dBicg, (size_t)B);
     }
     cd *r = c->dBi, *rh = r + vec, *p = rh + vec, *v = p + vec, *s = v + vec, *t = s + vec;
     std::vector<BicgState> state(B);
@@ -1354,7 +1412,7 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
         if (fast_ok || gen_ok) {
             const size_t rec = fast_ok ? causal_fast_rec() : (size_t)kMarchRows * ni;
             if (!I.pcr || I.pcr_size < rec * I.nv) {
-                ALLOC_LIVE(I.pcr, rec * I.nv);
+                ALLOC(I.pcr, rec * I.nv);
                 I.pcr_size = rec * I.nv;
             }
             // eta[v][l]: ||D_l^{-1}|| (||L_l|| + ||U_l||) of the system before level l;
@@ -1362,7 +1420,7 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
             // the prefix sums' multipliers over 2^l interfaces, l = 0 ..
             const int ld = fast_ok ? kPcrLevels + 1 : kGenLevelsMax + 1;
             const int L = fast_ok ? kPcrLevels : kGenLevelsMax, l0 = fast_ok ? 0 : 1;
-            if (!I.eta) ALLOC_LIVE(I.eta, (size_t)I.nv * (kGenLevelsMax + 1));
+            if (!I.eta) ALLOC(I.eta, (size_t)I.nv * (kGenLevelsMax + 1));
             if (fast_ok) HIPCHK(launch_causal_pcr_setup(c->N, nt, I.nv, I.cols, I.pcr, I.eta, st));
             else HIPCHK(launch_causal_march_setup(c->N, nt, I.nv, I.cols, I.pcr, I.eta, st));
             std::vector<double> eta((size_t)I.nv * ld);
@@ -1390,9 +1448,9 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
         if (I.path == 3 && ns > kDenseMaxSlots) I.path = 0;
         if (I.path == 3) {
             if (!I.Minv) {
-                ALLOC_LIVE(I.Minv, (size_t)I.nv * ns * ns);
-                ALLOC_LIVE(I.Mwork, (size_t)I.nv * ns * ns);
-                ALLOC_LIVE(I.piv, I.nv);
+                ALLOC(I.Minv, (size_t)I.nv * ns * ns);
+                ALLOC(I.Mwork, (size_t)I.nv * ns * ns);
+                ALLOC(I.piv, I.nv);
             }
             HIPCHK(launch_c0_inverse(c->N, ns, nt, I.nv, I.cols, I.Mwork, I.Minv, I.piv, st));
         }
@@ -1402,12 +1460,12 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
     if (I.path == 1 || I.path == 2) {
         const int tb = I.path == 1 ? kNearTb : march_tb(c->N, I.levels);
         if (!c->dBase || c->base_tb < tb) {
-            ALLOC_LIVE(c->dBase, (size_t)B * ns * tb);
+            ALLOC(c->dBase, (size_t)B * ns * tb);
             c->base_tb = tb;
         }
         const int max_seg = (nt - 1) / kCausalSuper;
         if (!c->dFacc && max_seg > 0)
-            ALLOC_LIVE(c->dFacc, (size_t)max_seg * B * ns * kCausalSuper);
+            ALLOC(c->dFacc, (size_t)max_seg * B * ns * kCausalSuper);
         // super-blocks are the absolute windows [S, S + kCausalSuper); the
         // steps [a0, a1) of one of them take the contribution of the finished
         // super-blocks (steps < S) from one block-Toeplitz product, which
@@ -1441,7 +1499,7 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
         }
         return SWR_OK;
     }
-    if (!c->dFar) ALLOC_LIVE(c->dFar, (size_t)B * ns * kCausalTb);
+    if (!c->dFar) ALLOC(c->dFar, (size_t)B * ns * kCausalTb);
     for (int n0 = n_lo; n0 < n_hi; n0 += kCausalTb) {
         const int nb = std::min(kCausalTb, n_hi - n0);
         LttArgs l{};
@@ -1590,12 +1648,12 @@ static swr_status pipe_resources(swr_ctx* c, int K) {
     if (!c->s2) HIPCHK(hipStreamCreateWithFlags(&c->s2, hipStreamNonBlocking));
     if (!c->s3) HIPCHK(hipStreamCreateWithFlags(&c->s3, hipStreamNonBlocking));
     const size_t st_rec = (size_t)2 * c->P * kWave;
-    if (!c->dStateB) ALLOC_LIVE(c->dStateB, (size_t)c->nBuild * st_rec);
-    if (!c->dStateF) ALLOC_LIVE(c->dStateF, (size_t)c->nSub * st_rec);
-    if (!c->dHistB && conv_hist(c->tr)) ALLOC_LIVE(c->dHistB, (size_t)c->nBuild * 2 * (c->nt + 1));
+    if (!c->dStateB) ALLOC(c->dStateB, (size_t)c->nBuild * st_rec);
+    if (!c->dStateF) ALLOC(c->dStateF, (size_t)c->nSub * st_rec);
+    if (!c->dHistB && conv_hist(c->tr)) ALLOC(c->dHistB, (size_t)c->nBuild * 2 * (c->nt + 1));
     if (c->tr >= SWR_P22) {
-        if (!c->dPadeStB) ALLOC_LIVE(c->dPadeStB, (size_t)c->nBuild * 6 * kWave);
-        if (!c->dPadeStF) ALLOC_LIVE(c->dPadeStF, (size_t)c->nSub * 6 * kWave);
+        if (!c->dPadeStB) ALLOC(c->dPadeStB, (size_t)c->nBuild * 6 * kWave);
+        if (!c->dPadeStF) ALLOC(c->dPadeStF, (size_t)c->nSub * 6 * kWave);
     }
     // sync events: fork, build j, causal j, join; timing events: 2 per sweep
     // launch plus the two ends of the interface solve
@@ -1808,7 +1866,7 @@ extern "C" swr_status swr_solve(swr_ctx* c, const double* u0d, double* uT, doubl
     if (snaps) {
         const size_t need = (size_t)c->B * nsnaps(c) * c->N * 2;
         if (c->snap_ends_size < need) {
-            ALLOC_LIVE(c->dSnapEnds, need);
+            ALLOC(c->dSnapEnds, need);
             c->snap_ends_size = need;
         }
     }
@@ -2002,6 +2060,7 @@ extern "C" swr_status swr_apply_R_noalloc(swr_ctx* c, const double* u0, const do
     auto* word = reinterpret_cast<unsigned long long*>(base);
     cd* dEnds = reinterpret_cast<cd*>(base + 256);
     cd* dHist = dEnds + ends;
+    c->tfac_shown = true;
     if (c->vk == SWR_V_STATIC) CHK(run_factor(c, c->dV, c->nv, c->L, false));
     else CHK(run_factor(c, nullptr, 1, c->L0, false));
     SweepIO io;
@@ -2105,7 +2164,7 @@ static bool store_schedule(const swr_ctx* c, const char* path, double ms) {
 
 extern "C" swr_status swr_tune(swr_ctx* c, const double* u0, double budget_ms, swr_schedule* chosen) {
     if (!c || !u0 || !(budget_ms > 0)) return SWR_EINVAL;
-    if (!c->dUT) ALLOC_LIVE(c->dUT, (size_t)c->B * c->nx);
+    if (!c->dUT) ALLOC(c->dUT, (size_t)c->B * c->nx);
     double* uT = reinterpret_cast<double*>(c->dUT);
     // candidate values (the current schedule first)
     std::vector<int> pipes{c->pipe_chunk}, helps{c->help_max}, restarts{c->o.restart}, graphs{c->graph},
@@ -2333,15 +2392,15 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
     hipStream_t st = c->st;
     if (!c->dCkpt) {
         c->Jc = (c->nt + kWave - 1) / kWave;
-        ALLOC_LIVE(c->dCkpt, (size_t)c->nSub * (c->Jc + 1) * c->P * kWave);
-        ALLOC_LIVE(c->dSeg, (size_t)c->nSub * kWave * c->P * kWave);
-        ALLOC_LIVE(c->dBsum, (size_t)c->nSub * 2 * c->nt);
-        ALLOC_LIVE(c->dGfwd, vec);
-        ALLOC_LIVE(c->dDadj, vec);
-        ALLOC_LIVE(c->dGadj, vec);
-        ALLOC_LIVE(c->dGends, (size_t)c->B * c->N * 2);
-        ALLOC_LIVE(c->dWends, (size_t)c->B * c->N * 2);
-        ALLOC_LIVE(c->dUT, (size_t)c->B * c->nx);
+        ALLOC(c->dCkpt, (size_t)c->nSub * (c->Jc + 1) * c->P * kWave);
+        ALLOC(c->dSeg, (size_t)c->nSub * kWave * c->P * kWave);
+        ALLOC(c->dBsum, (size_t)c->nSub * 2 * c->nt);
+        ALLOC(c->dGfwd, vec);
+        ALLOC(c->dDadj, vec);
+        ALLOC(c->dGadj, vec);
+        ALLOC(c->dGends, (size_t)c->B * c->N * 2);
+        ALLOC(c->dWends, (size_t)c->B * c->N * 2);
+        ALLOC(c->dUT, (size_t)c->B * c->nx);
     }
     int it_f = 0, it_b = 0;
     // ---- forward: factor, impulses + d, interface solve, final sweep with
