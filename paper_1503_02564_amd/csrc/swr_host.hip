@@ -264,14 +264,16 @@ static void* raw_alloc(const swr_ctx* c, size_t bytes) {
     return nullptr;
 }
 
-static void dfree(swr_ctx* c, void* p) {
-    for (auto it = c->allocs.begin(); it != c->allocs.end(); ++it)
+template <class T>
+static void dfree(swr_ctx* c, T*& p) {
+    for (auto it = c->allocs.begin(); p && it != c->allocs.end(); ++it)
         if (it->first == p) {
             hipFree(p);
             c->held -= it->second;
             c->allocs.erase(it);
-            return;
+            break;
         }
+    p = nullptr;
 }
 
 // the records of V(t,x) make room: the sweeps refactor from here on
@@ -279,7 +281,6 @@ static swr_status drop_records(swr_ctx* c) {
     if (!c->dTfac) return SWR_OK;
     HIPCHK(hipStreamSynchronize(c->st));
     dfree(c, c->dTfac);
-    c->dTfac = nullptr;
     c->tsteps = 0;
     return SWR_OK;
 }
@@ -1181,6 +1182,12 @@ static swr_status run_gmres(swr_ctx* c, const Op& A, const cd* rhs, cd* x, int* 
             c->dPart = part;
             c->part_out = m + 2;
         }
+        // (the last restart's are released first, and gm_m names no restart until
+        // all of the new ones are there: swr_tune goes on after a refusal)
+        c->gm_m = 0;
+        for (cd** p : {&c->dBasis, &c->dW, &c->dH, &c->dCs, &c->dSn, &c->dE, &c->dHp, &c->dHp2, &c->dY})
+            dfree(c, *p);
+        dfree(c, c->dResHist);
         ALLOC(c->dBasis, (size_t)(m + 1) * B * M);
         ALLOC(c->dW, (size_t)B * M);
         ALLOC(c->dH, (size_t)B * (m + 1) * m);

@@ -61,3 +61,38 @@ def test_restart_raised_after_setup(dev, tmp_path, vkind, how):
     assert got[2] == want[2]
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
     assert np.array_equal(got[3], want[3])
+
+
+def test_a_refused_restart_leaves_the_context_usable(dev, monkeypatch):
+    """swr_tune goes on to other candidates after one without room: a restart
+    whose basis is refused leaves no half of a workspace behind, and restarts
+    tried one after the other do not pile up."""
+    import torch
+    from paper_1503_02564_amd import swr
+    wl = W.small_case(J=[12] * 40, nt=64, trans=W.S02, B=2, seed=13, a0=-12.0, b0=12.0)
+    o = swr.swr_default_opts()
+    o.batch, o.restart, o.tol, o.solver = wl.B, 8, 1e-12, swr.SWR_SOLVER_GMRES
+    # a basis of 101 vectors takes 16 MB, one of 4001 640 MB
+    monkeypatch.setenv("SWR_DEBUG_ALLOC_LIMIT", str(64 << 20))
+    pb = swr.Problem(wl.a0, wl.b0, tuple(int(j) for j in wl.J), wl.dt, wl.dt * wl.nt, wl.vkind, wl.trans,
+                     wl.sigma, o, to_dev(np.asarray(wl.V, np.float64)))
+    u0 = to_dev(wl.u0)
+
+    def solve():
+        uT = torch.zeros_like(u0)
+        st, _ = swr.swr_solve(pb.ctx, u0, uT)
+        assert st == swr.SWR_OK
+        return to_np(uT)
+
+    first = solve()
+    say("restart refused")
+    swr.swr_set_schedule(pb.ctx, restart=4000)
+    with pytest.raises(swr.SwrError) as e:
+        solve()
+    assert e.value.status == swr.SWR_ENOMEM
+    swr.swr_set_schedule(pb.ctx, restart=8)
+    assert np.array_equal(solve(), first)
+    for k in range(8):
+        swr.swr_set_schedule(pb.ctx, restart=100 + k % 2)
+        solve()
+    pb.close()
