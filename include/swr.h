@@ -169,10 +169,10 @@ typedef struct {
  * bound; the GMRES restart changes the iterate, not the tolerance met). */
 typedef struct {
     int pipeline;     /* pipeline chunk of the static causal solve, 0 = staged */
-    int help_max;     /* S0^2 sweeps of V(t,x) that refactor in every step (more than 240 tasks):
-                         launches of at most this many tasks give every task a second wave that
-                         sums the far boundary history (the other sweeps form it on the matrix
-                         cores themselves) */
+    int help_max;     /* S0^2 sweeps of V(t,x) that refactor in every step (more than 240 tasks,
+                         or no room for factor records): launches of at most this many tasks
+                         give every task a second wave that sums the far boundary history (the
+                         other sweeps form it on the matrix cores themselves) */
     int restart;      /* GMRES restart length */
     int pair_from;    /* 1 or more; kept and reported, no launch depends on it (the static sweep
                          chooses how many tasks share a wave from the problem's sizes) */
@@ -294,10 +294,10 @@ swr_status swr_set_potential(swr_ctx* ctx, const double* V);
 
 /* The autotuner: times candidate schedules (pipeline chunks 0, 128, 256, 512,
  * 1024 for the static causal solve; helper-wave bounds 0, 512, all for S0^2
- * with V(t,x) or |u|^2; graph replay on and off for the static causal solve; restarts 20, 30, 60,
+ * with V(t,x) that refactors in every step, where they are different launches;
+ * graph replay on and off for the static causal solve; restarts 20, 30, 60,
  * 120 and residual read-back periods 1, 4, 16 for GMRES and the V(t,x)
- * iteration) with full
- * solves of the caller's u0 [B][nx] (one warm-up and the best of two timed
+ * iteration) with full solves of the caller's u0 [B][nx] (one warm-up and the best of two timed
  * solves each), until budget_ms of wall time is spent, and keeps the fastest
  * on the context.  With opts.tune_cache the choice is written to that file
  * under a key of the problem's shape (sizes, batch, potential kind,

@@ -2183,9 +2183,16 @@ extern "C" swr_status swr_tune(swr_ctx* c, const double* u0, double budget_ms, s
     if (c->vk == SWR_V_STATIC && c->o.solver == SWR_SOLVER_CAUSAL)
         for (int p : {0, 128, 256, 512, 1024})
             if (p < c->nt && std::find(pipes.begin(), pipes.end(), p) == pipes.end()) pipes.push_back(p);
-    if (c->tr == SWR_S02 && c->vk != SWR_V_STATIC)
+    // (only V(t,x) that refactors has helper waves; bounds between the same
+    // launch sizes are one schedule)
+    auto helped = [c](int h) {
+        return std::count_if(c->runs_sub.begin(), c->runs_sub.end(),
+                             [h](const WidthRun& r) { return r.P <= kMaxP && r.count <= h; });
+    };
+    if (c->tr == SWR_S02 && c->vk == SWR_V_TIME && !c->dTfac)
         for (int h : {0, kHelpMaxTasks, 1 << 30})
-            if (std::find(helps.begin(), helps.end(), h) == helps.end()) helps.push_back(h);
+            if (std::none_of(helps.begin(), helps.end(), [&](int x) { return helped(x) == helped(h); }))
+                helps.push_back(h);
     if (c->o.solver == SWR_SOLVER_GMRES || c->vk == SWR_V_TIME)
         for (int m : {20, 30, 60, 120})
             if (std::find(restarts.begin(), restarts.end(), m) == restarts.end()) restarts.push_back(m);
