@@ -210,10 +210,10 @@ struct swr_ctx {
     struct GraphKey {
         const void* u0;
         void *uT, *g, *tr, *sn;
-        int pipe, help, pair, group, vver;
+        int pipe, vver;
         bool operator==(const GraphKey& o) const {
             return u0 == o.u0 && uT == o.uT && g == o.g && tr == o.tr && sn == o.sn && pipe == o.pipe &&
-                   help == o.help && pair == o.pair && group == o.group && vver == o.vver;
+                   vver == o.vver;
         }
     } g_key{};
     // arguments of the last uncaptured static causal solve that succeeded:
@@ -1772,8 +1772,8 @@ static swr_status run_static_pipelined(swr_ctx* c, const cd* u0, cd* g, const Sw
 // ---------------------------------------------------------------------------
 static swr_ctx::GraphKey graph_key(const swr_ctx* c, const double* u0, double* uT, double* g,
                                    double* tr, double* sn) {
-    return swr_ctx::GraphKey{u0, uT, g, tr, sn, c->pipe_chunk, c->help_max, c->pair_from, c->group,
-                             c->v_version};
+    // (of the schedule, only the pipeline chunk changes a static solve's launches)
+    return swr_ctx::GraphKey{u0, uT, g, tr, sn, c->pipe_chunk, c->v_version};
 }
 
 static bool graph_ready(const swr_ctx* c, const swr_ctx::GraphKey& key) {
