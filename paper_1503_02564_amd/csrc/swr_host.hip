@@ -27,6 +27,7 @@
 
 #include "swr.h"
 #include "swr_common.h"
+#include "swr_rows_plan.h"
 
 
 using namespace swr;
@@ -64,19 +65,6 @@ struct Iface {
 // no longer runs with the registers and padded rows of the widest one.
 struct WidthRun {
     int P, start, count;
-};
-
-// Row form of the static sweep (swr_sweep_rows_kernel.h): the workgroups of a
-// task list that one kernel runs, whatever their widths.
-struct RowsRun {
-    int kind;             // RowsKind
-    int pmax;             // widest of them (LDS size)
-    int start, count;     // in the list's item table
-};
-struct RowsList {
-    std::vector<int4> host;
-    int4* dev = nullptr;
-    std::vector<RowsRun> runs;
 };
 
 struct swr_ctx {
@@ -454,80 +442,6 @@ static std::vector<cd> pade_coefficients(int m, double theta) {
     return out;
 }
 
-// Wide form: waves per task for a subdomain of at most 64 Pk nodes (Pk > kMaxP),
-// 0 past its sizes.  More waves than needed for 5 to 9 nodes per lane only add
-// exchanges; fewer would not hold the state in registers.
-static int wide_waves(int Pk) { return Pk <= 18 ? 2 : Pk <= 36 ? 4 : Pk <= 8 * kWideMaxP ? 8 : 0; }
-
-// ---------------------------------------------------------------------------
-// Row form of the static sweep: how many rows of 16 lanes a task of each
-// subdomain gets.  Fewer rows put more tasks in a wave and cost less per task
-// (each step's separator reduction, boundary terms and lane moves are shared by
-// the wave's tasks), but need more tasks to fill the GPU and more registers
-// per lane; wide tasks keep their interior coefficients in LDS, one copy per
-// workgroup, which wants tasks that share a record.  The choice depends on
-// the problem's sizes only, never on the schedule, so every schedule computes
-// the same bits.
-// ---------------------------------------------------------------------------
-static void rows_plan(swr_ctx* c, size_t ntasks, int sharing) {
-    c->rows.assign(c->N, 0);
-    c->wide.assign(c->N, 0);
-    c->rstride = c->wstride = 0;
-    c->stream_static = false;
-    const bool shared = sharing >= 4;
-    for (int k = 0; k < c->N; ++k) {
-        const int n = c->J[k] + 1;
-        if (n > kWave * kMaxP) {
-            const int NW = wide_waves(c->Pk[k]);
-            if (NW == 0) { c->stream_static = true; continue; }
-            const int P = (c->Pk[k] + NW - 1) / NW;
-            c->wide[k] = P + 32 * NW;
-            c->wstride = std::max(c->wstride, wide_record(P, NW));
-            continue;
-        }
-        int RW = 4;
-        if (n <= 128) {
-            if (ntasks >= kRowsFill1) RW = 1;
-        } else if (n <= 224 && shared && ntasks >= kRowsFill1Lds) {
-            RW = 1;
-        } else if (n <= 256) {
-            if (ntasks >= kRowsFill2) RW = 2;
-        } else if (shared && ntasks >= kRowsFill2Lds) {
-            RW = 2;
-        }
-        const int T = 16 * RW, P = (n + T - 1) / T;
-        c->rows[k] = P + 32 * RW;
-        c->rstride = std::max(c->rstride, (size_t)rows_fields(P, RW) * T);
-    }
-}
-
-// the workgroups of a task list (its order: width, then factor record).  A
-// workgroup takes the tasks of one width that fit its waves; with the record
-// in LDS, of one record.
-static void rows_items(const swr_ctx* c, const std::vector<Task>& list, RowsList& out) {
-    for (int kind = 0; kind < kRowsKinds; ++kind) {
-        RowsRun run{kind, 0, (int)out.host.size(), 0};
-        const RowsKind& rk = kRowsKind[kind];
-        const int cap = c->o.plain ? 1 : rk.waves * (4 / rk.RW);
-        for (size_t i = 0; i < list.size();) {
-            const int key = c->rows[list[i].k], P = key % 32;
-            if (key == 0 || key / 32 != rk.RW || (P >= kRowsLdsP) != rk.lds) { ++i; continue; }
-            size_t j = i + 1;
-            while (j < list.size() && (int)(j - i) < cap && c->rows[list[j].k] == key &&
-                   (!rk.lds || list[j].f == list[i].f))
-                ++j;
-            out.host.push_back(make_int4((int)i, (int)(j - i), P, 0));
-            run.pmax = std::max(run.pmax, P);
-            i = j;
-        }
-        run.count = (int)out.host.size() - run.start;
-        // widest first: the longest workgroups start first
-        std::stable_sort(out.host.begin() + run.start, out.host.end(),
-                         [](const int4& x, const int4& y) { return x.z > y.z; });
-        if (run.count) out.runs.push_back(run);
-    }
-}
-
 static swr_status fill_context(swr_ctx* c, const int* J, const double* V);
 
 extern "C" swr_status swr_setup(double a0, double b0, int N, const int* J, double dt, double T,
@@ -610,19 +524,24 @@ static swr_status fill_context(swr_ctx* c, const int* J, const double* V) {
     const int nt = c->nt, B = c->B, ns = c->ns, nv = c->nv;
     c->Pk.resize(N);
     for (int k = 0; k < N; ++k) c->Pk[k] = (J[k] + 1 + kWave - 1) / kWave;
-    // task lists, each ordered by chunk width (widest first; stable within a width)
+    // task lists (ordered by sort_tasks)
     std::vector<Task> build = impulse_tasks(N, nv), sub, imp0 = impulse_tasks(N, 1);
     for (int b = 0; b < B; ++b)
         for (int k = 0; k < N; ++k) build.push_back(Task{k, b, vof(c, b) * N + k, T_DATA_U0 | T_OUT_G});
     for (int b = 0; b < B; ++b)
         for (int k = 0; k < N; ++k) sub.push_back(Task{k, b, vof(c, b) * N + k, 0});
-    // ordered by width, then by factor record, so that tasks sharing a record
-    // are neighbours
+    if (tr == SWR_ROBIN || tr == SWR_S02) {
+        // (V(t,x), |u|^2: one task per wave, the form that their sweeps have)
+        const bool st = vk == SWR_V_STATIC;
+        RowsPlan p = rows_plan(c->J, c->Pk, st ? build.size() + sub.size() : 0, st && nv == 1 ? B : 0);
+        c->rows = std::move(p.rows);
+        c->wide = std::move(p.wide);
+        c->rstride = p.rstride;
+        c->wstride = p.wstride;
+        c->stream_static = p.streams;
+    }
     auto by_width = [c](std::vector<Task>& list, std::vector<WidthRun>& runs) {
-        std::stable_sort(list.begin(), list.end(), [c](const Task& x, const Task& y) {
-            if (c->Pk[x.k] != c->Pk[y.k]) return c->Pk[x.k] > c->Pk[y.k];
-            return x.f < y.f;
-        });
+        sort_tasks(list, c->Pk, c->rows);
         runs.clear();
         for (int i = 0; i < (int)list.size(); ++i) {
             const int P = c->Pk[list[i].k];
@@ -633,12 +552,10 @@ static swr_status fill_context(swr_ctx* c, const int* J, const double* V) {
     by_width(build, c->runs_build);
     by_width(sub, c->runs_sub);
     by_width(imp0, c->runs_L0);
-    if (tr == SWR_ROBIN || tr == SWR_S02) {
-        // (V(t,x), |u|^2: one task per wave, the form that their sweeps have)
-        rows_plan(c, vk == SWR_V_STATIC ? build.size() + sub.size() : 0, vk == SWR_V_STATIC && nv == 1 ? B : 0);
-        if (vk == SWR_V_STATIC) rows_items(c, build, c->rows_build);
-        else rows_items(c, imp0, c->rows_L0);
-        rows_items(c, sub, c->rows_sub);
+    if (!c->rows.empty()) {
+        if (vk == SWR_V_STATIC) rows_items(c->rows, build, o.plain, c->rows_build);
+        else rows_items(c->rows, imp0, o.plain, c->rows_L0);
+        rows_items(c->rows, sub, o.plain, c->rows_sub);
     }
     c->nBuild = (int)build.size();
     // default schedule; a tuning cache entry for this problem replaces it
@@ -696,8 +613,6 @@ static swr_status fill_context(swr_ctx* c, const int* J, const double* V) {
     ALLOC(c->dAct, B);
     // interface operator of the potential (static V) ...
     c->L.nv = nv;
-    c->L.tasks = c->dBuild;   // its impulse tasks lead the build list
-    c->L.ntasks = (int)impulse_tasks(N, nv).size();
     if (vk == SWR_V_STATIC) {
         if (c->rstride) ALLOC(c->L.rfac, (size_t)nv * N * c->rstride);
         else if (tr > SWR_S02) ALLOC(c->L.fac, (size_t)nv * N * fields * kWave);

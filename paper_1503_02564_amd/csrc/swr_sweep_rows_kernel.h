@@ -24,7 +24,7 @@
 //
 // Bound: FP64 issue.  Per step and wave about 26 instructions per node slot
 // (P) plus 130 to 190 that do not depend on P; a wave carries 4 / RW tasks, so
-// batches take fewer rows per task (rule in swr_host.hip).  Against one wave per
+// batches take fewer rows per task (rule in swr_rows_plan.h).  Against one wave per
 // task with a 64-lane reduction and one launch per width (before): 32 problems on
 // 500 uneven subdomains over 2000 steps 103.5 -> 75 ms per solve (67 with the
 // interface products' later forms), gradient of 16 potentials on 256 x 64 cells 148
