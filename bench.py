@@ -120,6 +120,7 @@ SWEEP_SOURCES = ("paper_1503_02564_amd/csrc/swr_rows.h",
                  "paper_1503_02564_amd/csrc/swr_lane.h",
                  "paper_1503_02564_amd/csrc/swr_sweep.hip",
                  "paper_1503_02564_amd/csrc/swr_common.h",
+                 "paper_1503_02564_amd/csrc/swr_rows_plan.h",
                  "paper_1503_02564_amd/csrc/swr_host.hip",
                  "paper_1503_02564_amd/build.py")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_kernel_batched_uneven_hbm.txt")

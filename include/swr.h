@@ -99,8 +99,9 @@ typedef enum {
     SWR_SOLVER_FIXED = 0,   /* fixed point g <- R g (Sec. 4 "Classical algorithm") */
     SWR_SOLVER_GMRES = 1,   /* restarted GMRES on (I - L) g = d (Sec. 4) */
     SWR_SOLVER_CAUSAL = 2,  /* exact forward substitution in time on (I - L) g = d; offered up to
-                               512 interface slots, or 513 subdomains when the per-step block
-                               system is block diagonally dominant (block PCR).  Beyond that the
+                               512 interface slots, or 1025 subdomains when the per-step block
+                               system is block diagonally dominant (block cyclic reduction up to
+                               64 interfaces, block elimination above).  Beyond that the
                                same system is solved by BiCGStab, and P^{-1} of the V_TIME /
                                V_CUBIC iterations by an inner BiCGStab to relative residual
                                1e-13 (the paper's way of applying P^{-1}, Sec. 5) */
@@ -201,11 +202,14 @@ void swr_default_opts(swr_opts* o);
  *   nonzero for Robin).
  *   opts: NULL for defaults.  stream: hipStream_t the work is enqueued on
  *   (NULL = default stream).  *out receives the context.
- * Errors: SWR_EINVAL for any violated condition above, tr beyond SWR_S02 with
- * a potential that is not STATIC, a nonzero-size
- * subdomain larger than the kernel's node bound (512 nodes per subdomain),
- * batch < 1, or CUBIC combined with batch > 1 problems of different V;
- * SWR_ENOMEM / SWR_EDEVICE on allocation / launch failure. */
+ * Errors: SWR_EINVAL for any violated condition above, an order-4 operator with
+ * CUBIC, a subdomain of more than 512 nodes with tr beyond SWR_S02 or of more
+ * than 524288 nodes, batch < 1, or v_per_problem with a potential that is not
+ * STATIC; SWR_ENOMEM / SWR_EDEVICE on allocation / launch failure (nothing is
+ * held then).  A V_TIME context of at most 240 (problem, subdomain) tasks keeps up
+ * to 4 GiB of factor records, at most a quarter of the memory that is free at
+ * setup, and gives them back when another of its buffers finds no room; its
+ * sweeps then refactor in every step (results equal to rounding). */
 swr_status swr_setup(double a0, double b0, int N, const int* J, double dt, double T,
                      int vk, const double* V, int tr, double s_re, double s_im,
                      const swr_opts* opts, void* stream, swr_ctx** out);

@@ -242,9 +242,10 @@ constexpr int kMaxP = 8;
 constexpr int kLongMaxQ = 8192;
 // default schedule: the S0^2 helper wave up to this many tasks per launch (every
 // wave then has a SIMD of its own); the static causal solve pipelined in
-// chunks of this many steps (measured on batched-uneven, whose sweeps fill the
-// GPU: 172 ms per solve pipelined, 175.5 ms staged, 202 ms with 128-step and
-// 176 ms with 512-step chunks)
+// chunks of this many steps (32 problems on 500 uneven subdomains, 2000 steps:
+// 66.5 ms per solve, staged 79.5; chunks of 128 steps 81.4, 192 79.7, 320 76.0,
+// 384 73.4, 512 69.4, 1024 73.0: chunks that straddle the 256-step super-blocks
+// split their launches, longer ones overlap less)
 constexpr int kHelpMaxTasks = 512;
 constexpr int kPipeChunk = 256;
 // V(t,x) with Robin or S0^2: up to this many (problem, subdomain) tasks the
@@ -257,7 +258,9 @@ constexpr int kPipeChunk = 256;
 constexpr int kTimeRecordTasks = 240;
 // ... and the memory of the records (at most a quarter of what is free, given
 // back when another buffer of the context needs it); longer windows are factored
-// piece by piece
+// piece by piece, anew for every sweep.  128 x 256 cells over 4000 steps, 17 GB
+// of records, a solve of 16 iterations: 326 ms in pieces, 483 refactoring, 239 with
+// all of them held (a bound that a context shares the card under, not the fastest).
 constexpr size_t kTimeRecordBytes = (size_t)4 << 30;
 // sweeps of V(t,x) and |u|^2 in the row form sum their S0^2 history in one
 // piece up to this many steps: 64 cycles of matrix instructions per 4 past
@@ -322,9 +325,9 @@ constexpr size_t kRowsFill2Lds = 4608;
 // S0^2: the time window is cut into super-chunks of this many steps for the
 // far history (the part of a block's far sum older than its super-chunk is
 // one batched Toeplitz product on the matrix cores per super-chunk; a
-// multiple of 256).  Measured on batched-uneven (32 problems, 2000 steps,
-// pipelined solve): 256 steps 146.1 ms, 512 steps 146.6 ms; the shorter one
-// keeps each lane's chain of recent terms shorter (at most 193 terms)
+// multiple of 256).  256 steps bound the terms that a sweep's block sums itself
+// by 320, the length of its beta window in LDS; 512 steps were no faster (146.6
+// against 146.1 ms, with the 64-lane sweeps that summed them lane by lane)
 constexpr int kFarSuper = 256;
 
 struct SweepArgs {

@@ -1598,8 +1598,8 @@ static swr_status run_static_pipelined(swr_ctx* c, const cd* u0, cd* g, const Sw
     // chunk boundaries: a short first chunk (64 steps) so the interface solve
     // starts early, then multiples of ch up to nt.  (A short last chunk, so
     // that the final sweep would end sooner after the interface solve, cost
-    // more in launches than it saved: 106.0 against 103.4 ms per
-    // batched-uneven solve, 3.62 against 3.56 ms on static-packet.)
+    // more in launches than it saved: with the 64-lane sweeps 106.0 against
+    // 103.4 ms per batched-uneven solve, 3.62 against 3.56 ms on static-packet.)
     std::vector<int> cut{0};
     auto push = [&](int x) { if (x > cut.back() && x < nt) cut.push_back(x); };
     push(kWave);

@@ -5,7 +5,7 @@
 // Bound: the chain of an inner iteration (nodal weights, chunk solve, reduction
 // over the lanes, convergence maxima), one wave per task.  128 x 256 cells, 600
 // steps: 4.1 ms a sweep in the 64-lane form with history on a second wave, 2.6 ms
-// now; the solve 44.1 -> 30.6 ms.
+// now; the solve 56.7 -> 30.4 ms (its iterations, so its time, depend on the data).
 #include "swr_sweep_rows_kernel.h"
 
 namespace swr {
