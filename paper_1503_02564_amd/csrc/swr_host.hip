@@ -61,8 +61,7 @@ struct Iface {
 // A run of tasks of one chunk width: tasks [start, start + count) of a task
 // list, whose subdomains all have P = ceil((J_k + 1) / 64) nodes per lane.
 // Every task list is ordered by width (widest first), so each width is one
-// launch of the sweep kernel instantiated for it: a subdomain of 41 nodes
-// no longer runs with the registers and padded rows of the widest one.
+// launch of the 64-lane sweep kernel instantiated for it.
 struct WidthRun {
     int P, start, count;
 };
@@ -2011,8 +2010,8 @@ extern "C" swr_status swr_apply_R_noalloc(swr_ctx* c, const double* u0, const do
 
 // ---------------------------------------------------------------------------
 // Schedule tuning.  The schedule parameters change no arithmetic of any
-// result (the pipelined and staged solves, and both sweep workgroup forms,
-// are bitwise equal; the GMRES restart changes the iterate, not the
+// result (the pipelined and staged solves, and sweeps with and without helper
+// waves, are bitwise equal; the GMRES restart changes the iterate, not the
 // tolerance it meets): pipeline chunk of the static causal solve, the task
 // bound of the S0^2 helper wave, the GMRES restart.  swr_tune times candidate
 // schedules on the caller's input and keeps the fastest; the tuning cache
