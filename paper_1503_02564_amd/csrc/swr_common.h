@@ -309,13 +309,16 @@ constexpr int kRowsLdsP = 9;         // widths from this on keep them in LDS
 //   up to 224 nodes, one row from LDS against two in registers: 201 nodes,
 //   8254 tasks 3.67 / 3.43, 16510 6.53 / 6.81, 33022 11.0 / 11.6 (251 nodes:
 //   16.5 / 14.9, so not there: 16 slots per lane spill)
-// A list that runs alone (swr_apply_R, the classical iteration) has about half of
-// those tasks and pays from there on; just above the line it still loses what
-// the solve gains (S0^2, 500 steps, fewer rows against four, sweep / solve of 400):
+// The lines are drawn for solves.  A list that runs alone (swr_apply_R, the
+// classical iteration) has about half of those tasks; just above the lines, and
+// with one potential per problem on uneven widths well above them, it loses what
+// the solve gains (S0^2, sweep of 500 and solve of 400 steps, fewer rows / four):
 //   one row:  101 nodes, 860 tasks of 3438 0.43 / 0.31 and 1.93 / 2.27 ms; 41 to 121
 //             nodes, 1200 of 2998 0.49 / 0.53 and 1.94 / 2.20; 65 nodes, 2000 of 7998 0.40 / 0.58
 //   two rows: 131 to 251 nodes, 1030 of 4118 0.53 / 0.59; 301 nodes from LDS, 2560 of
 //             5246 0.88 / 0.98 and 2.34 / 2.71; 301 to 501 nodes, 2400 of 4998 1.15 / 1.07
+//   both, 41 to 241 nodes, a potential per problem (sweep of 400 steps): 1600 of 6384
+//             0.98 / 0.59 and 2.58 / 3.28; 3000 of 11940 1.04 / 0.89 and 3.41 / 4.78
 // LDS forms want records shared by four tasks or more (one potential, batch >= 4).
 constexpr size_t kRowsFill1 = 2560;
 constexpr size_t kRowsFill1Lds = 12288;
