@@ -1198,7 +1198,9 @@ static swr_status run_bicgstab(swr_ctx* c, const Op& A, const cd* rhs, cd* x, in
     const long M = (long)c->ns * c->nt;
     const size_t vec = (size_t)B * M;
     hipStream_t st = c->st;
-    if (!c->dBi) {
+    if (!c->dBicg) {   // (the last of the group: a refusal leaves none of it in use)
+        dfree(c, c->dBi);
+        dfree(c, c->dCoef);
         ALLOC(c->dBi, 6 * vec);
         ALLOC(c->dCoef, (size_t)6 * B);
         ALLOC(c->dBicg, (size_t)B);
@@ -1328,7 +1330,6 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
     const int ver = (&I == &c->L) ? c->v_version : 0;
     if (I.dirty && I.built_version == ver) I.dirty = false;
     if (I.dirty) {
-        I.built_version = ver;
         I.path = 3;
         if (fast_ok || gen_ok) {
             const size_t rec = fast_ok ? causal_fast_rec() : (size_t)kMarchRows * ni;
@@ -1368,13 +1369,16 @@ static swr_status run_causal(swr_ctx* c, Iface& I, const cd* d, cd* g, hipStream
         // no dominance certificate and too many slots for a dense inverse
         if (I.path == 3 && ns > kDenseMaxSlots) I.path = 0;
         if (I.path == 3) {
-            if (!I.Minv) {
+            if (!I.piv) {
+                dfree(c, I.Minv);
+                dfree(c, I.Mwork);
                 ALLOC(I.Minv, (size_t)I.nv * ns * ns);
                 ALLOC(I.Mwork, (size_t)I.nv * ns * ns);
                 ALLOC(I.piv, I.nv);
             }
             HIPCHK(launch_c0_inverse(c->N, ns, nt, I.nv, I.cols, I.Mwork, I.Minv, I.piv, st));
         }
+        I.built_version = ver;   // (not before everything above is there)
         I.dirty = false;
     }
     if (I.path == 0) return kCausalOff;
@@ -2318,8 +2322,11 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
     const cd* u0 = reinterpret_cast<const cd*>(u0d);
     const size_t vec = (size_t)c->B * c->ns * c->nt;
     hipStream_t st = c->st;
-    if (!c->dCkpt) {
+    if (!c->dUT) ALLOC(c->dUT, (size_t)c->B * c->nx);
+    if (!c->dWends) {
         c->Jc = (c->nt + kWave - 1) / kWave;
+        for (cd** p : {&c->dCkpt, &c->dSeg, &c->dBsum, &c->dGfwd, &c->dDadj, &c->dGadj}) dfree(c, *p);
+        dfree(c, c->dGends);
         ALLOC(c->dCkpt, (size_t)c->nSub * (c->Jc + 1) * c->P * kWave);
         ALLOC(c->dSeg, (size_t)c->nSub * kWave * c->P * kWave);
         ALLOC(c->dBsum, (size_t)c->nSub * 2 * c->nt);
@@ -2328,7 +2335,6 @@ extern "C" swr_status swr_grad(swr_ctx* c, const double* u0d, const double* gbar
         ALLOC(c->dGadj, vec);
         ALLOC(c->dGends, (size_t)c->B * c->N * 2);
         ALLOC(c->dWends, (size_t)c->B * c->N * 2);
-        ALLOC(c->dUT, (size_t)c->B * c->nx);
     }
     int it_f = 0, it_b = 0;
     // ---- forward: factor, impulses + d, interface solve, final sweep with
